@@ -259,8 +259,8 @@ pf_status pf_filter2d_u8(int32_t c, int32_t h, int32_t w, int32_t r, int32_t shi
                          int32_t flags, void *stream);
 
 /* ---- single image with an explicit launch shape ----------------------------
- * The same computation as the call for `kind`/`variant`, with the launch
- * shape forced: rows_per_wave a multiple of 4 in 4..128, waves_per_group in
+ * The same computation as the call for `kind`/`variant`, bit for bit, on the
+ * strip kernel (the batch kernel's) with the launch shape forced: rows_per_wave a multiple of 4 in 4..128, waves_per_group in
  * {1, 2, 4, 8}. Used by the autotuner and by tests that check results do
  * not depend on the launch shape. kind PF_KIND_2D requires variant
  * PF_VAR_DIRECT; PF_KIND_SEP accepts all three variants. For PF_KIND_SEP,
@@ -279,7 +279,11 @@ pf_status pf_filter_f32_shaped(int32_t h, int32_t w, int32_t r, int32_t kind, in
  * (FP32 kinds only; four waves per workgroup; direct or separable
  * variant). Size classes: 0 small (< 256*256 px), 1 medium, 2 large
  * (> 1024*1024 px). A built-in default table is used until one is loaded.
- * Results depend on the variant only, never on the launch shape. */
+ * Results depend on the variant only, never on the launch shape. FP32
+ * single-image calls of the direct and separable variants run on LDS tiles
+ * whose size the library chooses by the image's; an FP32 entry's shape is
+ * that of the strip kernel, which runs PF_VAR_SEP_DIRECT (and images of a
+ * few columns and over 2^28 rows). */
 #define PF_TUNE_SINGLE 0
 #define PF_TUNE_BATCH  1
 
@@ -306,13 +310,13 @@ pf_status pf_tune_load(const char *path);
 pf_status pf_tune_save(const char *path);
 /* Measure, on the current device with hipEvents (median of 5 groups of
  * `reps` timed runs over buffers rotated through 1 GiB), for r in 0..r_max
- * and the three size
- * classes: every (rows_per_wave in {8, 16, 32, 64}, for PF_KIND_U8 also
- * 12, 20, 24 and 48, for the FP32 kinds also the heights up to 64 that fill
- * whole row chunks of the radius) x (waves_per_group in {1, 2, 4, 8}) shape of
- * single-image calls of every kind, and for
- * PF_KIND_SEP (r <= PF_SEP_DIRECT_R_MAX) also the PF_VAR_SEP_DIRECT variant
- * at the best shape, and for PF_KIND_U8 (r <= PF_U8_MFMA_R_MAX) also the
+ * and the three size classes: the FP32 kinds' single-image call (one
+ * candidate, no shape); for PF_KIND_SEP (r <= PF_SEP_DIRECT_R_MAX) also the
+ * PF_VAR_SEP_DIRECT variant at every (rows_per_wave in {8, 16, 32, 64} and
+ * the heights up to 64 that fill whole row chunks of the radius) x
+ * (waves_per_group in {1, 2, 4, 8}) shape; for PF_KIND_U8 every
+ * (rows_per_wave in {8, 12, 16, 20, 24, 32, 48, 64}) x (waves_per_group in
+ * {1, 2, 4, 8}) shape; for PF_KIND_U8 (r <= PF_U8_MFMA_R_MAX) also the
  * PF_VAR_MFMA variant at rows_per_wave in {16, 32, 48, 64} x
  * waves_per_group in {1, 2, 4, 8} within PF_U8_MFMA_TILE_MAX; and the
  * tile heights {8, 16, 32, 64} of the batch kernel on a batch of class

@@ -76,7 +76,9 @@ static pf_status check_f32_bufs(int32_t h, int32_t w, const float *in, const flo
     return PF_OK;
 }
 
-// fa: 2D taps or fx; fb: fy (separable kinds only).
+// fa: 2D taps or fx; fb: fy (separable kinds only). by > 0: the strip kernel
+// with that shape; by == 0: the tile kernel, which chooses its own (direct
+// and separable variants).
 static pf_status run_f32(int32_t h, int32_t w, int32_t r, int32_t kind, int var, int by, int wpg, const float *in,
                          const float *fa, const float *fb, float *out, int32_t flags, void *stream) {
     if (flags & ~PF_FLAG_EXACT) return fail(PF_EINVAL, "unknown flags");
@@ -90,7 +92,9 @@ static pf_status run_f32(int32_t h, int32_t w, int32_t r, int32_t kind, int var,
         if (overlap(fa, k * sizeof(float), out, bytes) || overlap(fb, k * sizeof(float), out, bytes))
             return fail(PF_EALIAS, "filter and output overlap (restrict)");
     }
-    hipError_t e = launch_f32(r, var, (flags & PF_FLAG_EXACT) != 0, in, fa, fb, out, h, w, by, wpg, (hipStream_t)stream);
+    const bool exact = (flags & PF_FLAG_EXACT) != 0;
+    hipError_t e = by > 0 ? launch_f32(r, var, exact, in, fa, fb, out, h, w, by, wpg, (hipStream_t)stream)
+                          : launch_tile(r, var == PF_VAR_SEPARABLE, exact, in, fa, fb, out, h, w, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return PF_OK;
 }
@@ -127,8 +131,8 @@ pf_status pf_filter2d_f32(int32_t h, int32_t w, int32_t r, const float *in, cons
     if (st) return st;
     if ((st = check_f32_bufs(h, w, in, out))) return st;
     const pf_tune_entry e = tune_lookup(PF_KIND_2D, r, (int64_t)h * w);
-    return run_f32(h, w, r, PF_KIND_2D, PF_VAR_DIRECT, e.rows_per_wave, e.waves_per_group, in, filt, nullptr, out, flags,
-                   stream);
+    return run_f32(h, w, r, PF_KIND_2D, PF_VAR_DIRECT, tile_fits(h, w) ? 0 : e.rows_per_wave, e.waves_per_group, in, filt,
+                   nullptr, out, flags, stream);
 }
 
 pf_status pf_filter_chain_f32(int32_t h, int32_t w, int32_t r, int32_t passes, int32_t border, const float *in,
@@ -247,7 +251,8 @@ pf_status pf_filter_sep_f32(int32_t h, int32_t w, int32_t r, const float *in, co
     // always runs the separable form.
     const bool exact = (flags & PF_FLAG_EXACT) != 0;
     const int var = (!exact && e.variant == PF_VAR_SEP_DIRECT) ? PF_VAR_SEP_DIRECT : PF_VAR_SEPARABLE;
-    return run_f32(h, w, r, PF_KIND_SEP, var, e.rows_per_wave, e.waves_per_group, in, fx, fy, out, flags, stream);
+    const int by = var == PF_VAR_SEPARABLE && tile_fits(h, w) ? 0 : e.rows_per_wave;
+    return run_f32(h, w, r, PF_KIND_SEP, var, by, e.waves_per_group, in, fx, fy, out, flags, stream);
 }
 
 pf_status pf_filter_f32_shaped(int32_t h, int32_t w, int32_t r, int32_t kind, int32_t variant, int32_t rows_per_wave,

@@ -23,6 +23,22 @@ hipError_t launch_f32(int r, int var, bool exact, const float *in, const float *
     }
 }
 
+hipError_t launch_tile(int r, bool sep, bool exact, const float *in, const float *fa, const float *fb, float *out,
+                       int h, int w, hipStream_t s) {
+    switch (r) {
+        case 0: return launch_tile_radius<0>(sep, exact, in, fa, fb, out, h, w, s);
+        case 1: return launch_tile_radius<1>(sep, exact, in, fa, fb, out, h, w, s);
+        case 2: return launch_tile_radius<2>(sep, exact, in, fa, fb, out, h, w, s);
+        case 3: return launch_tile_radius<3>(sep, exact, in, fa, fb, out, h, w, s);
+        case 4: return launch_tile_radius<4>(sep, exact, in, fa, fb, out, h, w, s);
+        case 5: return launch_tile_radius<5>(sep, exact, in, fa, fb, out, h, w, s);
+        case 6: return launch_tile_radius<6>(sep, exact, in, fa, fb, out, h, w, s);
+        case 7: return launch_tile_radius<7>(sep, exact, in, fa, fb, out, h, w, s);
+        case 8: return launch_tile_radius<8>(sep, exact, in, fa, fb, out, h, w, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 bool u8_variant_ok(int var, int r, int by, int wpg) {
     if (var == PF_VAR_DIRECT) return true;
     return var == PF_VAR_MFMA && r >= 1 && r <= PF_U8_MFMA_R_MAX && by % 16 == 0 && by * wpg <= PF_U8_MFMA_TILE_MAX;

@@ -184,7 +184,17 @@ pf_status fail_hip(hipError_t e, const char *what);
 void clear_error();
 
 // Launchers (kernels.hip). All validate nothing: callers have already.
-// fa: 2D taps (PF_VAR_DIRECT) or fx; fb: fy (ignored for PF_VAR_DIRECT).
+// Single-image calls on LDS tiles (tile.hip): fa: 2D taps (sep false) or
+// fx; fb: fy (ignored for 2D taps). tile_fits: the grid stays within the
+// 2^32 work items a launch dimension holds (images of a few columns and
+// hundreds of millions of rows do not; the strip kernel takes those).
+constexpr int kTileThreads = 256;
+inline bool tile_fits(int h, int w) {
+    return ((int64_t)w + 63) / 64 * (((int64_t)h + 15) / 16) * kTileThreads < ((int64_t)1 << 32);
+}
+hipError_t launch_tile(int r, bool sep, bool exact, const float *in, const float *fa, const float *fb, float *out,
+                       int h, int w, hipStream_t s);
+// The strip kernel with an explicit shape. fa: 2D taps (PF_VAR_DIRECT) or fx; fb: fy (ignored for PF_VAR_DIRECT).
 hipError_t launch_f32(int r, int var, bool exact, const float *in, const float *fa, const float *fb, float *out,
                       int h, int w, int by, int wpg, hipStream_t s);
 // var: PF_VAR_DIRECT (v_dot4) or PF_VAR_MFMA (int8 matrix cores, u8_mfma.hip).
@@ -241,7 +251,13 @@ void *batch_kernel_fn(int group, bool exact, int mask);
 template <int R>
 hipError_t launch_f32_radius(int var, bool exact, const float *in, const float *fa, const float *fb, float *out,
                              int h, int w, int by, int wpg, hipStream_t s);
+template <int R>
+hipError_t launch_tile_radius(bool sep, bool exact, const float *in, const float *fa, const float *fb, float *out,
+                              int h, int w, hipStream_t s);
 #define PF_DECL_RADIUS(R)                                                                                  \
+    template <>                                                                                            \
+    hipError_t launch_tile_radius<R>(bool sep, bool exact, const float *in, const float *fa,               \
+                                     const float *fb, float *out, int h, int w, hipStream_t s);            \
     template <>                                                                                            \
     hipError_t launch_f32_radius<R>(int var, bool exact, const float *in, const float *fa, const float *fb, \
                                     float *out, int h, int w, int by, int wpg, hipStream_t s);

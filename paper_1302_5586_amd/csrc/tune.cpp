@@ -434,13 +434,18 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
             // rotating buffer sets of one image (uint8: 3 planes)
             const int nb1 = (int)std::max<size_t>(1, std::min<size_t>(64, (big * 4 * nrot) / (px * planes * 4)));
             for (int r = 0; r <= r_max && st == PF_OK; ++r) {
-                // ---- single-image calls: every (rows, waves) shape
+                // ---- single-image calls. FP32: the tile kernel, which takes
+                // its own shape (the entry keeps the default one), and for
+                // separable filters the 2D-taps variant on the strip kernel
+                // at every (rows, waves) shape. uint8: every shape.
                 const pf_tune_entry dflt = default_entry(PF_TUNE_SINGLE, kind, r, sc);
                 pf_tune_entry best = dflt;
                 best.us = INFINITY;
-                const int var = kind == PF_KIND_SEP ? PF_VAR_SEPARABLE : PF_VAR_DIRECT;
+                const bool f32 = kind != PF_KIND_U8;
+                const int var = kind == PF_KIND_SEP ? PF_VAR_SEP_DIRECT : PF_VAR_DIRECT;
                 std::vector<std::pair<int, int>> shapes;
-                shapes.push_back({dflt.rows_per_wave, dflt.waves_per_group});
+                if (!f32 || (kind == PF_KIND_SEP && r <= PF_SEP_DIRECT_R_MAX))
+                    shapes.push_back({dflt.rows_per_wave, dflt.waves_per_group});
                 // The uint8 kernel is bound by ALU work and by how evenly its
                 // few waves spread over the SIMDs: finer tile heights too.
                 std::vector<int> cand(bys, bys + 4);
@@ -450,7 +455,8 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
                         if (std::find(cand.begin(), cand.end(), by) == cand.end()) cand.push_back(by);
                 for (int by : cand)
                     for (int wpg : wpgs)
-                        if (by != dflt.rows_per_wave || wpg != dflt.waves_per_group) shapes.push_back({by, wpg});
+                        if (!shapes.empty() && (by != dflt.rows_per_wave || wpg != dflt.waves_per_group))
+                            shapes.push_back({by, wpg});
                 auto time_single = [&](int v, int by, int wpg, float *us) -> pf_status {
                     if (kind == PF_KIND_U8) {
                         return time_launch(
@@ -464,14 +470,17 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
                     return time_launch(
                         [&](int i) {
                             const size_t o = (size_t)i * px;
+                            if (v != PF_VAR_SEP_DIRECT)
+                                return launch_tile(r, v == PF_VAR_SEPARABLE, false, in + o, filt, filt + (2 * r + 1),
+                                                   outb + o, h, w, s);
                             return launch_f32(r, v, false, in + o, filt, filt + (2 * r + 1), outb + o, h, w, by, wpg,
                                               s);
                         },
                         nb1, reps, 5, s, us);
                 };
-                // A default on another variant (uint8 on the matrix cores) is
-                // timed first, so that it keeps its place unless beaten by 3%.
-                if (dflt.variant != var) {
+                // The FP32 tile kernel, and a uint8 default on the matrix cores,
+                // are timed first: they keep their place unless beaten by 3%.
+                if (f32 || dflt.variant != var) {
                     float us = 0.0f;
                     st = time_single(dflt.variant, dflt.rows_per_wave, dflt.waves_per_group, &us);
                     if (st != PF_OK) break;
@@ -504,15 +513,6 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
                             }
                         }
                         if (st != PF_OK) break;
-                    }
-                }
-                // The variant axis: a separable filter may run as 2D taps.
-                if (st == PF_OK && kind == PF_KIND_SEP && r <= PF_SEP_DIRECT_R_MAX) {
-                    float us = 0.0f;
-                    st = time_single(PF_VAR_SEP_DIRECT, best.rows_per_wave, best.waves_per_group, &us);
-                    if (st == PF_OK && better(us, best)) {
-                        best.variant = PF_VAR_SEP_DIRECT;
-                        best.us = us;
                     }
                 }
                 if (st != PF_OK) break;

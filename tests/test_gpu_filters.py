@@ -407,3 +407,36 @@ def test_class_autotune_keeps_results(tmp_path):
                 assert np.array_equal(got, oracle.filter2d_u8(img, f8, 6)), "tuned u8 r=%d %dx%dx%d" % (r, c, h, w)
     finally:
         pf.tune_reset()
+
+
+# Sizes at the edges of the LDS tiles: 64 x 16 outputs per tile while all
+# tiles fit on the chip (2048 on 256 CUs), 128 x 16 (radii 0..3) or 64 x 32
+# (above) beyond; the last three shapes have more than 2048 small tiles.
+TILE_SHAPES = [(15, 64), (16, 63), (17, 65), (33, 129), (5, 3), (40, 4), (32784, 5), (32801, 2), (2, 131137)]
+
+
+@pytest.mark.parametrize("r", range(0, 9))
+def test_tiles_match_the_oracle_and_the_strip_kernel(r):
+    """At tile edges: exact mode bit for bit the oracle; both modes bit for
+    bit the strip kernel (same taps in the same order), which the batch
+    kernel shares."""
+    dev = device()
+    rng = np.random.default_rng(3000 + r)
+    f = _rand_filter(rng, r)
+    fx, fy = rng.standard_normal((2, 2 * r + 1)).astype(np.float32)
+    fd, fxd, fyd, f2 = _t(f, dev), _t(fx, dev), _t(fy, dev), _t(np.concatenate([fx, fy]), dev)
+    for h, w in TILE_SHAPES:
+        img = rng.standard_normal((h, w)).astype(np.float32)
+        img.flat[rng.integers(0, img.size)] = np.inf
+        x = _t(img, dev)
+        with np.errstate(invalid="ignore"):
+            ref2, refs = oracle.filter2d_f32(img, f), oracle.filter_sep_f32(img, fx, fy)
+        for exact in (False, True):
+            got2 = pf.filter2d(x, fd, exact=exact).cpu().numpy()
+            gots = pf.filter_sep(x, fxd, fyd, exact=exact).cpu().numpy()
+            strip2 = pf.filter_shaped(x, fd, r, pf.KIND_2D, pf.VAR_DIRECT, 16, 4, exact=exact).cpu().numpy()
+            strips = pf.filter_shaped(x, f2, r, pf.KIND_SEP, pf.VAR_SEPARABLE, 16, 4, exact=exact).cpu().numpy()
+            assert np.array_equal(got2, strip2, equal_nan=True), "2d r=%d %dx%d differs from the strip" % (r, h, w)
+            assert np.array_equal(gots, strips, equal_nan=True), "sep r=%d %dx%d differs from the strip" % (r, h, w)
+        assert np.array_equal(got2, ref2, equal_nan=True), "exact 2d r=%d %dx%d" % (r, h, w)
+        assert np.array_equal(gots, refs, equal_nan=True), "exact sep r=%d %dx%d" % (r, h, w)

@@ -43,6 +43,7 @@ DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-pa
 # batch-kernel group is its own object so that they build in parallel.
 VARIANTS = {
     "f32_inst.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(9)],
+    "chain.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(9)],
     "tile.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(9)],
     "batch_inst.hip": [("g%de%dm%d" % (g, e, m), ["-DPF_GROUP=%d" % g, "-DPF_EXACT=%d" % e, "-DPF_VMASK=%d" % m])
                        for g, m in ((0, 1), (0, 2), (0, 3)) for e in (0, 1)],

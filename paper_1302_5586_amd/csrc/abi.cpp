@@ -94,7 +94,8 @@ static pf_status run_f32(int32_t h, int32_t w, int32_t r, int32_t kind, int var,
     }
     const bool exact = (flags & PF_FLAG_EXACT) != 0;
     hipError_t e = by > 0 ? launch_f32(r, var, exact, in, fa, fb, out, h, w, by, wpg, (hipStream_t)stream)
-                          : launch_tile(r, var == PF_VAR_SEPARABLE, exact, in, fa, fb, out, h, w, (hipStream_t)stream);
+                          : launch_tile(r, var == PF_VAR_SEPARABLE, exact, in, fa, fb, out, h, w, PF_BORDER_CLAMP,
+                                        (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return PF_OK;
 }

@@ -1,53 +1,68 @@
-// Chains of 2D filter passes fused per tile, under four border rules.
+// Chains of 2D filter passes fused in one kernel, under four border rules;
+// one radius (PF_R, set by the build) per object.
 //
 // A chain applies the same (2r+1)^2 filter `passes` times; pass p reads the
 // FP32 image pass p-1 produced, with that image extended past its edges by
 // the border rule. Composing several stencil passes into one kernel is the
 // cross-component optimisation the paper motivates (Sec. II), for the
 // image-processing and fluid-dynamics stencil domains it names (Sec. I);
-// every pass keeps the independent-iteration semantics of Sec. II-B.3.
+// every pass keeps the independent-iteration semantics of Sec. II-B.3. Only
+// the input is read from HBM and only the last pass is written: 8 bytes per
+// pixel for the whole chain instead of 8 per pass.
 //
-// Design (time tiling in LDS): a workgroup owns a 64 x 32 output tile. It
-// loads the tile plus a halo of H = r * passes rows and columns once from
-// HBM, border-extended on load. Pass p computes, from the LDS image of pass
-// p-1, every in-image position within H - p*r of the tile, then writes the
-// border extension of its own result into the out-of-image positions of
-// that region (interior tiles have none). Reads of a pass therefore never
-// need index arithmetic for borders, and only the last pass goes to HBM:
-// 8 bytes of HBM traffic per pixel for the whole chain instead of 8 per
-// pass. The price is recomputing the halo ring, which shrinks by r per
-// pass.
+// Two forms, the same bits from both:
+//
+//  * Tiles (k_chain_tiles): a workgroup owns an output tile, stages it with
+//    a halo of H = R * passes in LDS, border-extended, and runs the passes
+//    between two LDS images. Pass p computes, from the image of pass p-1,
+//    every in-image position within H - p R of the tile; a tile at the
+//    image's edge then writes the border extension of that result. A thread
+//    takes 4 x Q outputs at a time, window rows in registers as in the tile
+//    kernel (tile.hip). Any size, radius and pass count.
+//  * Streams (k_chain_stream): a wave walks a strip of 256 columns down the
+//    image and runs every pass in registers: pass p folds each row of pass
+//    p-1 into a ring of 2R+1 row accumulators as the row is completed, so an
+//    input row costs each pass its multiply-adds and 2R lane shifts and
+//    nothing is staged, exchanged or waited for but the next input row. The
+//    strips cover the image but for a frame of at most 64 columns and 32
+//    rows, which workgroups at the end of the same launch compute as tiles.
 //
 // Arithmetic per output: taps in definition order (dy outer, dx inner,
 // ascending), one FMA per tap, or with EXACT a separate FP32 multiply and
 // add (built with -ffp-contract=off), which reproduces the sequential
 // program bit for bit at every pass.
-#include "dev_common.h"
-#include "pf_internal.h"
+//
+// What bounds it: large images, FP32 issue (and at one or two 3 x 3 passes
+// HBM); small ones, the passes' latency in one tile, about 0.9 us each at the
+// image's edge (LDS reads, a barrier, the extension, a barrier). The chain
+// before held one LDS image of 64 x 32 tiles, a pass's results in registers
+// over a barrier, 4 x 4 outputs per thread. Before -> now, us, three images
+// reused: 4 x (3 x 3) over 4096 x 4096 70 -> 30, over 1080 x 1920 24 -> 13,
+// over 64 x 64 20 -> 9; 8 x (5 x 5) over 4096 x 4096 281 -> 154; 5 x (7 x 7)
+// over 2160 x 2600 126 -> 90.
+#include "filter_body.h"
+
+#ifndef PF_R
+#error "PF_R must be defined"
+#endif
 
 namespace pf {
 namespace chain {
 
-constexpr int kTileX = 64, kTileY = 32, kThreads = 256;
+using dev::f4u;
+using dev::madd;
+using dev::static_for;
 
-// Source index of position i of an axis of n elements under a border rule;
-// -1 where the rule reads a zero.
-__device__ __forceinline__ int border_index(int i, int n, int border) {
-    if (i >= 0 && i < n) return i;
-    if (border == PF_BORDER_CLAMP) return i < 0 ? 0 : n - 1;
-    if (border == PF_BORDER_ZERO) return -1;
-    if (border == PF_BORDER_REFLECT) {  // period 2n, edge repeated: d c b a | a b c d | d c b a
-        const int p = 2 * n;
-        int m = i % p;
-        if (m < 0) m += p;
-        return m < n ? m : p - 1 - m;
-    }
-    if (n == 1) return 0;  // PF_BORDER_MIRROR: period 2n-2, edge not repeated
-    const int p = 2 * n - 2;
-    int m = i % p;
-    if (m < 0) m += p;
-    return m < n ? m : p - m;
-}
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 256;
+
+__host__ __device__ constexpr int ceil4(int v) { return (v + 3) / 4 * 4; }
+constexpr int pad_of(int r) { return ceil4(r); }
+constexpr int window_vecs(int r) { return 1 + pad_of(r) / 2; }
+// Buffer columns left of the tile: what the first pass's region and its
+// window reach. h: halo R * passes.
+__host__ __device__ constexpr int left_of(int r, int h) { return ceil4(h > r ? h - r : 0) + pad_of(r); }
 
 // Workgroup barrier that orders LDS only (a plain __syncthreads() also
 // waits for every global access in flight).
@@ -57,317 +72,448 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <bool EXACT>
-__device__ __forceinline__ float madd(float wgt, float x, float acc) {
-    if constexpr (EXACT) {
-        const float prod = wgt * x;
-        return acc + prod;
-    } else {
-        return __builtin_fmaf(wgt, x, acc);
-    }
-}
-
-
-// LDS layout: one image of (kTileY + 2H) rows and `pitch` floats per row.
-// Image column ox (= x0 - H) sits at buffer column pad(R), a multiple of 4
-// that is >= R, so the 4-output task at any 4-aligned buffer column c reads
-// its window [c - R, c + 3 + R] as 16-byte aligned LDS vectors starting at
-// c - pad(R), and consecutive lanes read consecutive 16-byte blocks (no
-// bank conflicts).
-__host__ __device__ constexpr int lds_pad(int r) { return 4 * ((r + 3) / 4); }
-__host__ __device__ constexpr int lds_pitch(int r, int halo) {
-    return (2 * lds_pad(r) + kTileX + 2 * halo + 4 + 3) / 4 * 4;
-}
-__host__ __device__ constexpr int lds_rows(int halo) { return kTileY + 2 * halo + 4; }
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-
-// Linear task index -> (row, column) over a rows x n grid, stepping by
-// kThreads without a division per step.
-struct Walk {
-    int row, col, drow, dcol, n;
-    __device__ __forceinline__ Walk(int start, int n_) : n(n_) {
-        row = start / n;
-        col = start - row * n;
-        drow = kThreads / n;
-        dcol = kThreads - drow * n;
-    }
-    __device__ __forceinline__ void next() {
-        row += drow;
-        col += dcol;
-        if (col >= n) {
-            col -= n;
-            ++row;
-        }
-    }
-};
-
-// Loads the rows x W0 input region at image (oy, ox) into the buffer
-// (region column c at buffer column PAD + c). A lane owns region columns
-// lane and lane + 64 (W0 <= 64 + 2 * PF_CHAIN_HALO_MAX), so their source
-// columns, border-mapped, are found once; wave v takes rows v, v + 4, ...,
-// eight rows (up to 16 loads per lane) in flight before any is waited for.
-// BORDER: some positions lie outside the image and read through the border
-// rule.
-template <bool BORDER>
-__device__ __forceinline__ void load_region(const float *__restrict__ in, float *buf, int h, int w, int oy, int ox,
-                                            int rows, int W0, int pitch, int pad, int border) {
-    constexpr int kRows = 8;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool two = lane + 64 < W0;
-    int sx0 = ox + lane, sx1 = ox + lane + 64;
-    if constexpr (BORDER) {
-        sx0 = border_index(sx0, w, border);
-        sx1 = border_index(sx1, w, border);
-    }
-    float *dst = buf + pad + lane;
-    for (int r0 = wave; r0 < rows; r0 += 4 * kRows) {
-        float v0[kRows], v1[kRows];
+// One tile: outputs [y0, ye) x [x0, xe), at most TY x TX of them. `first`
+// (0..3): the wave that takes a pass's first task; a pass of fewer tasks than
+// threads leaves whole waves idle, each on its own SIMD, so it moves on past
+// the waves the previous pass used. lds: 2 images of (TY + 2H + Q - 1) rows.
+template <int R, bool EXACT, int TX, int TY, int Q>
+__device__ __forceinline__ void chain_tile(const float *__restrict__ in, const float *__restrict__ filt,
+                                           float *__restrict__ out, int h, int w, int passes, int border, int x0,
+                                           int y0, int xe, int ye, int first, float *lds) {
+    constexpr int K = 2 * R + 1, PAD = pad_of(R), NB = window_vecs(R);
+    constexpr bool ALL = K * K <= 49;  // every tap stays in scalar registers
+    const int H = R * passes, LEFT = left_of(R, H);
+    const int pitch = TX + 2 * LEFT, rows = TY + 2 * H;
+    const int image = (rows + Q - 1) * pitch;  // floats of one LDS image
+    const bool interior = x0 >= LEFT && w - x0 >= TX + LEFT && y0 >= H && h - y0 >= TY + H;
+    float wt[ALL ? 1 : 2][ALL ? K * K : K];
+    load_taps(filt, wt[0]);
+    {
+        // Pass 0: rows y0 - H .., columns x0 - LEFT .., border-extended. LC
+        // lanes across a row.
+        constexpr int LC = TX + 2 * left_of(R, 16) <= 128 ? 32 : 64, LR = kThreads / LC, DEEP = 6;
+        const int c = 4 * (threadIdx.x % LC), r0 = threadIdx.x / LC;
+        const bool on = c < pitch;
+        if (interior) {
+            const float *src = in + (int64_t)(y0 - H) * w + (x0 - LEFT);
+            for (int b = 0; b < rows; b += DEEP * LR) {
+                f4 v[DEEP];
 #pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-            const int r = r0 + 4 * u;
-            int sy = oy + r;
-            if constexpr (BORDER) sy = border_index(sy, h, border);
-            const bool row_ok = r < rows && sy >= 0;
-            const float *src = in + (int64_t)sy * w;
-            v0[u] = v1[u] = 0.0f;
-            if (row_ok && (!BORDER || sx0 >= 0)) v0[u] = src[sx0];
-            if (row_ok && two && (!BORDER || sx1 >= 0)) v1[u] = src[sx1];
-        }
+                for (int u = 0; u < DEEP; ++u)
+                    if (on && b + r0 + LR * u < rows)
+                        v[u] = *reinterpret_cast<const f4u *>(src + (int64_t)(b + r0 + LR * u) * w + c);
 #pragma unroll
-        for (int u = 0; u < kRows; ++u) {
-            const int r = r0 + 4 * u;
-            if (r >= rows) break;
-            dst[r * pitch] = v0[u];
-            if (two) dst[r * pitch + 64] = v1[u];
-        }
-    }
-}
-
-// Tasks one thread holds in registers over a pass (a task: 4 x 4 outputs):
-// the largest pass region has at most kTileX / 4 + 2 * ceil((H - R) / 4) + 2
-// column blocks and (kTileY + 2 (H - R)) / 4 + 1 row blocks, H <=
-// PF_CHAIN_HALO_MAX.
-constexpr int kMaxTasks = ((kTileX / 4 + 2 * ((PF_CHAIN_HALO_MAX + 3) / 4) + 2) *
-                               ((kTileY + 2 * PF_CHAIN_HALO_MAX) / 4 + 1) +
-                           kThreads - 1) /
-                          kThreads;
-
-// The passes of one tile over its LDS image `buf` (pass 0 already in it):
-// buffer row 0 / column pad(R) holds image position (y0 - H, x0 - H).
-template <int R, bool EXACT>
-__device__ __forceinline__ void tile_passes(float *buf, int pitch, const float *__restrict__ filt,
-                                            float *__restrict__ out, int h, int w, int passes, int border, int x0,
-                                            int y0, bool interior, int first) {
-    constexpr int K = 2 * R + 1;
-    constexpr int PAD = lds_pad(R);
-    constexpr int NB = 1 + 2 * PAD / 4;  // 16-byte blocks per window row
-    const int H = R * passes;
-    const int ox = x0 - H, oy = y0 - H;
-    const int cx = PAD - ox;  // buffer column of image column x is x + cx
-    // The taps, loaded once: read inside the task loop, their scalar loads
-    // would share the LDS reads' wait counter and force a full wait in the
-    // middle of every task.
-    float wk[K * K];
+                for (int u = 0; u < DEEP; ++u)
+                    if (on && b + r0 + LR * u < rows)
+                        *reinterpret_cast<f4 *>(lds + (b + r0 + LR * u) * pitch + c) = v[u];
+            }
+        } else {
+            int xs[4];
 #pragma unroll
-    for (int i = 0; i < K * K; ++i) wk[i] = filt[i];
-    // A pass with fewer tasks than threads leaves whole waves idle, and each
-    // wave of the workgroup runs on its own SIMD: the wave that takes the
-    // pass's first tasks (`first`) therefore moves on past the waves the
-    // previous pass used, so that the passes' work spreads over the SIMDs.
-    // One LDS image: a pass computes its whole region into registers, and
-    // only after a barrier overwrites the previous pass's image with it.
-    for (int p = 1; p <= passes; ++p) {
-        const bool last = p == passes;
-        const int m = (passes - p) * R;  // reach of pass p's region beyond the tile
-        const int ylo = max(y0 - m, 0), yhi = min(y0 + kTileY + m, h);
-        const int xlo = max(x0 - m, 0), xhi = min(x0 + kTileX + m, w);
-        // Tasks: 4 x 4 outputs, rows from ylo in steps of 4, columns at
-        // 4-aligned buffer columns covering [xlo, xhi). Window reads stay
-        // inside the buffer: columns from c - PAD >= 0 (c >= xlo + cx >= PAD +
-        // H - m) to c + 3 + PAD < pitch, rows from ylo - R - oy >= H - m - R
-        // >= 0 to at most yhi + 3 + R - oy < rows (4 spare rows). Outputs
-        // outside [ylo, yhi) x [xlo, xhi) are computed from whatever the
-        // buffer holds there: the last pass does not store them, and task
-        // writes back to LDS (rows up to yhi + 2 - oy, columns up to c + 3)
-        // stay inside the buffer too.
-        const int cb0 = (xlo + cx) >> 2, cb1 = ((xhi - 1 + cx) >> 2) + 1;
-        const int ncb = cb1 - cb0, ntask = ((yhi - ylo + 3) >> 2) * ncb;
-        float res[kMaxTasks][4][4];
-        int at_y[kMaxTasks], at_c[kMaxTasks];
-        const int v = (threadIdx.x - 64 * first) & (kThreads - 1);  // this thread's place in task order
-        Walk t(v, ncb);
+            for (int k = 0; k < 4; ++k) xs[k] = border_index(x0 - LEFT + c + k, w, border);
+            for (int b = 0; b < rows; b += DEEP * LR) {
+                f4 v[DEEP];
 #pragma unroll
-        for (int u = 0; u < kMaxTasks; ++u) {
-            at_y[u] = ylo + 4 * t.row;
-            at_c[u] = 4 * (cb0 + t.col);
-            t.next();
-            if (v + u * kThreads >= ntask) continue;
-            const float *base = buf + (at_y[u] - R - oy) * pitch + (at_c[u] - PAD);
-            float acc[4][4];
+                for (int u = 0; u < DEEP; ++u) {
+                    const int r = b + r0 + LR * u;
+                    const int y = border_index(y0 - H + r, h, border);
+                    v[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+                    if (on && r < rows && y >= 0) {
+                        const float *src = in + (int64_t)y * w;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) acc[j][k] = 0.0f;
-            // Input row i of the window feeds output rows j = i - dy; rows
-            // come in ascending order, so each output takes dy ascending.
-#pragma unroll
-            for (int i = 0; i < 4 + 2 * R; ++i) {
-                float v[4 * NB];
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const f4 q = *reinterpret_cast<const f4 *>(base + i * pitch + 4 * b);
-                    v[4 * b] = q.x;
-                    v[4 * b + 1] = q.y;
-                    v[4 * b + 2] = q.z;
-                    v[4 * b + 3] = q.w;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int dy = i - j;
-                    if (dy < 0 || dy >= K) continue;
-#pragma unroll
-                    for (int dx = 0; dx < K; ++dx) {
-                        const float wt = wk[dy * K + dx];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) acc[j][k] = madd<EXACT>(wt, v[PAD - R + k + dx], acc[j][k]);
+                        for (int k = 0; k < 4; ++k)
+                            if (xs[k] >= 0) v[u][k] = src[xs[k]];
                     }
                 }
+#pragma unroll
+                for (int u = 0; u < DEEP; ++u)
+                    if (on && b + r0 + LR * u < rows)
+                        *reinterpret_cast<f4 *>(lds + (b + r0 + LR * u) * pitch + c) = v[u];
             }
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) res[u][j][k] = acc[j][k];
         }
-        if (last) {
+    }
+    __syncthreads();
+    float *cur = lds, *nxt = lds + image;
+    for (int p = 1; p <= passes; ++p) {
+        const bool last = p == passes;
+        const int m = (passes - p) * R;
+        const int ylo = max(y0 - m, 0), yhi = ye + min(m, h - ye);
+        const int xlo = max(x0 - m, 0), xhi = xe + min(m, w - xe);
+        // Tasks: 4 x Q outputs, rows from ylo in steps of Q, 4-aligned buffer
+        // columns covering [xlo, xhi). Window reads stay inside an image: rows
+        // from H - m - R >= 0 to at most TY + 2H + Q - 2, columns from
+        // LEFT - ceil4(m) - PAD >= 0 to TX + LEFT + ceil4(m) + PAD <= pitch.
+        // Outputs past the region are computed from whatever is there: the
+        // last pass does not store them, the next one reads none of them but
+        // the positions that the extension below rewrites first.
+        const int cb0 = (xlo - x0 + LEFT) >> 2, cb1 = (xhi - x0 + LEFT + 3) >> 2;
+        const int ncb = cb1 - cb0, ntask = ((yhi - ylo + Q - 1) / Q) * ncb;
+        const int v0 = (threadIdx.x - 64 * first) & (kThreads - 1);
+        int tr = v0 / ncb, tc = v0 - tr * ncb;
+        const int dr = kThreads / ncb, dc = kThreads - dr * ncb;
+        for (int t = v0; t < ntask; t += kThreads) {
+            const int row = ylo + Q * tr - (y0 - H), col = 4 * (cb0 + tc);
+            int at = (row - R) * pitch + col - PAD;
+            float acc[Q][4];
 #pragma unroll
-            for (int u = 0; u < kMaxTasks; ++u) {
-                if (v + u * kThreads >= ntask) continue;
-                const int x = at_c[u] - cx;
-                const bool full = x >= xlo && x + 3 < xhi;
+            for (int j = 0; j < Q; ++j)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int y = at_y[u] + j;
-                    if (y >= yhi) continue;
-                    float *o = out + (int64_t)y * w;
-                    if (full) {
-                        // One 16-byte store per row: a wave's lanes cover whole
-                        // cache lines (rows need only 4-byte alignment).
-                        f4u q;
-                        q.x = res[u][j][0];
-                        q.y = res[u][j][1];
-                        q.z = res[u][j][2];
-                        q.w = res[u][j][3];
-                        __builtin_nontemporal_store(q, reinterpret_cast<f4u *>(o + x));
+                for (int k = 0; k < 4; ++k) acc[j][k] = 0.0f;
+            float win[Q + 1][4 * NB];
+#pragma unroll
+            for (int j = 0; j < Q; ++j) load_window<NB>(cur + at + j * pitch, win[j]);
+            at += Q * pitch;
+            static_for<0, K>([&](auto dcst) __attribute__((always_inline)) {
+                constexpr int dy = decltype(dcst)::value;
+                if constexpr (!ALL) load_taps<K>(filt + (dy + 1 < K ? dy + 1 : 0) * K, wt[ALL ? 0 : (dy + 1) & 1]);
+                if constexpr (dy + 1 < K) {
+                    asm volatile("" : "+v"(at));
+                    load_window<NB>(cur + at, win[(dy + Q) % (Q + 1)]);
+                    at += pitch;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int dx = 0; dx < K; ++dx)
+#pragma unroll
+                    for (int j = 0; j < Q; ++j)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            acc[j][k] = madd<EXACT>(ALL ? wt[0][ALL ? dy * K + dx : 0] : wt[ALL ? 0 : dy & 1][dx],
+                                                    win[(dy + j) % (Q + 1)][PAD - R + k + dx], acc[j][k]);
+                end_step<Q>(acc);
+            });
+            if constexpr (!ALL) {
+                // K is odd: the next task's tap row 0 was loaded to slot 1.
+#pragma unroll
+                for (int i = 0; i < K; ++i) wt[0][i] = wt[1][i];
+            }
+            if (last) {
+                const int y = ylo + Q * tr, x = col - LEFT;  // relative to x0
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    if (y + j >= yhi) continue;
+                    float *o = out + (int64_t)(y + j) * w + x0 + x;
+                    if (x + 4 <= xhi - x0) {
+                        const f4u q = {acc[j][0], acc[j][1], acc[j][2], acc[j][3]};
+                        __builtin_nontemporal_store(q, reinterpret_cast<f4u *>(o));
                     } else {
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            if (x + k >= xlo && x + k < xhi) __builtin_nontemporal_store(res[u][j][k], o + x + k);
+                            if (x + k < xhi - x0) __builtin_nontemporal_store(acc[j][k], o + k);
                     }
                 }
+            } else {
+#pragma unroll
+                for (int j = 0; j < Q; ++j) {
+                    const f4 q = {acc[j][0], acc[j][1], acc[j][2], acc[j][3]};
+                    *reinterpret_cast<f4 *>(nxt + (row + j) * pitch + col) = q;
+                }
             }
-            break;
+            tr += dr;
+            tc += dc;
+            if (tc >= ncb) {
+                tc -= ncb;
+                ++tr;
+            }
         }
+        if (last) break;
         first = (first + ((ntask + 63) >> 6)) & 3;
-        lds_barrier();  // every read of the previous image is done
-        // Whole tasks go back to LDS, also their outputs outside the region:
-        // those positions lie inside the buffer (the bounds above), and the
-        // next pass reads none of them, except out-of-image positions, which
-        // the border extension below rewrites first.
-#pragma unroll
-        for (int u = 0; u < kMaxTasks; ++u) {
-            if (v + u * kThreads >= ntask) continue;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                f4 q;
-                q.x = res[u][j][0];
-                q.y = res[u][j][1];
-                q.z = res[u][j][2];
-                q.w = res[u][j][3];
-                *reinterpret_cast<f4 *>(buf + (at_y[u] + j - oy) * pitch + at_c[u]) = q;
-            }
-        }
         lds_barrier();
         if (!interior) {
-            // Border extension of pass p's image over the out-of-image
-            // positions that pass p+1 reads: those of its region within R of
-            // the image. Each source lies in the in-image part just written:
-            // a rule maps a position within R of an edge to within R of it
-            // (m >= R here), or wraps inside an image narrower than a tile,
-            // which a single tile covers.
-            const int ya = max(y0 - m, -R), yb = min(y0 + kTileY + m, h + R);
-            const int xa = max(x0 - m, -R), xb = min(x0 + kTileX + m, w + R);
-            Walk f(threadIdx.x, xb - xa);
-            for (int i = threadIdx.x; i < (yb - ya) * (xb - xa); i += kThreads, f.next()) {
-                const int y = ya + f.row, x = xa + f.col;
-                if (y >= 0 && y < h && x >= 0 && x < w) continue;
+            // Border extension of this pass's image: the positions outside the
+            // image that the next pass reads, those of its region within R of
+            // the image: whole rows above and below, then what is left and
+            // right of the rows between. Each source lies in the part just
+            // written: a rule maps a position within R of an edge to within R
+            // of it (m >= R here), or wraps inside an image narrower than a
+            // tile, which a single tile covers.
+            const int ya = max(y0 - m, -R), yb = ye + min(m, h - ye + R);
+            const int xa = max(x0 - m, -R), xb = xe + min(m, w - xe + R);
+            auto at = [&](int y, int x) -> float & { return nxt[(y - y0 + H) * pitch + x - x0 + LEFT]; };
+            const int nv = (ylo - ya) + (yb - yhi), wv = xb - xa;
+            for (int i = threadIdx.x; i < nv * wv; i += kThreads) {
+                const int r = i / wv, x = xa + i - r * wv;
+                const int y = r < ylo - ya ? ya + r : yhi + r - (ylo - ya);
                 const int yy = border_index(y, h, border), xx = border_index(x, w, border);
-                buf[(y - oy) * pitch + x + cx] = (yy < 0 || xx < 0) ? 0.0f : buf[(yy - oy) * pitch + xx + cx];
+                at(y, x) = (yy < 0 || xx < 0) ? 0.0f : at(yy, xx);
+            }
+            const int wc = (xlo - xa) + (xb - xhi), nc = yhi - ylo;
+            for (int i = threadIdx.x; i < nc * wc; i += kThreads) {
+                const int r = i / wc, c = i - r * wc, y = ylo + r;
+                const int x = c < xlo - xa ? xa + c : xhi + c - (xlo - xa);
+                const int xx = border_index(x, w, border);
+                at(y, x) = xx < 0 ? 0.0f : at(y, xx);
             }
             lds_barrier();
         }
+        float *sw = cur;
+        cur = nxt;
+        nxt = sw;
     }
 }
 
-template <int R, bool EXACT>
-__global__ __launch_bounds__(kThreads) void k_chain_f32(const float *__restrict__ in, const float *__restrict__ filt,
-                                                        float *__restrict__ out, int h, int w, int passes, int border,
-                                                        int tiles_x, int ntiles) {
-    constexpr int PAD = lds_pad(R);
-    extern __shared__ float lds[];
-    const int tile = xcd_remap(blockIdx.x, gridDim.x);
-    if (tile >= ntiles) return;
-    const int H = R * passes;
-    const int pitch = lds_pitch(R, H), rows = lds_rows(H);
-    const int W0 = kTileX + 2 * H;
-    const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    const int x0 = tx * kTileX, y0 = ty * kTileY;
-    const int ox = x0 - H, oy = y0 - H;
-    const bool interior = ox >= 0 && oy >= 0 && x0 + kTileX + H <= w && y0 + kTileY + H <= h;
-    // Pass 0: the input region, border-extended.
-    if (interior)
-        load_region<false>(in, lds, h, w, oy, ox, rows - 4, W0, pitch, PAD, border);
-    else
-        load_region<true>(in, lds, h, w, oy, ox, rows - 4, W0, pitch, PAD, border);
-    __syncthreads();
-    tile_passes<R, EXACT>(lds, pitch, filt, out, h, w, passes, border, x0, y0, interior, tile & 3);
+template <int R, bool EXACT, int TX, int TY, int Q>
+__global__ __launch_bounds__(kThreads) void k_chain_tiles(const float *__restrict__ in,
+                                                          const float *__restrict__ filt, float *__restrict__ out,
+                                                          int h, int w, int passes, int border, int tiles_x) {
+    extern __shared__ __align__(16) float lds[];
+    int tx, ty;
+    window_tile(blockIdx.x, gridDim.x, tiles_x, tx, ty);
+    const int x0 = tx * TX, y0 = ty * TY;
+    chain_tile<R, EXACT, TX, TY, Q>(in, filt, out, h, w, passes, border, x0, y0, x0 + min(TX, w - x0),
+                                    y0 + min(TY, h - y0), blockIdx.x & 3, lds);
 }
 
-template <int R, bool EXACT>
-hipError_t launch_r(const float *in, const float *filt, float *out, int h, int w, int passes, int border,
-                    hipStream_t s) {
+// ---------------------------------------------------------------- streams
+
+// What a stream launch covers: rows [ya, yb) x columns [xa, xb) in strips x
+// bands wave tiles of `by` rows; `frame` workgroups for the rest, fx tiles
+// per tile row above and below, then (1 + right) per tile row between.
+struct StreamPlan {
+    int xa, ya, xb, yb;
+    int strips, bands, by;
+    int frame, fx;
+};
+constexpr int kFrameX = 64, kFrameY = 32;  // a frame tile
+
+// DPP wavefront shifts that give 0 to the lane without a source lane (a halo
+// lane, whose values are not used): no register is set up first.
+__device__ __forceinline__ float from_left0(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_right0(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+
+// Folds one row of a pass's input, 4 columns per lane, into its ring of row
+// accumulators; RES: the row's number modulo K. Output row j collects rows
+// j .. j + 2R and lives in slot j mod K; the slot of the row's first tap
+// starts from 0.
+template <int R, bool EXACT, int RES>
+__device__ __forceinline__ void fold(const float (&wk)[(2 * R + 1) * (2 * R + 1)], const float (&v)[4],
+                                     float (&acc)[2 * R + 1][4]) {
+    constexpr int K = 2 * R + 1;
+    static_assert(R <= 4, "a window within the adjacent lanes");
+    float win[12];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        win[k] = from_left0(v[k]);
+        win[4 + k] = v[k];
+        win[8 + k] = from_right0(v[k]);
+    }
+#pragma unroll
+    for (int dy = -R; dy <= R; ++dy) {
+        const int slot = ((RES - R - dy) % K + K) % K;
+#pragma unroll
+        for (int dx = -R; dx <= R; ++dx)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                acc[slot][k] = madd<EXACT>(wk[(dy + R) * K + dx + R], win[4 + k + dx],
+                                           dy == -R && dx == -R ? 0.0f : acc[slot][k]);
+    }
+}
+
+// Passes p .. P - 1 for input row i of the strip (i = S modulo K): v, the row
+// pass p reads, becomes the row the last pass completes. A pass starts with
+// its first complete input row, 2R rows after the pass before it. One pass
+// at a time for the scheduler: interleaved, their windows cost 30 to 90 more
+// registers.
+template <int R, int P, bool EXACT, int S, int p>
+__device__ __forceinline__ void run_passes(const float (&wk)[(2 * R + 1) * (2 * R + 1)], float (&v)[4],
+                                           float (&acc)[P][2 * R + 1][4], int i) {
+    constexpr int K = 2 * R + 1;
+    if (p > 0 && i < 2 * R * p) return;
+    constexpr int RES = (S + p) % K;  // row i - 2R p of pass p's input
+    fold<R, EXACT, RES>(wk, v, acc[p]);
+    constexpr int done = (RES + 1) % K;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = acc[p][done][k];
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (p + 1 < P) run_passes<R, P, EXACT, S, p + 1>(wk, v, acc, i);
+}
+
+// Input rows in flight per wave: a multiple of K near 6 (9 at R = 1: 24 more
+// registers and 34.6 us against 30.1 us for 4 passes over 4096 x 4096). Each
+// row's register is loaded again as soon as its row is folded.
+constexpr int stream_rows(int r) { return (2 * r + 1) * (6 / (2 * r + 1) > 0 ? 6 / (2 * r + 1) : 1); }
+
+// One wave: outputs [y0, y0 + rows) x [x0, x0 + 256 - 8 IL), every halo row
+// and column inside the image.
+template <int R, int P, bool EXACT>
+__device__ __forceinline__ void stream_strip(const float *__restrict__ in, const float *__restrict__ filt,
+                                             float *__restrict__ out, int w, int x0, int y0, int rows, int lane) {
+    constexpr int K = 2 * R + 1, H = R * P, IL = (H + 3) / 4, CH = stream_rows(R);
+    float wk[K * K];
+    load_taps<K * K>(filt, wk);
+    float acc[P][K][4];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int s = 0; s < K; ++s)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[p][s][k] = 0.0f;
+    const bool out_lane = lane >= IL && lane < 64 - IL;
+    const int nin = rows + 2 * H;
+    const float *src = in + (int64_t)(y0 - H) * w + (x0 - 4 * IL);
+    float *dst = out + (int64_t)y0 * w + (x0 + 4 * (lane - IL));
+    const uint32_t col = 4 * lane;
+    f4 q[CH];
+#pragma unroll
+    for (int s = 0; s < CH; ++s) q[s] = *reinterpret_cast<const f4u *>(src + (int64_t)min(s, nin - 1) * w + col);
+    src += (int64_t)min(CH, nin - 1) * w;  // row i + CH, or the last one
+    for (int i0 = 0; i0 < nin; i0 += CH) {
+        static_for<0, CH>([&](auto sc) __attribute__((always_inline)) {
+            constexpr int s = decltype(sc)::value;
+            const int i = i0 + s;
+            float v[4] = {q[s].x, q[s].y, q[s].z, q[s].w};
+            q[s] = *reinterpret_cast<const f4u *>(src + col);
+            src += i + CH + 1 < nin ? w : 0;
+            run_passes<R, P, EXACT, s, 0>(wk, v, acc, i);
+            if (i >= 2 * H && i < nin && out_lane) {
+                const f4u t = {v[0], v[1], v[2], v[3]};
+                __builtin_nontemporal_store(t, reinterpret_cast<f4u *>(dst + (int64_t)(i - 2 * H) * w));
+            }
+        });
+    }
+}
+
+// The strips come first in the grid, four waves per workgroup, so that they
+// spread one workgroup per CU; the frame's tiles fill in behind them (frame
+// first, two strip workgroups share some CUs and the launch takes up to
+// twice as long).
+template <int R, int P, bool EXACT>
+__global__ __launch_bounds__(kThreads) void k_chain_stream(const float *__restrict__ in,
+                                                           const float *__restrict__ filt, float *__restrict__ out,
+                                                           int h, int w, int border, StreamPlan pl) {
+    extern __shared__ __align__(16) float lds[];
+    const int ns = gridDim.x - pl.frame;
+    if ((int)blockIdx.x >= ns) {
+        int b = blockIdx.x - ns, x0, y0, xe, ye;
+        const int below = (h - pl.yb + kFrameY - 1) / kFrameY, right = (w - pl.xb + kFrameX - 1) / kFrameX;
+        if (b < pl.fx * (1 + below)) {
+            const int r = b / pl.fx;
+            x0 = (b - r * pl.fx) * kFrameX;
+            xe = min(x0 + kFrameX, w);
+            y0 = r == 0 ? 0 : pl.yb + (r - 1) * kFrameY;
+            ye = r == 0 ? pl.ya : min(y0 + kFrameY, h);
+        } else {
+            b -= pl.fx * (1 + below);
+            const int r = b / (1 + right), c = b - r * (1 + right);
+            y0 = pl.ya + r * kFrameY;
+            ye = min(y0 + kFrameY, pl.yb);
+            x0 = c == 0 ? 0 : pl.xb + (c - 1) * kFrameX;
+            xe = c == 0 ? pl.xa : min(x0 + kFrameX, w);
+        }
+        chain_tile<R, EXACT, kFrameX, kFrameY, 2>(in, filt, out, h, w, P, border, x0, y0, xe, ye, blockIdx.x & 3, lds);
+        return;
+    }
+    constexpr int IL = (R * P + 3) / 4, SW = 4 * (64 - 2 * IL);
+    const int lane = threadIdx.x & 63, wave = dev::uniform(threadIdx.x >> 6);
+    const int t = xcd_remap(blockIdx.x, ns) * 4 + wave;
+    if (t >= pl.strips * pl.bands) return;
+    const int sy = t / pl.strips, sx = t - sy * pl.strips;
+    // The last strip is moved left to end at xb: it and its neighbour store
+    // the same values to the columns they share.
+    const int y0 = pl.ya + sy * pl.by, x0 = min(pl.xa + sx * SW, pl.xb - SW);
+    stream_strip<R, P, EXACT>(in, filt, out, w, x0, y0, min(pl.by, pl.yb - y0), lane);
+}
+
+// ---------------------------------------------------------------- launch
+
+template <int R>
+size_t lds_bytes(int passes, int tx, int ty, int q) {
     const int H = R * passes;
-    const int tiles_x = (w + kTileX - 1) / kTileX, tiles_y = (h + kTileY - 1) / kTileY;
-    const int64_t ntiles = (int64_t)tiles_x * tiles_y;
-    if (ntiles > INT32_MAX) return hipErrorInvalidValue;
-    const size_t lds = (size_t)lds_rows(H) * lds_pitch(R, H) * sizeof(float);
-    hipLaunchKernelGGL((k_chain_f32<R, EXACT>), dim3((unsigned)ntiles), dim3(kThreads), lds, s, in, filt, out, h, w,
-                       passes, border, tiles_x, (int)ntiles);
+    return (size_t)(ty + 2 * H + q - 1) * (tx + 2 * left_of(R, H)) * sizeof(float) * (passes > 1 ? 2 : 1);
+}
+
+template <int R, bool EXACT, int TX, int TY, int Q>
+hipError_t launch_tiles(const float *in, const float *filt, float *out, int h, int w, int passes, int border,
+                        hipStream_t s) {
+    const int64_t tiles_x = dev::cdiv(w, TX), n = tiles_x * dev::cdiv(h, TY);
+    if (n > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_chain_tiles<R, EXACT, TX, TY, Q>), dim3((unsigned)n), dim3(kThreads),
+                       lds_bytes<R>(passes, TX, TY, Q), s, in, filt, out, h, w, passes, border, (int)tiles_x);
     return hipGetLastError();
+}
+
+template <int R, int P, bool EXACT>
+hipError_t launch_stream(const float *in, const float *filt, float *out, int h, int w, int border,
+                         const StreamPlan &pl, hipStream_t s) {
+    const int64_t grid = pl.frame + dev::cdiv((int64_t)pl.strips * pl.bands, 4);
+    hipLaunchKernelGGL((k_chain_stream<R, P, EXACT>), dim3((unsigned)grid), dim3(kThreads),
+                       lds_bytes<R>(P, kFrameX, kFrameY, 2), s, in, filt, out, h, w, border, pl);
+    return hipGetLastError();
+}
+
+// Passes a stream is built for: its rings fit in registers (at most 160 of
+// them). At R = 4 the 81 taps no longer fit in scalar registers beside the
+// rest and the tiles are as fast.
+constexpr int stream_max(int r) { return r == 1 || r == 2 ? 8 : (r == 3 ? 5 : 0); }
+
+// The stream's plan, or false where the tiles are faster. Bands are as tall
+// as one wave per SIMD makes them (a second one per SIMD repeats 2H more halo
+// rows per band), but half that where the bands are still at least 8H tall
+// and a pixel costs 27 multiply-adds or more: two waves then hide each
+// other's waits (4096 x 4096, us, one / two: R = 1, 4 passes 34.0 / 30.1; 8
+// passes 58 / 65; 2 passes 23.9 / 26.3, HBM-bound). Least rows per band, from
+// streams / tiles (us): R = 1, 9 rows (1300 x 1800), 4 passes 12.5 / 14.8;
+// R = 2, 9 rows 26.7 / 24.8, 12 rows (1533 x 2047) 27.7 / 31.8; R = 3, 18 rows
+// (1800 x 2400), 3 passes 47.3 / 44.8, 24 rows (2160 x 2600) 47.9 / 52.6.
+inline bool stream_plan(int r, int passes, int h, int w, StreamPlan &pl) {
+    if (passes < 2 || passes > stream_max(r)) return false;
+    const int H = r * passes, IL = (H + 3) / 4, SW = 4 * (64 - 2 * IL);
+    pl.xa = kFrameX, pl.ya = kFrameY;
+    pl.xb = w - 4 * IL, pl.yb = h - H;
+    if (pl.xb - pl.xa < SW || pl.yb <= pl.ya) return false;
+    const int simds = 4 * std::max(dev_info().cus, 1), rows = pl.yb - pl.ya;
+    pl.strips = dev::cdiv(pl.xb - pl.xa, SW);
+    pl.by = dev::cdiv(rows, std::max(1, simds / pl.strips));
+    if (pl.by < (r == 1 ? 8 : (r == 2 ? 10 : 20))) return false;
+    if (pl.by >= 16 * H && passes * (2 * r + 1) * (2 * r + 1) >= 27)
+        pl.by = dev::cdiv(rows, std::max(1, 2 * simds / pl.strips));
+    pl.bands = dev::cdiv(rows, pl.by);
+    pl.fx = dev::cdiv(w, kFrameX);
+    const int64_t frame = (int64_t)pl.fx * (1 + dev::cdiv(h - pl.yb, kFrameY)) +
+                          (int64_t)dev::cdiv(rows, kFrameY) * (1 + dev::cdiv(w - pl.xb, kFrameX));
+    if (frame + (int64_t)pl.strips * pl.bands > (1 << 23)) return false;  // grid of 2^32 work items
+    pl.frame = (int)frame;
+    return true;
+}
+
+template <int R, bool EXACT, int P = 2>
+hipError_t launch_stream_passes(const float *in, const float *filt, float *out, int h, int w, int passes, int border,
+                                const StreamPlan &pl, hipStream_t s) {
+    if constexpr (P <= stream_max(R)) {
+        if (passes == P) return launch_stream<R, P, EXACT>(in, filt, out, h, w, border, pl, s);
+        return launch_stream_passes<R, EXACT, P + 1>(in, filt, out, h, w, passes, border, pl, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// Tiles of 64 x 32; of 64 x 16 while there are at most two per CU, where a
+// tile's latency is the launch's time (400 x 600, 8 x (5 x 5): 19.5 us against
+// 23.9 us); of 32 x 16 at one per CU at most (257 x 255: 16.8 us against
+// 19.4 us).
+template <int R, bool EXACT>
+hipError_t launch(const float *in, const float *filt, float *out, int h, int w, int passes, int border,
+                  hipStream_t s) {
+    StreamPlan pl;
+    if (stream_plan(R, passes, h, w, pl))
+        return launch_stream_passes<R, EXACT>(in, filt, out, h, w, passes, border, pl, s);
+    const int64_t cus = std::max(dev_info().cus, 1), rows16 = dev::cdiv(h, 16);
+    if (dev::cdiv(w, 32) * rows16 <= cus) return launch_tiles<R, EXACT, 32, 16, 1>(in, filt, out, h, w, passes, border, s);
+    if (dev::cdiv(w, 64) * rows16 <= 2 * cus) return launch_tiles<R, EXACT, 64, 16, 1>(in, filt, out, h, w, passes, border, s);
+    return launch_tiles<R, EXACT, 64, 32, 2>(in, filt, out, h, w, passes, border, s);
 }
 
 }  // namespace chain
 
-hipError_t launch_chain(int r, bool exact, const float *in, const float *filt, float *out, int h, int w, int passes,
-                        int border, hipStream_t s) {
-#define PF_CH(R) \
-    return exact ? chain::launch_r<R, true>(in, filt, out, h, w, passes, border, s) \
-                 : chain::launch_r<R, false>(in, filt, out, h, w, passes, border, s)
-    switch (r) {
-        case 0: PF_CH(0);
-        case 1: PF_CH(1);
-        case 2: PF_CH(2);
-        case 3: PF_CH(3);
-        case 4: PF_CH(4);
-        case 5: PF_CH(5);
-        case 6: PF_CH(6);
-        case 7: PF_CH(7);
-        case 8: PF_CH(8);
-        default: return hipErrorInvalidValue;
-    }
-#undef PF_CH
+template <>
+hipError_t launch_chain_radius<PF_R>(bool exact, const float *in, const float *filt, float *out, int h, int w,
+                                     int passes, int border, hipStream_t s) {
+    return exact ? chain::launch<PF_R, true>(in, filt, out, h, w, passes, border, s)
+                 : chain::launch<PF_R, false>(in, filt, out, h, w, passes, border, s);
 }
 
 }  // namespace pf

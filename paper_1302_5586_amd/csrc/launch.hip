@@ -24,17 +24,36 @@ hipError_t launch_f32(int r, int var, bool exact, const float *in, const float *
 }
 
 hipError_t launch_tile(int r, bool sep, bool exact, const float *in, const float *fa, const float *fb, float *out,
-                       int h, int w, hipStream_t s) {
+                       int h, int w, int border, hipStream_t s) {
     switch (r) {
-        case 0: return launch_tile_radius<0>(sep, exact, in, fa, fb, out, h, w, s);
-        case 1: return launch_tile_radius<1>(sep, exact, in, fa, fb, out, h, w, s);
-        case 2: return launch_tile_radius<2>(sep, exact, in, fa, fb, out, h, w, s);
-        case 3: return launch_tile_radius<3>(sep, exact, in, fa, fb, out, h, w, s);
-        case 4: return launch_tile_radius<4>(sep, exact, in, fa, fb, out, h, w, s);
-        case 5: return launch_tile_radius<5>(sep, exact, in, fa, fb, out, h, w, s);
-        case 6: return launch_tile_radius<6>(sep, exact, in, fa, fb, out, h, w, s);
-        case 7: return launch_tile_radius<7>(sep, exact, in, fa, fb, out, h, w, s);
-        case 8: return launch_tile_radius<8>(sep, exact, in, fa, fb, out, h, w, s);
+        case 0: return launch_tile_radius<0>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 1: return launch_tile_radius<1>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 2: return launch_tile_radius<2>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 3: return launch_tile_radius<3>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 4: return launch_tile_radius<4>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 5: return launch_tile_radius<5>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 6: return launch_tile_radius<6>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 7: return launch_tile_radius<7>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 8: return launch_tile_radius<8>(sep, exact, in, fa, fb, out, h, w, border, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_chain(int r, bool exact, const float *in, const float *filt, float *out, int h, int w, int passes,
+                        int border, hipStream_t s) {
+    // One pass has nothing to fuse: the tile kernel (4096 x 4096 reflect, R =
+    // 1: 25 us, the chain's own tiles 29 us).
+    if (passes == 1 && tile_fits(h, w)) return launch_tile(r, false, exact, in, filt, nullptr, out, h, w, border, s);
+    switch (r) {
+        case 0: return launch_chain_radius<0>(exact, in, filt, out, h, w, passes, border, s);
+        case 1: return launch_chain_radius<1>(exact, in, filt, out, h, w, passes, border, s);
+        case 2: return launch_chain_radius<2>(exact, in, filt, out, h, w, passes, border, s);
+        case 3: return launch_chain_radius<3>(exact, in, filt, out, h, w, passes, border, s);
+        case 4: return launch_chain_radius<4>(exact, in, filt, out, h, w, passes, border, s);
+        case 5: return launch_chain_radius<5>(exact, in, filt, out, h, w, passes, border, s);
+        case 6: return launch_chain_radius<6>(exact, in, filt, out, h, w, passes, border, s);
+        case 7: return launch_chain_radius<7>(exact, in, filt, out, h, w, passes, border, s);
+        case 8: return launch_chain_radius<8>(exact, in, filt, out, h, w, passes, border, s);
         default: return hipErrorInvalidValue;
     }
 }

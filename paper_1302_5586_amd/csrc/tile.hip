@@ -2,6 +2,9 @@
 // kernel behind pf_filter2d_f32 and pf_filter_sep_f32, one radius (PF_R, set
 // by the build) per object.
 //
+// pf_filter2d_f32_border and one-pass chains run the 2D kernel with their
+// border rule.
+//
 // A 256-thread workgroup owns a tile of 4 CX columns x (256 / CX) Q rows of
 // outputs and a thread 4 columns x Q rows of it. The tile's input rows and
 // columns with their halo are staged in LDS once, clamped to the image as
@@ -44,7 +47,6 @@ using dev::madd;
 using dev::static_for;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(4))) const float cfloat;  // read through the scalar cache
 
 constexpr int kThreads = kTileThreads;
 
@@ -55,33 +57,13 @@ constexpr int pitch_of(int r, int cx) { return 4 * cx + 2 * pad_of(r); }
 constexpr int rows_of(int r, int cx, int q) { return kThreads / cx * q + 2 * r; }
 constexpr int window_vecs(int r) { return 1 + pad_of(r) / 2; }
 
-// Workgroup -> tile, tiles numbered row by row. The launch is taken in
-// windows of about kWindow tiles, as many workgroups as the chip holds at
-// once (8 per CU): the tiles in flight cover one compact band of the image
-// that advances down it, and inside a window each XCD has a contiguous
-// eighth, so that most of a tile's neighbours are in the same L2. One
-// contiguous eighth of the whole image per XCD keeps eight windows of HBM
-// pages open: 30.0 us against 27.5 us at 4096 x 4096, R = 2 (buffers rotated
-// through 2 GiB; 26 us against 25.2 us where three images are reused and
-// partly in the last-level cache). Dealt in groups of 32 tiles instead,
-// halo rows cross XCDs: 14.5 us against 13.7 us at 2160 x 3840 from that
-// cache. Windows of 1024 and 4096 tiles measured within 3% of 2048.
-__device__ __forceinline__ void tile_of(int b, int n, int tiles_x, int &tx, int &ty) {
-    constexpr int kWindow = 2048;
-    const int windows = max(1, (n + kWindow / 2) / kWindow);
-    const int size = ((n + windows - 1) / windows + 7) / 8 * 8;  // a multiple of 8: workgroup b runs on XCD b mod 8
-    const int first = b / size * size;
-    const int t = first + xcd_remap(b - first, min(size, n - first));
-    ty = t / tiles_x;
-    tx = t - ty * tiles_x;
-}
-
-// Stages image rows y0 - R .. and columns x0 - PAD .. into buf, clamped to
-// the image; all of a thread's loads are in flight before any is written.
-// Rows and columns are clamped relative to the tile's origin, so nothing
+// Stages image rows y0 - R .. and columns x0 - PAD .. into buf, extended past
+// the image by the border rule; all of a thread's loads are in flight before
+// any is written. Clamping is relative to the tile's origin, so nothing
 // overflows at the largest images.
 template <int R, int CX, int Q>
-__device__ __forceinline__ void stage(const float *__restrict__ in, float *buf, int h, int w, int x0, int y0) {
+__device__ __forceinline__ void stage(const float *__restrict__ in, float *buf, int h, int w, int x0, int y0,
+                                      int border) {
     constexpr int PAD = pad_of(R), PITCH = pitch_of(R, CX), ROWS = rows_of(R, CX, Q), CY = kThreads / CX;
     const int right = w - 1 - x0, below = h - 1 - y0;  // >= 0
     if (x0 >= PAD && right >= 4 * CX + PAD - 1 && y0 >= R && below >= CY * Q + R - 1 && w <= (1 << 24)) {
@@ -122,6 +104,21 @@ __device__ __forceinline__ void stage(const float *__restrict__ in, float *buf, 
     // 4 columns: one load per column).
     constexpr int V = PITCH / 4, N = ROWS * V, NL = (N + kThreads - 1) / kThreads;
     f4 v[NL];
+    if (border != PF_BORDER_CLAMP) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int i = min((int)threadIdx.x + u * kThreads, N - 1);
+            const int row = i / V, c = 4 * (i - row * V) - PAD;
+            const int y = border_index(y0 + row - R, h, border);
+            const float *src = in + (int64_t)y * w;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int x = border_index(x0 + c + k, w, border);
+                v[u][k] = 0.0f;
+                if (x >= 0 && y >= 0) v[u][k] = src[x];
+            }
+        }
+    } else
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
         const int i = min((int)threadIdx.x + u * kThreads, N - 1);
@@ -168,47 +165,16 @@ __device__ __forceinline__ void store_tile(float *__restrict__ out, int h, int w
     }
 }
 
-// N taps through the scalar cache. The address is opaque to the compiler
-// here, so that a row of taps is loaded where it is asked for: hoisted to
-// the kernel's start, (2R+1)^2 taps spill.
-template <int N>
-__device__ __forceinline__ void load_taps(const float *p, float (&t)[N]) {
-    uint64_t a = (uint64_t)p;
-    asm volatile("" : "+s"(a));
-    const cfloat *c = (const cfloat *)a;
-#pragma unroll
-    for (int i = 0; i < N; ++i) t[i] = c[i];
-}
-
-template <int NB>
-__device__ __forceinline__ void load_window(const float *p, float (&t)[4 * NB]) {
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const f4 q = *reinterpret_cast<const f4 *>(p + 4 * b);
-        t[4 * b] = q.x;
-        t[4 * b + 1] = q.y;
-        t[4 * b + 2] = q.z;
-        t[4 * b + 3] = q.w;
-    }
-}
-
-// Keeps the accumulators' updates of a step before the loads of the next
-// ones: with them the compiler keeps every window row alive at once.
-template <int Q>
-__device__ __forceinline__ void end_step(float (&acc)[Q][4]) {
-#pragma unroll
-    for (int j = 0; j < Q; ++j) asm volatile("" : "+v"(acc[j][0]), "+v"(acc[j][1]), "+v"(acc[j][2]), "+v"(acc[j][3]));
-}
-
 template <int R, bool EXACT, int CX, int Q>
 __global__ __launch_bounds__(kThreads) void k_tile_2d(const float *__restrict__ in, const float *__restrict__ filt,
-                                                      float *__restrict__ out, int h, int w, int tiles_x) {
+                                                      float *__restrict__ out, int h, int w, int tiles_x,
+                                                      int border) {
     constexpr int K = 2 * R + 1, PAD = pad_of(R), PITCH = pitch_of(R, CX), NB = window_vecs(R);
     __shared__ __align__(16) float buf[rows_of(R, CX, Q) * PITCH];
     int tx, ty;
-    tile_of(blockIdx.x, gridDim.x, tiles_x, tx, ty);
+    window_tile(blockIdx.x, gridDim.x, tiles_x, tx, ty);
     const int x0 = tx * 4 * CX, y0 = ty * (kThreads / CX) * Q;
-    stage<R, CX, Q>(in, buf, h, w, x0, y0);
+    stage<R, CX, Q>(in, buf, h, w, x0, y0, border);
     float wt[2][K];
     load_taps<K>(filt, wt[0]);
     __syncthreads();
@@ -238,7 +204,6 @@ __global__ __launch_bounds__(kThreads) void k_tile_2d(const float *__restrict__ 
                 for (int k = 0; k < 4; ++k)
                     acc[j][k] = madd<EXACT>(wt[dy & 1][dx], win[(dy + j) % (Q + 1)][PAD - R + k + dx], acc[j][k]);
         end_step<Q>(acc);
-        __builtin_amdgcn_sched_barrier(0);
     });
     store_tile<Q>(out, h, w, x0, y0, 4 * cx, Q * cy, acc);
 }
@@ -252,9 +217,9 @@ __global__ __launch_bounds__(kThreads) void k_tile_sep(const float *__restrict__
     constexpr int NT = (ROWS + CY - 1) / CY;  // staged rows per thread in the row pass
     __shared__ __align__(16) float buf[ROWS * PITCH];
     int tx, ty;
-    tile_of(blockIdx.x, gridDim.x, tiles_x, tx, ty);
+    window_tile(blockIdx.x, gridDim.x, tiles_x, tx, ty);
     const int x0 = tx * 4 * CX, y0 = ty * CY * Q;
-    stage<R, CX, Q>(in, buf, h, w, x0, y0);
+    stage<R, CX, Q>(in, buf, h, w, x0, y0, PF_BORDER_CLAMP);
     float wx[K], wy[K];
     load_taps<K>(fx, wx);
     load_taps<K>(fy, wy);
@@ -303,14 +268,14 @@ __global__ __launch_bounds__(kThreads) void k_tile_sep(const float *__restrict__
 
 template <int R, bool EXACT, int CX, int Q>
 hipError_t launch_shape(bool sep, const float *in, const float *fa, const float *fb, float *out, int h, int w,
-                        hipStream_t s) {
+                        int border, hipStream_t s) {
     const int64_t tiles_x = dev::cdiv(w, 4 * CX), n = tiles_x * dev::cdiv(h, kThreads / CX * Q);
     if (sep)
         hipLaunchKernelGGL((k_tile_sep<R, EXACT, CX, Q>), dim3((unsigned)n), dim3(kThreads), 0, s, in, fa, fb, out, h,
                            w, (int)tiles_x);
     else
         hipLaunchKernelGGL((k_tile_2d<R, EXACT, CX, Q>), dim3((unsigned)n), dim3(kThreads), 0, s, in, fa, out, h, w,
-                           (int)tiles_x);
+                           (int)tiles_x, border);
     return hipGetLastError();
 }
 
@@ -322,21 +287,21 @@ hipError_t launch_shape(bool sep, const float *in, const float *fa, const float 
 // pieces; 4096 x 4096, R = 1: 25.5 us against 27.5 us for 64 x 32), 64 x 32
 // above (half the vertical halo; separable R = 6: 31.6 us against 36.1 us).
 template <int R, bool EXACT>
-hipError_t launch(bool sep, const float *in, const float *fa, const float *fb, float *out, int h, int w,
+hipError_t launch(bool sep, const float *in, const float *fa, const float *fb, float *out, int h, int w, int border,
                   hipStream_t s) {
     if ((int64_t)dev::cdiv(w, 64) * dev::cdiv(h, 16) <= 8 * (int64_t)dev_info().cus)
-        return launch_shape<R, EXACT, 16, 1>(sep, in, fa, fb, out, h, w, s);
-    if constexpr (R <= 3) return launch_shape<R, EXACT, 32, 2>(sep, in, fa, fb, out, h, w, s);
-    else return launch_shape<R, EXACT, 16, 2>(sep, in, fa, fb, out, h, w, s);
+        return launch_shape<R, EXACT, 16, 1>(sep, in, fa, fb, out, h, w, border, s);
+    if constexpr (R <= 3) return launch_shape<R, EXACT, 32, 2>(sep, in, fa, fb, out, h, w, border, s);
+    else return launch_shape<R, EXACT, 16, 2>(sep, in, fa, fb, out, h, w, border, s);
 }
 
 }  // namespace tile
 
 template <>
 hipError_t launch_tile_radius<PF_R>(bool sep, bool exact, const float *in, const float *fa, const float *fb,
-                                    float *out, int h, int w, hipStream_t s) {
-    return exact ? tile::launch<PF_R, true>(sep, in, fa, fb, out, h, w, s)
-                 : tile::launch<PF_R, false>(sep, in, fa, fb, out, h, w, s);
+                                    float *out, int h, int w, int border, hipStream_t s) {
+    return exact ? tile::launch<PF_R, true>(sep, in, fa, fb, out, h, w, border, s)
+                 : tile::launch<PF_R, false>(sep, in, fa, fb, out, h, w, border, s);
 }
 
 }  // namespace pf

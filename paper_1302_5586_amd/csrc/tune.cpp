@@ -472,7 +472,7 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
                             const size_t o = (size_t)i * px;
                             if (v != PF_VAR_SEP_DIRECT)
                                 return launch_tile(r, v == PF_VAR_SEPARABLE, false, in + o, filt, filt + (2 * r + 1),
-                                                   outb + o, h, w, s);
+                                                   outb + o, h, w, PF_BORDER_CLAMP, s);
                             return launch_f32(r, v, false, in + o, filt, filt + (2 * r + 1), outb + o, h, w, by, wpg,
                                               s);
                         },

@@ -111,3 +111,31 @@ def test_chain_rejects():
         pf.filter_chain(x, f, 5)  # r * passes = 20
     with pytest.raises(pf.PFInvalid):
         pf.filter_chain(x, f[:3, :3].contiguous(), 0)
+
+
+# Images at the stream form's least size: one strip of columns, then two that
+# overlap by all but one column; just enough rows for the least rows per band
+# of one wave per SIMD (1024 of them), the last band one row high.
+@pytest.mark.parametrize("r,passes,border", [(1, 2, 0), (1, 3, 2), (1, 7, 1), (1, 8, 3), (2, 2, 1), (2, 5, 3), (2, 8, 2),
+                                             (3, 2, 3), (3, 4, 0), (3, 5, 1)])
+def test_chain_streams(r, passes, border):
+    """Exact mode bit for bit the oracle; default mode within passes * 1e-5
+    of it, and bit for bit what the tile form computes for a crop of rows."""
+    dev = device()
+    halo = r * passes
+    side = 4 * ((halo + 3) // 4)
+    least = {1: 8, 2: 10, 3: 20}[r]
+    rng = np.random.default_rng(500 + 100 * r + 10 * passes + border)
+    for strips in (1, 2):
+        w = 64 + (256 - 2 * side) + side + (strips - 1)
+        h = 32 + (least - 1) * (1024 // strips) + 1 + halo
+        img = rng.random((h, w), dtype=np.float32)
+        f = synth.gaussian_2d(r, 1.0)
+        x, fd = _t(img, dev), _t(f, dev)
+        ref = oracle.filter_chain_f32(img, f, passes, border)
+        got = pf.filter_chain(x, fd, passes, border, exact=True).cpu().numpy()
+        assert np.array_equal(got, ref), "stream %dx%d r=%d passes=%d border=%d" % (h, w, r, passes, border)
+        fma = pf.filter_chain(x, fd, passes, border).cpu().numpy()
+        assert np.all(np.abs(fma - ref) <= passes * 1e-5 * np.abs(ref) + 1e-30)
+        crop = pf.filter_chain(x[100:260].contiguous(), fd, passes, border).cpu().numpy()
+        assert np.array_equal(crop[halo:160 - halo], fma[100 + halo:260 - halo]), "stream and tiles differ"

@@ -153,6 +153,13 @@ _SIGS = {
 }
 
 _lib = None
+# The native short path of the calls below (csrc/fastcall.cpp), once the
+# library is loaded. It takes the plain case of a call and returns
+# NotImplemented for anything else, which the Python code then handles.
+_fast = None
+_FAST_FNS = ("pf_filter2d_f32", "pf_filter_sep_f32", "pf_filter_chain_f32", "pf_filter2d_f32_border", "pf_filter2d_u8",
+             "pf_sum_workspace", "pf_sum_f32", "pf_sum_f32_noalloc", "pf_hist_workspace", "pf_hist256_u8",
+             "pf_server_submit", "pf_server_result")
 
 
 def library_path() -> str:
@@ -173,6 +180,32 @@ def load() -> ctypes.CDLL:
         fn.argtypes = args
     _lib = lib
     return lib
+
+
+_fast_tried = False
+
+
+def _load_fast(lib):
+    """Bind the short path to the loaded library (once, on the first call
+    that comes this way with a tensor, so torch is imported). Where it is not
+    built, or for another torch, the Python path serves every call."""
+    global _fast, _fast_tried
+    _fast_tried = True
+    try:
+        from . import _fastcall
+    except ImportError:
+        return
+    _fastcall.bind(tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _FAST_FNS))
+    _fast = _fastcall
+
+
+def _done(y) -> bool:
+    """Whether the short path served a call; raises for a nonzero status."""
+    if y is NotImplemented:
+        return False
+    if type(y) is int:
+        _check(y)
+    return True
 
 
 def _status_name(s: int) -> str:
@@ -200,9 +233,17 @@ def _torch():
 
 
 def _stream_ptr(stream=None) -> int:
+    if stream is not None:
+        return int(stream.cuda_stream)
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if not _fast_tried:
+        _load_fast(load())
+    try:
+        # The current stream's handle without a Stream object around it
+        # (0.1 us; torch.cuda.current_stream() takes 2.7 us).
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return int(torch.cuda.current_stream().cuda_stream)
 
 
 def _dev_tensor(t, dtype, name, ndim=None):
@@ -228,6 +269,10 @@ def _radius_of(n: int, what: str) -> int:
 
 def filter2d(x, f, *, exact: bool = False, out=None, stream=None):
     """FP32 clamp-to-edge 2D correlation of ``x`` [H, W] with ``f`` [2r+1, 2r+1]."""
+    if stream is None and _fast is not None:
+        y = _fast.filter2d(x, f, exact, out)
+        if _done(y):
+            return y
     torch = _torch()
     _dev_tensor(x, torch.float32, "x", (2,))
     _dev_tensor(f, torch.float32, "f", (2,))
@@ -245,6 +290,10 @@ def filter2d(x, f, *, exact: bool = False, out=None, stream=None):
 
 def filter2d_border(x, f, border: int, *, exact: bool = False, out=None, stream=None):
     """FP32 2D correlation of ``x`` [H, W] with ``f`` under a border rule (BORDER_*)."""
+    if stream is None and _fast is not None:
+        y = _fast.filter2d_border(x, f, border, exact, out)
+        if _done(y):
+            return y
     torch = _torch()
     _dev_tensor(x, torch.float32, "x", (2,))
     _dev_tensor(f, torch.float32, "f", (2,))
@@ -262,6 +311,10 @@ def filter2d_border(x, f, border: int, *, exact: bool = False, out=None, stream=
 
 def filter_chain(x, f, passes: int, border: int = 0, *, exact: bool = False, out=None, stream=None):
     """``passes`` fused applications of the 2D filter ``f`` to ``x`` [H, W] (one kernel)."""
+    if stream is None and _fast is not None:
+        y = _fast.filter_chain(x, f, passes, border, exact, out)
+        if _done(y):
+            return y
     torch = _torch()
     _dev_tensor(x, torch.float32, "x", (2,))
     _dev_tensor(f, torch.float32, "f", (2,))
@@ -287,6 +340,10 @@ def _workspace(fn, n, dev):
 def sum_f32(x, *, out=None, workspace=None, stream=None):
     """Reproducible float64 sum and mean of a contiguous FP32 tensor:
     returns a device float64 tensor [sum, mean]."""
+    if stream is None and _fast is not None:
+        y = _fast.sum_f32(x, out, workspace)
+        if _done(y):
+            return y
     torch = _torch()
     if not x.is_cuda or x.dtype != torch.float32 or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA float32 tensor")
@@ -305,6 +362,10 @@ def sum_f32_noalloc(x, *, out=None, stream=None):
     library's static device scratch holds the partials (x up to 2^29
     elements). Calls that overlap in time on one GPU share that scratch and
     must be ordered by the caller."""
+    if stream is None and _fast is not None:
+        y = _fast.sum_f32_noalloc(x, out)
+        if _done(y):
+            return y
     torch = _torch()
     if not x.is_cuda or x.dtype != torch.float32 or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA float32 tensor")
@@ -342,6 +403,10 @@ def probe_copy(x, out, stream=None):
 
 def hist256_u8(x, *, out=None, workspace=None, stream=None):
     """256-bin histogram (int64 counts) of a contiguous uint8 tensor."""
+    if stream is None and _fast is not None:
+        y = _fast.hist256_u8(x, out, workspace)
+        if _done(y):
+            return y
     torch = _torch()
     if not x.is_cuda or x.dtype != torch.uint8 or not x.is_contiguous():
         raise ValueError("x must be a contiguous CUDA uint8 tensor")
@@ -408,6 +473,10 @@ def edge_inc_atomic(edge_to_cells, edge, cell, stream=None):
 
 def filter_sep(x, fx, fy, *, exact: bool = False, out=None, stream=None):
     """FP32 separable filter: row pass with ``fx``, then column pass with ``fy``."""
+    if stream is None and _fast is not None:
+        y = _fast.filter_sep(x, fx, fy, exact, out)
+        if _done(y):
+            return y
     torch = _torch()
     _dev_tensor(x, torch.float32, "x", (2,))
     _dev_tensor(fx, torch.float32, "fx", (1,))
@@ -427,6 +496,10 @@ def filter_sep(x, fx, fy, *, exact: bool = False, out=None, stream=None):
 def filter2d_u8(x, f, shift: int = 6, *, out=None, stream=None):
     """uint8 planar [C, H, W] (or [H, W]) with int8 weights: int32 sum,
     arithmetic shift, saturation to uint8."""
+    if stream is None and _fast is not None:
+        y = _fast.filter2d_u8(x, f, shift, out)
+        if _done(y):
+            return y
     torch = _torch()
     _dev_tensor(x, torch.uint8, "x", (2, 3))
     _dev_tensor(f, torch.int8, "f", (2,))
@@ -674,6 +747,13 @@ class Server:
     def submit(self, x, r: int, kind: int, filt: np.ndarray, arrival_ns: int = 0, stream=None) -> int:
         """Submit one FP32 image: a GPU tensor (read in place) or a host numpy
         array (copied into the server's arena)."""
+        if stream is None and _fast is not None and self._s:
+            t = _fast.server_submit(self._s.value, x, r, kind, filt, arrival_ns)
+            if t is not NotImplemented:
+                if t < 0:
+                    _check(-t)
+                self._inputs[t] = x
+                return t
         f = np.ascontiguousarray(filt, dtype=np.float32).ravel()
         t = _I64()
         if isinstance(x, np.ndarray):
@@ -727,6 +807,12 @@ class Server:
             _check(load().pf_server_result(self._s, ticket, h, w, _np_ptr(a), 1))
             self._inputs.pop(ticket, None)
             return a
+        if _fast is not None and self._s:
+            st = _fast.server_result(self._s.value, ticket, h, w, out)
+            if st is not NotImplemented:
+                _check(st)
+                self._inputs.pop(ticket, None)
+                return out
         torch = _torch()
         _dev_tensor(out, torch.float32, "out", (2,))
         _check(load().pf_server_result(self._s, ticket, h, w, out.data_ptr(), 0))

@@ -32,6 +32,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpencilfilter.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")  # the Python binding's short path
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall", "-Wno-unused-function",
@@ -53,6 +54,7 @@ VARIANTS = {
 def _jobs():
     out = []
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
+    srcs.remove(os.path.join(CSRC, "fastcall.cpp"))
     for s in srcs:
         for tag, defs in VARIANTS.get(os.path.basename(s), [("", [])]):
             out.append((s, tag, defs))
@@ -130,6 +132,33 @@ def check_resources(objs, out_path: str) -> None:
         raise RuntimeError("batch kernels that use scratch (see %s):\n  %s" % (out_path, "\n  ".join(batch)))
 
 
+def build_fastcall(verbose: bool = False, incremental: bool = False) -> str:
+    """Compile the torch extension behind the Python binding's short path
+    (host code only; it holds no kernel and links no part of the library)."""
+    import sysconfig
+
+    from torch.utils import cpp_extension as ext
+
+    src = os.path.join(CSRC, "fastcall.cpp")
+    if incremental and os.path.exists(FASTCALL) and \
+            os.path.getmtime(FASTCALL) > max(os.path.getmtime(src), _newest_header(), os.path.getmtime(__file__)):
+        return FASTCALL
+    incs = ext.include_paths("cuda") + [sysconfig.get_paths()["include"], INCLUDE]
+    libs = ["c10", "c10_hip", "torch_cpu", "torch", "torch_python"]
+    tmp = FASTCALL + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
+    cmd += [a for i in incs for a in ("-isystem", i)] + [src, "-o", tmp]
+    cmd += ["-L" + d for d in ext.library_paths("cuda")] + ["-l" + n for n in libs]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("compilation failed: %s" % src)
+    os.replace(tmp, FASTCALL)
+    return FASTCALL
+
+
 def build(verbose: bool = False, jobs: int = 0, defines=(), out: str = LIB, incremental: bool = False) -> str:
     """Compile every source and link the shared library; returns its path.
     ``defines`` (e.g. ["-DPF_STRIP_ALIGNED=0"]) and ``out`` build a variant
@@ -142,7 +171,9 @@ def build(verbose: bool = False, jobs: int = 0, defines=(), out: str = LIB, incr
     work.sort(key=lambda j: (not j[0].endswith(".hip"), -len(j[1])))
     jobs = jobs or min(os.cpu_count() or 8, 16, len(work))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        fast = ex.submit(build_fastcall, verbose, incremental)
         objs = list(ex.map(lambda j: _compile(j, verbose, objdir, defines, incremental), work))
+        fast.result()
     check_resources(objs, os.path.join(objdir, "resource_usage.txt"))
     tmp = out + ".tmp%d" % os.getpid()
     cmd = [HIPCC, *DEVICE, "-shared", "-fPIC", "-o", tmp, *objs, "-lpthread"]

@@ -1,0 +1,96 @@
+"""The Python binding's native short path against its Python path.
+
+With an explicit `stream` a call takes the Python path, without one the short
+path: both must return the same bits and raise the same errors, and the short
+path must leave everything that is not the plain case to the Python path."""
+import numpy as np
+import pytest
+
+import paper_1302_5586_amd as pf
+
+torch = pytest.importorskip("torch")
+
+
+def _fast():
+    pf.load()
+    if not pf._fast_tried:
+        pf._load_fast(pf.load())
+    assert pf._fast is not None, "the short path is not built"
+    return pf._fast
+
+
+def test_leaves_other_arguments_to_python():
+    fast = _fast()
+    x, f = torch.zeros(4, 4), torch.zeros(3, 3)  # CPU tensors
+    assert fast.filter2d(x, f, False, None) is NotImplemented
+    assert fast.filter2d(x.numpy(), f, False, None) is NotImplemented
+    assert fast.filter2d(x, f, False) is NotImplemented
+    assert fast.filter2d_border(x, f, 1, False, None) is NotImplemented
+    assert fast.filter_chain(x, f, 2, 1, False, None) is NotImplemented
+    assert fast.filter_sep(x, f[0], f[0], False, None) is NotImplemented
+    assert fast.filter2d_u8(x.byte(), f.char(), 6, None) is NotImplemented
+    assert fast.sum_f32(x, None, None) is NotImplemented
+    assert fast.sum_f32_noalloc(x, None) is NotImplemented
+    assert fast.hist256_u8(x.byte(), None, None) is NotImplemented
+    assert fast.server_submit(0, x, 1, 1, np.zeros(6, np.float32), 0) is NotImplemented
+    assert fast.server_result(0, 1, 4, 4, x) is NotImplemented
+    with pytest.raises(ValueError):
+        pf.filter2d(x, f)
+    with pytest.raises(TypeError):
+        pf.filter2d(x.numpy(), f)
+    with pytest.raises(TypeError):
+        fast.bind(())
+
+
+CALLS = [
+    ("filter2d", lambda p, x, f, u, w, s: pf.filter2d(x, f, stream=s)),
+    ("filter2d exact", lambda p, x, f, u, w, s: pf.filter2d(x, f, exact=True, stream=s)),
+    ("filter2d out", lambda p, x, f, u, w, s: pf.filter2d(x, f, out=torch.empty_like(x), stream=s)),
+    ("border", lambda p, x, f, u, w, s: pf.filter2d_border(x, f, pf.BORDER_MIRROR, stream=s)),
+    ("chain", lambda p, x, f, u, w, s: pf.filter_chain(x, f, 3, pf.BORDER_ZERO, exact=True, stream=s)),
+    ("sep", lambda p, x, f, u, w, s: pf.filter_sep(x, f[0], f[2], stream=s)),
+    ("u8", lambda p, x, f, u, w, s: pf.filter2d_u8(u, w, 4, stream=s)),
+    ("u8 2D", lambda p, x, f, u, w, s: pf.filter2d_u8(u[0], w, 4, stream=s)),
+    ("sum", lambda p, x, f, u, w, s: pf.sum_f32(x, stream=s)),
+    ("sum noalloc", lambda p, x, f, u, w, s: pf.sum_f32_noalloc(x, stream=s)),
+    ("hist", lambda p, x, f, u, w, s: pf.hist256_u8(u, stream=s)),
+]
+BAD = [
+    ("alias", pf.PFAlias, lambda x, f, u, w, s: pf.filter2d(x, f, out=x, stream=s)),
+    ("passes", pf.PFInvalid, lambda x, f, u, w, s: pf.filter_chain(x, f, 0, stream=s)),
+    ("halo", pf.PFUnsupported, lambda x, f, u, w, s: pf.filter_chain(x, f, 17, stream=s)),
+    ("border", pf.PFInvalid, lambda x, f, u, w, s: pf.filter2d_border(x, f, 9, stream=s)),
+    ("shift", pf.PFInvalid, lambda x, f, u, w, s: pf.filter2d_u8(u, w, 40, stream=s)),
+    ("strides", ValueError, lambda x, f, u, w, s: pf.filter2d(x.t()[1:], f, stream=s)),
+    ("type", TypeError, lambda x, f, u, w, s: pf.filter2d(x.double(), f, stream=s)),
+    ("even filter", ValueError, lambda x, f, u, w, s: pf.filter2d(x, f[:2, :2].contiguous(), stream=s)),
+    ("small workspace", pf.PFInvalid,
+     lambda x, f, u, w, s: pf.sum_f32(x, workspace=torch.empty(0, dtype=torch.float64, device=x.device), stream=s)),
+]
+
+
+@pytest.mark.gpu
+def test_same_results_and_errors_as_the_python_path():
+    from gpu_util import device
+    dev = device()
+    fast = _fast()
+    g = torch.Generator(device=dev).manual_seed(3)
+    x = torch.randn((70, 133), generator=g, device=dev)
+    f = torch.randn((3, 3), generator=g, device=dev)
+    u = torch.randint(0, 256, (2, 37, 61), generator=g, device=dev, dtype=torch.uint8)
+    w = torch.randint(-8, 9, (5, 5), generator=g, device=dev, dtype=torch.int8)
+    assert isinstance(fast.filter2d(x, f, False, None), torch.Tensor)  # the short path serves the plain case
+    for name, call in CALLS:
+        assert torch.equal(call(pf, x, f, u, w, None), call(pf, x, f, u, w, torch.cuda.current_stream())), name
+        side = torch.cuda.Stream()  # the short path enqueues on the current stream
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            y = call(pf, x, f, u, w, None)
+        side.synchronize()
+        assert torch.equal(y, call(pf, x, f, u, w, None)), name
+    for name, err, call in BAD:
+        for s in (None, torch.cuda.current_stream()):
+            with pytest.raises(err):
+                call(x, f, u, w, s)
+    with pytest.raises(RuntimeError):  # a tensor without storage: the Python path reports it
+        torch.vmap(lambda t: pf.filter2d(t, f))(torch.zeros((2, 8, 8), device=dev))

@@ -158,6 +158,14 @@ struct pf_server {
     std::deque<std::shared_ptr<Request>> admitted;
     std::unordered_map<int64_t, std::shared_ptr<Request>> tickets;
     std::vector<hipEvent_t> events;    // free events for producer-stream ordering
+    // A device-to-device result copy may still be queued on the null stream
+    // when its request's arena bytes are given back. Whoever gets those bytes
+    // runs after it: a request submitted on the null stream by its `ready`
+    // event, any other by `copied`, recorded on the null stream behind the
+    // copy (record_copies_locked) and waited for by every batch since.
+    hipEvent_t copied = nullptr;
+    bool any_copied = false;           // `copied` was recorded
+    bool uncovered = false;            // a copy was queued since
     int64_t next_ticket = 1;
     bool stop = false;
     pf_status dev_error = PF_OK;
@@ -195,6 +203,23 @@ void drop_event_locked(pf_server *s, const std::shared_ptr<Request> &q) {
     q->ready = nullptr;
 }
 
+// Have later batches wait for the result copies queued so far (lock held).
+hipError_t record_copies_locked(pf_server *s) {
+    int dev = s->device;
+    (void)hipGetDevice(&dev);
+    if (dev != s->device) (void)hipSetDevice(s->device);
+    hipError_t e = hipEventRecord(s->copied, nullptr);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        e = hipStreamSynchronize(nullptr);
+    } else {
+        s->any_copied = true;
+    }
+    if (e == hipSuccess) s->uncovered = false;
+    if (dev != s->device) (void)hipSetDevice(dev);
+    return e;
+}
+
 void fail_locked(pf_server *s, const std::shared_ptr<Request> &q, pf_status st, const std::string &msg) {
     q->state = kFailed;
     q->fail_status = st;
@@ -229,7 +254,7 @@ pf_status ensure_slot(Slot &sl, size_t need, size_t need_ws) {
 
 // Build and launch one batch on a slot (lock NOT held; the requests are
 // owned by the slot). Returns a status; on failure nothing is in flight.
-pf_status launch_slot(pf_server *s, Slot &sl) {
+pf_status launch_slot(pf_server *s, Slot &sl, bool after_copies) {
     const bool exact = (s->flags & PF_FLAG_EXACT) != 0;
     auto arena_addr = [&](int64_t off) { return (int64_t)((uintptr_t)s->arena_dev + off); };
     // Filter requests: descriptors for the persistent batch kernel.
@@ -326,6 +351,10 @@ pf_status launch_slot(pf_server *s, Slot &sl) {
     put(o_st, sum_tasks.data(), sum_tasks.size() * sizeof(ReduceTask));
     put(o_ht, hist_tasks.data(), hist_tasks.size() * sizeof(ReduceTask));
     hipError_t e;
+    // The arena bytes of this batch may have been given back by a request
+    // whose result copy has not run yet.
+    if (after_copies && (e = hipStreamWaitEvent(sl.stream, s->copied, 0)) != hipSuccess)
+        return fail_hip(e, "server wait on result copies");
     // Device inputs: wait for the work their producer stream had queued at
     // submit. Upload-mode inputs: copy them into the arena.
     for (auto &q : sl.reqs) {
@@ -459,8 +488,9 @@ void engine_main(pf_server *s) {
             }
             for (auto &r : sl.reqs) r->state = kLaunched;
             sl.busy = true;
+            const bool after_copies = s->any_copied;
             lk.unlock();
-            const pf_status st = launch_slot(s, sl);
+            const pf_status st = launch_slot(s, sl, after_copies);
             lk.lock();
             ++s->batches;
             s->batched_reqs += (int64_t)sl.reqs.size();
@@ -517,6 +547,12 @@ pf_status check_budget(pf_server *s, const Request &q, bool upload) {
 // device input after the work queued on `stream` (order = false: the input
 // is known to be complete).
 pf_status stage_input(pf_server *s, Request &q, const void *in, bool upload, void *stream, bool order) {
+    if (s->uncovered) {
+        int dev = -1;
+        (void)hipGetDevice(&dev);
+        if (upload || !order || stream || dev != s->device)
+            if (hipError_t e = record_copies_locked(s)) return fail_hip(e, "server result copies");
+    }
     if (upload) {
         const uint8_t *b = (const uint8_t *)in;
         q.in_host.assign(b, b + q.in_bytes);
@@ -600,9 +636,22 @@ pf_status copy_result(pf_server *s, int64_t ticket, int32_t op, int32_t h, int32
         if (q->op != op) return fail(PF_EINVAL, "the request is of another kind");
         if (op == kOpFilter && (h != q->h || w != q->w)) return fail(PF_EINVAL, "size differs from the request's");
     }
-    const hipError_t e = hipMemcpy(out, s->arena_dev + q->out_off, (size_t)q->out_bytes,
-                                   out_is_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice);
+    hipError_t e = hipMemcpy(out, s->arena_dev + q->out_off, (size_t)q->out_bytes,
+                             out_is_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice);
     std::lock_guard<std::mutex> lk(s->mu);
+    if (!out_is_host && e == hipSuccess) {
+        // The copy is only queued here, on the null stream of the caller's
+        // current device; that of another device than the server's is waited
+        // for. Requests in the queue may get the bytes at once.
+        int dev = s->device;
+        (void)hipGetDevice(&dev);
+        if (dev != s->device) {
+            e = hipStreamSynchronize(nullptr);
+        } else {
+            s->uncovered = true;
+            if (!s->queued.empty()) e = record_copies_locked(s);
+        }
+    }
     release_locked(s, q);
     wake_engine_locked(s);
     if (e != hipSuccess) return fail_hip(e, "result copy");
@@ -639,6 +688,7 @@ pf_status pf_server_create(int64_t hbm_budget_bytes, int32_t n_streams, int32_t 
             if (x.host) (void)hipHostFree(x.host);
             if (x.ws) (void)hipFree(x.ws);
         }
+        if (s->copied) (void)hipEventDestroy(s->copied);
         if (s->arena_dev) (void)hipFree(s->arena_dev);
         delete s;
         return st;
@@ -649,6 +699,10 @@ pf_status pf_server_create(int64_t hbm_budget_bytes, int32_t n_streams, int32_t 
         return cleanup(fail_hip(e, "server arena"));
     }
     s->arena.reset(hbm_budget_bytes);
+    if ((e = hipEventCreateWithFlags(&s->copied, hipEventDisableTiming)) != hipSuccess) {
+        s->copied = nullptr;
+        return cleanup(fail_hip(e, "server result event"));
+    }
     s->slots.resize(n_streams);
     for (Slot &sl : s->slots) {
         if ((e = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking)) != hipSuccess ||
@@ -871,6 +925,7 @@ pf_status pf_server_destroy(pf_server *s) {
     for (hipEvent_t e : s->events) (void)hipEventDestroy(e);
     for (auto &kv : s->tickets)
         if (kv.second->ready) (void)hipEventDestroy(kv.second->ready);
+    (void)hipEventDestroy(s->copied);
     (void)hipFree(s->arena_dev);
     delete s;
     return PF_OK;

@@ -255,3 +255,35 @@ def test_queue_full_budget_and_shutdown():
     t0 = time.time()
     s.close()                                    # t4 can never be admitted while t2's result is held
     assert time.time() - t0 < 5.0
+
+
+@pytest.mark.parametrize("late", [False, True])
+def test_arena_bytes_wait_for_the_result_copy(late):
+    """A request that gets the arena bytes of one whose result is taken to
+    the GPU runs after that copy, also where the copy is still queued behind
+    other work when the bytes are given back. late: the request comes from
+    another stream after the result was taken, and is not in the queue then."""
+    dev = device()
+    import torch
+    h, w = 512, 768
+    rng = np.random.default_rng(77)
+    g = synth.gaussian_1d(2, 1.1)
+    f = np.concatenate([g, g])
+    imgs = [rng.random((h, w), dtype=np.float32) for _ in range(6)]
+    xs = [torch.from_numpy(a).to(dev) for a in imgs]
+    outs = [torch.zeros(h, w, device=dev) for _ in imgs]
+    busy = torch.randn(4096, 4096, device=dev)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with pf.Server((1 if late else 2) * h * w * 4, n_streams=2, max_batch=1) as s:
+        tickets = [] if late else [s.submit(x, 2, pf.KIND_SEP, f) for x in xs]
+        for i, o in enumerate(outs):
+            if late:
+                tickets.append(s.submit(xs[i], 2, pf.KIND_SEP, f, stream=side))
+            s.wait(tickets[i], timeout_s=60)
+            for _ in range(8):
+                busy = busy @ busy * 1e-2                             # the copy is queued behind these
+            s.result(tickets[i], h, w, out=o)
+    torch.cuda.synchronize()
+    for img, o in zip(imgs, outs):
+        assert_close(o.cpu().numpy(), oracle.filter_sep_f32(img, g, g), tolerance_sep(img, g, g), "result copy")

@@ -190,7 +190,9 @@ pf_status pf_sum_f32_noalloc(int64_t n, PF_ARR(const float, x, n), PF_ARR(double
  * (Sec. II-B.3) with repeated indices: hist[v] = number of i with
  * x[i] == v. Exact. n >= 1, at most 2^40. x: uint8_t[n] device (any
  * alignment). hist: int64_t[256] device, 8-byte aligned. workspace: at
- * least pf_hist_workspace(n) bytes, 4-byte aligned, as for pf_sum_f32. */
+ * least pf_hist_workspace(n) bytes, 4-byte aligned, as for pf_sum_f32. Up to
+ * min(n / 32768 + 1, 1024) KiB are used if workspace_bytes says they are
+ * there: arrays of 32 KiB to 64 MiB then spread over more of the device. */
 pf_status pf_hist_workspace(int64_t n, PF_OUTP(size_t, bytes));
 pf_status pf_hist256_u8(int64_t n, PF_ARR(const uint8_t, x, n), PF_ARR(int64_t, hist, 256),
                         void *workspace, size_t workspace_bytes, void *stream);

@@ -330,11 +330,11 @@ def filter_chain(x, f, passes: int, border: int = 0, *, exact: bool = False, out
     return out
 
 
-def _workspace(fn, n, dev):
+def _workspace(fn, n, dev, useful=0):
     torch = _torch()
     nb = ctypes.c_size_t(0)
     _check(fn(n, ctypes.byref(nb)))
-    return torch.empty(max((nb.value + 7) // 8, 1), dtype=torch.float64, device=dev)
+    return torch.empty(max((max(nb.value, useful) + 7) // 8, 1), dtype=torch.float64, device=dev)
 
 
 def sum_f32(x, *, out=None, workspace=None, stream=None):
@@ -414,7 +414,8 @@ def hist256_u8(x, *, out=None, workspace=None, stream=None):
     if out is None:
         out = torch.empty(256, dtype=torch.int64, device=x.device)
     if workspace is None:
-        workspace = _workspace(load().pf_hist_workspace, n, x.device)
+        # One sub-histogram per CU and 32 KiB of data (see pf_hist256_u8).
+        workspace = _workspace(load().pf_hist_workspace, n, x.device, 1024 * min(n // 32768 + 1, 256))
     _check(load().pf_hist256_u8(n, x.data_ptr(), out.data_ptr(), workspace.data_ptr(),
                                 workspace.numel() * workspace.element_size(), _stream_ptr(stream)))
     return out

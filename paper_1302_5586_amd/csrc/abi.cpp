@@ -8,6 +8,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -230,7 +231,10 @@ pf_status pf_hist256_u8(int64_t n, const uint8_t *x, int64_t *hist, void *worksp
     if (overlap(x, (size_t)n, hist, 256 * sizeof(int64_t)) || overlap(x, (size_t)n, workspace, need) ||
         overlap(hist, 256 * sizeof(int64_t), workspace, need))
         return fail(PF_EALIAS, "x, hist and workspace must not overlap (restrict)");
-    hipError_t e = launch_hist(x, n, hist, workspace, (hipStream_t)stream);
+    // A larger workspace is used as far as it helps and is the call's alone.
+    size_t use = std::min(workspace_bytes, std::max(need, (size_t)hist_rows_wanted(n) * 256 * sizeof(uint32_t)));
+    if (overlap(x, (size_t)n, workspace, use) || overlap(hist, 256 * sizeof(int64_t), workspace, use)) use = need;
+    hipError_t e = launch_hist(x, n, hist, workspace, use, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return PF_OK;
 }

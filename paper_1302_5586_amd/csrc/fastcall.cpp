@@ -248,6 +248,8 @@ PyObject *hist256_u8(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (!x || !any_tensor(a[1]) || !any_tensor(a[2])) return not_handled();
         size_t need = 0;
         if (f_hist_ws(x->numel(), &need) != PF_OK) return not_handled();
+        // One sub-histogram per CU and 32 KiB of data (see pf_hist256_u8).
+        need = std::max(need, (size_t)1024 * (size_t)std::min<int64_t>(x->numel() / 32768 + 1, 256));
         return run(
             a[1], [&] { return at::empty({256}, x->options().dtype(at::kLong)); },
             [&](const at::Tensor &y) {

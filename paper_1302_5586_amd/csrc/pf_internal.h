@@ -220,7 +220,11 @@ hipError_t launch_chain(int r, bool exact, const float *in, const float *filt, f
 size_t sum_workspace_bytes(int64_t n);
 size_t hist_workspace_bytes(int64_t n);
 hipError_t launch_sum(const float *x, int64_t n, double *out, void *workspace, hipStream_t s);
-hipError_t launch_hist(const uint8_t *x, int64_t n, int64_t *hist, void *workspace, hipStream_t s);
+// Sub-histograms (1 KiB of workspace each) that an n-byte histogram runs
+// fastest with; launch_hist takes as many of them as the workspace holds.
+int64_t hist_rows_wanted(int64_t n);
+hipError_t launch_hist(const uint8_t *x, int64_t n, int64_t *hist, void *workspace, size_t workspace_bytes,
+                       hipStream_t s);
 // Reduction requests of a server batch (reduce.hip). in / out are absolute
 // device addresses (the input array; double[2] or int64_t[256] result);
 // `first` is the request's first slot in the batch workspace: chunk

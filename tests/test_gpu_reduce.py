@@ -116,3 +116,70 @@ def test_reduce_rejects():
         pf._check(pf.load().pf_sum_f32(100, x.data_ptr(), out.data_ptr(), small.data_ptr(), 0, None))
     with pytest.raises(pf.PFAlias):
         pf._check(pf.load().pf_sum_f32(100, x.data_ptr(), x.data_ptr() + 8, ws.data_ptr(), 8, None))
+
+
+def _tree(v):
+    """The fixed pairwise tree over 256 float64 values."""
+    half = 128
+    while half:
+        v = v[:half] + v[half:2 * half]
+        half //= 2
+    return v[0]
+
+
+def _fixed_sum(x):
+    """The device sum's definition: chunks of 65536, thread t of 256 adds the
+    4-element groups t, t + 256, ... in order, then the tree; the chunk sums
+    the same way."""
+    sums = []
+    for c in range(0, x.size, 65536):
+        g = np.zeros(65536, np.float64)
+        part = x[c:c + 65536]
+        g[:part.size] = part
+        acc = np.zeros(256)
+        for group in g.reshape(64, 256, 4):
+            for e in range(4):
+                acc = acc + group[:, e]
+        sums.append(_tree(acc))
+    acc = np.zeros(256)
+    for c in range(0, len(sums), 256):
+        row = np.zeros(256)
+        row[:len(sums[c:c + 256])] = sums[c:c + 256]
+        acc = acc + row
+    return _tree(acc)
+
+
+@pytest.mark.parametrize("n", [1, 5, 1023, 4098, 65535, 65536, 65539, 3 * 65536 + 1021, 300 * 65536 + 6, (1 << 26) + 5])
+def test_sum_bits(n):
+    """One chunk in one launch, ragged last chunks (whole groups, a partial
+    group, less than a group), more than 256 chunks, and the streamed loads
+    from 2^26 elements up: all the definition's bits."""
+    dev = device()
+    import torch
+    x = torch.randn(n, generator=torch.Generator(device=dev).manual_seed(n), device=dev)
+    got = pf.sum_f32(x).cpu().numpy()
+    assert got[0] == _fixed_sum(x.cpu().numpy()) and got[1] == got[0] / n
+    assert np.array_equal(pf.sum_f32_noalloc(x).cpu().numpy(), got)
+
+
+# One workgroup takes up to 32 KiB; 256 of them 8 MiB before any loops.
+@pytest.mark.parametrize("n", [1, 14, 15, 16, 17, 4099, 32767, 32768, 32769, 65551, (1 << 23) - 1, (1 << 23) + 32785])
+def test_hist_edges(n):
+    dev = device()
+    import ctypes
+    import torch
+    rng = np.random.default_rng(n)
+    y = rng.integers(0, 256, n + 16).astype(np.uint8)
+    yt = _t(y, dev)
+    for offset in (0, 1, 4, 15):  # starts off the 16-byte vectors
+        x = yt[offset:offset + n]
+        ref = oracle.hist256_u8(y[offset:offset + n])
+        assert np.array_equal(pf.hist256_u8(x).cpu().numpy(), ref), offset
+        # the least workspace: fewer sub-histograms, the same counts
+        nb = ctypes.c_size_t(0)
+        pf._check(pf.load().pf_hist_workspace(n, ctypes.byref(nb)))
+        ws = torch.full((nb.value // 8 + 8,), float("nan"), dtype=torch.float64, device=dev)
+        h = torch.empty(256, dtype=torch.int64, device=dev)
+        pf._check(pf.load().pf_hist256_u8(n, x.data_ptr(), h.data_ptr(), ws.data_ptr(), nb.value, pf._stream_ptr()))
+        assert np.array_equal(h.cpu().numpy(), ref), offset
+        assert torch.isnan(ws[nb.value // 8:]).all()  # nothing past the workspace

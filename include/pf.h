@@ -206,8 +206,8 @@ pf_status pf_hist256_u8(int64_t n, PF_ARR(const uint8_t, x, n), PF_ARR(int64_t, 
  * inverts the map once (host copy `edge_to_cells`, int32[2 * nedges],
  * read during the call only; entries in 0..ncells-1, else PF_EINVAL;
  * nedges <= 2^30) and keeps its tables in device memory until destroyed.
- * pf_inc_plan_run adds every cell's increments in the loop's order, one
- * thread per cell: edge: double[nedges] device, cell: double[ncells]
+ * pf_inc_plan_run adds every cell's increments in the loop's order, without
+ * atomics: edge: double[nedges] device, cell: double[ncells]
  * device (read and written), 8-byte aligned, disjoint (else PF_EALIAS);
  * sizes must match the plan's. */
 typedef struct pf_inc_plan pf_inc_plan;

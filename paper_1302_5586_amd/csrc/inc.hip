@@ -9,29 +9,55 @@
 //    self-loop edge twice, its second cell first). The kernel then gives
 //    each cell to one thread, which adds the cell's increments in exactly
 //    that order: no atomics, no colouring, and the result equals the
-//    sequential loop bit for bit.
+//    sequential loop bit for bit. Large meshes in random order take a second
+//    form of the plan with the same property (k_rounds).
 //  * A scatter with float64 atomic adds: one thread per edge. Fast to set
 //    up, but the order in which a cell's increments land varies from run
 //    to run, so only a tolerance holds.
+#include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
+#include <memory>
+#include <new>
 #include <vector>
 
 #include "dev_common.h"
 #include "pf_internal.h"
 
+namespace pf {
+namespace inc {
+
+typedef int32_t i2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+
+constexpr int kThreads = 256;
+
+constexpr int kWaves = 16;        // waves of a k_rounds workgroup, a bin of cells each
+constexpr int kMaxCells = 1024;   // cells of a bin; the slot behind them takes the padding
+constexpr int kGroup = 2;         // rounds per step
+constexpr int kSlotBits = 11;     // a round's entry: slot of the cell, then edge - base of the round
+constexpr int32_t kSpan = 1 << (32 - kSlotBits);
+
+}  // namespace inc
+}  // namespace pf
+
 struct pf_inc_plan {
     int32_t ncells = 0, nedges = 0;
     int device = -1;
-    void *dev = nullptr;  // offsets (ncells + 1) then edge lists (2 * nedges), int32
+    void *dev = nullptr;  // all tables
+    // Lists: offsets (ncells + 1), the cells' edges (2 * nedges).
     const int32_t *off = nullptr, *idx = nullptr;
+    // Rounds (nbins > 0): the bins' first groups (nbins + 1); per group, the
+    // edge base of each round and 64 entries of each.
+    int32_t nbins = 0, per = 0;
+    const int32_t *first = nullptr;
+    const pf::inc::i2 *base = nullptr;
+    const pf::inc::u2 *entry = nullptr;
 };
 
 namespace pf {
 namespace inc {
-
-constexpr int kThreads = 256;
-
 
 // cell[c] += edge[idx[k]] for k in off[c] .. off[c+1], in that order.
 __global__ __launch_bounds__(kThreads) void k_gather(const int32_t *__restrict__ off, const int32_t *__restrict__ idx,
@@ -55,6 +81,81 @@ __global__ __launch_bounds__(kThreads) void k_gather(const int32_t *__restrict__
     cell[c] = v;
 }
 
+__device__ __forceinline__ void round_values(const double *__restrict__ edge, u2 e, i2 b, double *v) {
+#pragma unroll
+    for (int u = 0; u < kGroup; ++u) v[u] = edge[b[u] + (int32_t)(e[u] >> kSlotBits)];
+}
+
+// The same increments for large meshes in random order. There k_gather is
+// bound by what it fetches, not by what it uses: every 8-byte value comes as a
+// line of 128 bytes through the last-level cache (16.8 million of them for a
+// 2048 x 2048 quad mesh: 2.1 GB at 7 TB/s). Here the cells sit in LDS, 1024
+// per wave and 16384 per CU, so a mesh of up to 4.2 million cells is resident
+// at once, and all waves walk the edge array from its start to its end: a
+// line is fetched once per XCD while its workgroups pass it. Wave b owns bin
+// b (cells b * per ..) and takes the bin's visits in the loop's order, cut on
+// the host into rounds of 64 in which no cell occurs twice, and a cell's
+// visits in rounds that ascend: one read-modify-write per lane and round, in
+// the order of the loop, without atomics (LDS operations of one wave are
+// performed in order). The barrier per step only keeps the 16 waves together:
+// without it they drift apart by more than the L2 holds (79% misses, 254 us).
+// Two rounds per step: 132 us; one 140, four 144, and a third step of loads in
+// flight 135.
+// 2048 x 2048 quads: 309 -> 133 us; 1024 x 1024: 64.5 -> 37.6 us.
+__global__ __launch_bounds__(64 * kWaves) void k_rounds(const int32_t *__restrict__ first, const i2 *__restrict__ base,
+                                                        const u2 *__restrict__ entry, const double *__restrict__ edge,
+                                                        double *__restrict__ cell, int32_t ncells, int32_t per) {
+    __shared__ double acc[kWaves][kMaxCells + 1];
+    __shared__ int most;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.x * kWaves + wave;
+    const int64_t c0 = (int64_t)b * per;
+    const int cnt = (int)min((int64_t)per, max((int64_t)0, ncells - c0));
+    double *a = acc[wave];
+    for (int i = lane; i < cnt; i += 64) a[i] = __builtin_nontemporal_load(cell + c0 + i);
+    int g0 = 0, g1 = 0;
+    if (cnt > 0) {
+        g0 = first[b];
+        g1 = first[b + 1];
+    }
+    if (threadIdx.x == 0) most = 0;
+    __syncthreads();
+    if (lane == 0) atomicMax(&most, g1 - g0);
+    __syncthreads();
+    const int steps = most;
+    if (steps > 0) {
+        // Entries two steps ahead, values one; past the bin's last group the
+        // loads repeat it (or the group before an empty bin).
+        const int gl = max(g1 - 1, 0);
+        u2 e = __builtin_nontemporal_load(entry + (int64_t)min(g0, gl) * 64 + lane);
+        u2 en = __builtin_nontemporal_load(entry + (int64_t)min(g0 + 1, gl) * 64 + lane);
+        double v[kGroup], vn[kGroup];
+        round_values(edge, e, base[min(g0, gl)], v);
+#pragma unroll 1
+        for (int k = 0; k < steps; ++k) {
+            const int g = g0 + k;
+            round_values(edge, en, base[min(g + 1, gl)], vn);
+            const u2 e2 = __builtin_nontemporal_load(entry + (int64_t)min(g + 2, gl) * 64 + lane);
+            __builtin_amdgcn_sched_barrier(0);
+            if (g < g1) {
+#pragma unroll
+                for (int u = 0; u < kGroup; ++u) {
+                    const int slot = e[u] & ((1 << kSlotBits) - 1);
+                    a[slot] = a[slot] + v[u];
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+            e = en;
+            en = e2;
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u) v[u] = vn[u];
+            __builtin_amdgcn_s_barrier();
+        }
+    }
+    for (int i = lane; i < cnt; i += 64) __builtin_nontemporal_store(a[i], cell + c0 + i);
+}
+
 // One thread per edge: cell[e2c[2i+1]] += edge[i]; cell[e2c[2i]] += edge[i].
 __global__ __launch_bounds__(kThreads) void k_scatter(const int32_t *__restrict__ e2c, const double *__restrict__ edge,
                                                       double *__restrict__ cell, int32_t ncells, int32_t nedges) {
@@ -66,6 +167,161 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const int32_t *__restrict_
     // entries outside 0..ncells-1 are skipped rather than written through.
     if ((uint32_t)c1 < (uint32_t)ncells) unsafeAtomicAdd(&cell[c1], e);
     if ((uint32_t)c0 < (uint32_t)ncells) unsafeAtomicAdd(&cell[c0], e);
+}
+
+}  // namespace inc
+}  // namespace pf
+
+namespace pf {
+namespace inc {
+
+// Which plans are rounds. From 10 MiB of edge values: below, the L2s hold
+// most of what k_gather fetches and the rounds' steps cost more (random quads:
+// 724 x 724, 8 MiB: 25.4 us against 33 us; 860 x 860: 42 us against 29 us).
+// Only where the edges next to each other name cells far apart (a sample):
+// with edges numbered along the cells the values of k_gather are in the L2
+// (2048 x 2048 numbered row by row: 44.6 us against 49.5 us; shuffled within a
+// sixteenth of the mesh: 103 us against 108 us).
+bool rounds_suit(int32_t ncells, int32_t nedges, const int32_t *e2c) {
+    if (nedges < (10 << 20) / 8 || ncells > 1 << 30) return false;  // cells: see Quotient
+    constexpr int kSamples = 4096;
+    int far = 0;
+    for (int s = 0; s < kSamples; ++s) {
+        const int64_t i = (int64_t)s * (nedges - 1) / kSamples;
+        for (int k = 0; k < 2; ++k)
+            far += abs(e2c[2 * i + k] - e2c[2 * i + 2 + k]) > ncells / 16;
+    }
+    return far > kSamples;
+}
+
+// n / d by a multiplication: exact for n < 2^30 and 2^10 <= d <= 2^14 and for
+// n < 2^14 and 1 <= d <= 2^14, since m = ceil(2^44 / d) is at most 1 more than
+// 2^44 / d, and n m fits 64 bits.
+struct Quotient {
+    uint64_t m;
+    explicit Quotient(int32_t d) : m((((uint64_t)1 << 44) + (uint64_t)d - 1) / (uint64_t)d) {}
+    int32_t operator()(int32_t n) const { return (int32_t)((uint64_t)n * m >> 44); }
+};
+
+struct Rounds {
+    int32_t nbins = 0, per = 0;
+    std::vector<int32_t> first, base;
+    std::unique_ptr<uint32_t[]> entry;
+    size_t entries = 0;
+};
+
+// The visits of each bin in rounds of 64 (k_rounds). False where the rounds
+// would be more than a quarter padding, or the longest bin more than twice
+// the mean: a cell in many edges has a round for each of its visits.
+bool make_rounds(int32_t ncells, int32_t nedges, const int32_t *e2c, Rounds *out) {
+    const int64_t visits = 2 * (int64_t)nedges;
+    // Bins for one workgroup per CU, or for as many sweeps of 256 workgroups as
+    // the cells need; at least 192 cells, since small bins leave no 64 visits
+    // of different cells to choose from (17% padding at 192, over 25% at 128).
+    constexpr int64_t kResident = 256 * kWaves;
+    const int64_t sweeps = (ncells + kResident * kMaxCells - 1) / (kResident * kMaxCells);
+    const int32_t per = (int32_t)std::max<int64_t>(192, (ncells + kResident * sweeps * 64 - 1) / (kResident * sweeps * 64) * 64);
+    const int32_t nbins = (int32_t)((ncells + (int64_t)per - 1) / per);
+    // First by workgroup: few enough streams for the caches, in edge order.
+    const int32_t block = per * kWaves, nblocks = (int32_t)((ncells + (int64_t)block - 1) / block);
+    const Quotient by_block(block), by_per(per);
+    struct Visit {
+        int32_t edge, slot;
+    };
+    std::vector<int64_t> at((size_t)nblocks + 1, 0);
+    for (int64_t j = 0; j < visits; ++j) ++at[(size_t)by_block(e2c[j]) + 1];
+    for (int32_t b = 0; b < nblocks; ++b) at[(size_t)b + 1] += at[b];
+    std::vector<int64_t> fill(at.begin(), at.end() - 1);
+    std::unique_ptr<Visit[]> list(new Visit[(size_t)visits]);
+    for (int32_t i = 0; i < nedges; ++i)
+        for (int k = 1; k >= 0; --k) {  // the second cell is incremented first
+            const int32_t c = e2c[2 * (int64_t)i + k], b = by_block(c);
+            list[(size_t)fill[(size_t)b]++] = {i, c - b * block};
+        }
+    struct Round {
+        int32_t base, count;
+    };
+    struct Bin {
+        int32_t low = 0;  // rounds below are full or out of reach
+        std::vector<Round> round;
+        std::vector<uint32_t> entry;
+    };
+    const size_t most = (size_t)(visits + visits / 4);
+    out->first.assign(1, 0);
+    out->entry.reset(new uint32_t[most]);
+    std::vector<Bin> bins(kWaves);
+    std::vector<int32_t> last((size_t)block);  // the cells' last rounds
+    size_t longest = 0;
+    for (int32_t w = 0; w < nblocks; ++w) {
+        for (Bin &q : bins) {
+            q.low = 0;
+            q.round.clear();
+            q.entry.clear();
+        }
+        std::fill(last.begin(), last.end(), -1);
+        const Visit *v = list.get() + at[(size_t)w], *const end = list.get() + at[(size_t)w + 1];
+        for (; v != end; ++v) {
+            const int32_t edge = v->edge, in = by_per(v->slot);
+            Bin &q = bins[(size_t)in];
+            const int32_t n = (int32_t)q.round.size();
+            Round *const rd = q.round.data();
+            auto closed = [&](int32_t r) { return rd[r].count == 64 || edge - rd[r].base >= kSpan; };
+            int32_t low = q.low;
+            while (low < n && closed(low)) ++low;
+            q.low = low;
+            int32_t r = std::max(low, last[(size_t)v->slot] + 1);
+            while (r < n && closed(r)) ++r;
+            last[(size_t)v->slot] = r;
+            if (r == n) {
+                if (r % kGroup == 0) {
+                    if (q.entry.size() >= most) return false;
+                    q.entry.resize(q.entry.size() + 64 * kGroup, (uint32_t)kMaxCells);
+                }
+                q.round.push_back({edge, 0});
+            }
+            Round &t = q.round[(size_t)r];
+            q.entry[((size_t)(r / kGroup) * 64 + (size_t)t.count++) * kGroup + r % kGroup] =
+                (uint32_t)(edge - t.base) << kSlotBits | (uint32_t)(v->slot - in * per);
+        }
+        for (int32_t k = 0; k < kWaves && w * kWaves + k < nbins; ++k) {
+            Bin &q = bins[(size_t)k];
+            if (out->entries + q.entry.size() > most) return false;
+            if (!q.entry.empty())
+                memcpy(out->entry.get() + out->entries, q.entry.data(), q.entry.size() * sizeof(uint32_t));
+            out->entries += q.entry.size();
+            longest = std::max(longest, q.entry.size());
+            q.round.resize(q.entry.size() / 64, {0, 0});  // a round of padding reads edge 0
+            for (const Round &t : q.round) out->base.push_back(t.base);
+            out->first.push_back((int32_t)(out->base.size() / kGroup));
+        }
+    }
+    out->nbins = nbins;
+    out->per = per;
+    return longest * (size_t)nbins <= 2 * out->entries;
+}
+
+// Device memory for the plan's tables, filled from the host.
+struct Part {
+    const void *p;
+    size_t bytes;
+};
+
+hipError_t upload(pf_inc_plan *p, const Part *parts, int n) {
+    size_t total = 4;
+    for (int i = 0; i < n; ++i) total += parts[i].bytes;
+    hipError_t e = hipMalloc(&p->dev, total);
+    if (e != hipSuccess) {
+        p->dev = nullptr;
+        return e;
+    }
+    size_t at = 0;
+    for (int i = 0; i < n && e == hipSuccess; at += parts[i++].bytes)
+        if (parts[i].bytes) e = hipMemcpy((char *)p->dev + at, parts[i].p, parts[i].bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(p->dev);
+        p->dev = nullptr;
+    }
+    return e;
 }
 
 }  // namespace inc
@@ -87,6 +343,33 @@ pf_status pf_inc_plan_create(int32_t ncells, int32_t nedges, const int32_t *__re
         if (edge_to_cells[j] < 0 || edge_to_cells[j] >= ncells)
             return fail(PF_EINVAL, "edge " + std::to_string(j / 2) + " names a cell outside 0.." +
                                        std::to_string(ncells - 1));
+    pf_inc_plan *p = new (std::nothrow) pf_inc_plan;
+    if (!p) return fail(PF_ENOMEM, "plan allocation");
+    p->ncells = ncells;
+    p->nedges = nedges;
+    (void)hipGetDevice(&p->device);
+    // Lists are made as well where rounds find no memory, on either side.
+    inc::Rounds rounds;
+    bool made = false;
+    try {
+        made = inc::rounds_suit(ncells, nedges, edge_to_cells) && inc::make_rounds(ncells, nedges, edge_to_cells, &rounds);
+    } catch (const std::bad_alloc &) {
+    }
+    if (made) {
+        const size_t be = rounds.entries * 4, bb = rounds.base.size() * 4, bf = rounds.first.size() * 4;
+        const inc::Part parts[] = {{rounds.entry.get(), be}, {rounds.base.data(), bb}, {rounds.first.data(), bf}};
+        if (inc::upload(p, parts, 3) == hipSuccess) {
+            p->entry = (const inc::u2 *)p->dev;
+            p->base = (const inc::i2 *)((char *)p->dev + be);
+            p->first = (const int32_t *)((char *)p->dev + be + bb);
+            p->nbins = rounds.nbins;
+            p->per = rounds.per;
+            *plan = p;
+            return PF_OK;
+        }
+        (void)hipGetLastError();
+        rounds = inc::Rounds();
+    }
     // Counting sort of the (edge, slot) visits by cell, in visit order.
     std::vector<int32_t> off((size_t)ncells + 1, 0);
     for (int64_t j = 0; j < 2 * (int64_t)nedges; ++j) ++off[(size_t)edge_to_cells[j] + 1];
@@ -97,23 +380,11 @@ pf_status pf_inc_plan_create(int32_t ncells, int32_t nedges, const int32_t *__re
         idx[(size_t)fill[edge_to_cells[2 * (int64_t)i + 1]]++] = i;  // the second cell is incremented first
         idx[(size_t)fill[edge_to_cells[2 * (int64_t)i]]++] = i;
     }
-    pf_inc_plan *p = new (std::nothrow) pf_inc_plan;
-    if (!p) return fail(PF_ENOMEM, "plan allocation");
-    p->ncells = ncells;
-    p->nedges = nedges;
-    (void)hipGetDevice(&p->device);
     const size_t bo = off.size() * sizeof(int32_t), bi = idx.size() * sizeof(int32_t);
-    hipError_t e = hipMalloc(&p->dev, bo + bi + 4);
-    if (e != hipSuccess) {
+    const inc::Part parts[] = {{off.data(), bo}, {idx.data(), bi}};
+    if (hipError_t e = inc::upload(p, parts, 2)) {
         delete p;
-        return fail_hip(e, "plan allocation");
-    }
-    e = hipMemcpy(p->dev, off.data(), bo, hipMemcpyHostToDevice);
-    if (e == hipSuccess && bi) e = hipMemcpy((char *)p->dev + bo, idx.data(), bi, hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        (void)hipFree(p->dev);
-        delete p;
-        return fail_hip(e, "plan upload");
+        return fail_hip(e, "plan tables");
     }
     p->off = (const int32_t *)p->dev;
     p->idx = (const int32_t *)((char *)p->dev + bo);
@@ -131,9 +402,15 @@ pf_status pf_inc_plan_run(const pf_inc_plan *p, int32_t ncells, int32_t nedges, 
     const uintptr_t a = (uintptr_t)edge, b = (uintptr_t)cell;
     const uintptr_t na = (uintptr_t)nedges * 8, nb = (uintptr_t)ncells * 8;
     if (nedges > 0 && a < b + nb && b < a + na) return fail(PF_EALIAS, "edge and cell arrays overlap (restrict)");
-    const int grid = (int)((ncells + inc::kThreads - 1) / inc::kThreads);
-    hipLaunchKernelGGL(inc::k_gather, dim3(grid), dim3(inc::kThreads), 0, (hipStream_t)stream, p->off, p->idx, edge,
-                       cell, ncells);
+    if (p->nbins) {
+        const int grid = (p->nbins + inc::kWaves - 1) / inc::kWaves;
+        hipLaunchKernelGGL(inc::k_rounds, dim3(grid), dim3(64 * inc::kWaves), 0, (hipStream_t)stream, p->first, p->base,
+                           p->entry, edge, cell, ncells, p->per);
+    } else {
+        const int grid = (int)((ncells + inc::kThreads - 1) / inc::kThreads);
+        hipLaunchKernelGGL(inc::k_gather, dim3(grid), dim3(inc::kThreads), 0, (hipStream_t)stream, p->off, p->idx, edge,
+                           cell, ncells);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return PF_OK;

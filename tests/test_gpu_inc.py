@@ -40,6 +40,35 @@ def test_plan_bitwise(ncells, nedges):
     plan.close()
 
 
+@pytest.mark.parametrize("kind,ncells,nedges", [
+    ("random", 700001, 1400000), ("random", 4300000, 2700000), ("hub", 700001, 1400000), ("sparse", 700001, 5000000),
+    ("few", 1000, 1400000), ("ordered", 900000, 1400000)])
+def test_large_plans_bitwise(kind, ncells, nedges):
+    """Meshes above and around the sizes where a plan keeps its visits in
+    rounds: a remainder of cells in the last bin, more cells than one sweep
+    holds, a cell in very many edges, a bin visited a few times far apart,
+    few cells, and edges numbered along the cells."""
+    dev = device()
+    e2c, edge, cell = _random_mesh(nedges, ncells, nedges)
+    if kind == "hub":
+        e2c[::50, 0] = 12345
+    elif kind == "sparse":
+        e2c = np.maximum(e2c, 256)            # cells below 256 only as set here
+        e2c[[7, 2500000, 4999999], 0] = 3
+        e2c[4999998] = [255, 3]
+    elif kind == "ordered":
+        e2c[:, 0] = np.arange(nedges) * ncells // nedges
+        e2c[:, 1] = (e2c[:, 0] + 1) % ncells
+    edge[[5, 6]] = [np.inf, -0.0]
+    cell[-1] = -0.0
+    ref = oracle.edge_inc_f64(ncells, e2c, edge, cell)
+    plan = pf.IncPlan(ncells, e2c)
+    for _ in range(2):
+        got = plan.run(_t(edge, dev), _t(cell, dev)).cpu().numpy()
+        assert np.array_equal(got, ref, equal_nan=True)
+    plan.close()
+
+
 def test_plan_mesh_bitwise_and_repeatable():
     dev = device()
     m = synth.config_mesh()

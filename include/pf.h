@@ -71,8 +71,8 @@ typedef int32_t pf_status;
 /* Largest supported filter radius (filters up to 17 x 17). */
 #define PF_R_MAX 8
 /* Largest radius inside batch plans and served requests (9 x 9 filters):
- * the persistent batch kernel is built only for radii 0..4, where every
- * body fits in registers; larger radii run as single-image calls. */
+ * the batch kernel is built only for radii 0..4; larger radii run as
+ * single-image calls. */
 #define PF_BATCH_R_MAX 4
 
 /* Flags for single-image calls, batch plans and servers. */
@@ -262,8 +262,8 @@ pf_status pf_filter2d_u8(int32_t c, int32_t h, int32_t w, int32_t r, int32_t shi
 
 /* ---- single image with an explicit launch shape ----------------------------
  * The same computation as the call for `kind`/`variant`, bit for bit, on the
- * strip kernel (the batch kernel's) with the launch shape forced: rows_per_wave a multiple of 4 in 4..128, waves_per_group in
- * {1, 2, 4, 8}. Used by the autotuner and by tests that check results do
+ * strip kernel with the launch shape forced: rows_per_wave a multiple of 4
+ * in 4..128, waves_per_group in {1, 2, 4, 8}. Used by the autotuner and by tests that check results do
  * not depend on the launch shape. kind PF_KIND_2D requires variant
  * PF_VAR_DIRECT; PF_KIND_SEP accepts all three variants. For PF_KIND_SEP,
  * filt holds fx then fy (2*(2r+1) floats). */
@@ -277,15 +277,16 @@ pf_status pf_filter_f32_shaped(int32_t h, int32_t w, int32_t r, int32_t kind, in
 /* ---- tuning (profile-based auto-tuning, Sec. II, Fig. 1 flow) -------------
  * The tune table maps (context, kind, r, size class) to a variant and a
  * launch shape. Contexts: PF_TUNE_SINGLE for single-image calls,
- * PF_TUNE_BATCH for the persistent batch kernel of batch plans and servers
- * (FP32 kinds only; four waves per workgroup; direct or separable
- * variant). Size classes: 0 small (< 256*256 px), 1 medium, 2 large
+ * PF_TUNE_BATCH for batch plans and servers (FP32 kinds only; four waves
+ * per workgroup; direct or separable variant). Size classes: 0 small (< 256*256 px), 1 medium, 2 large
  * (> 1024*1024 px). A built-in default table is used until one is loaded.
  * Results depend on the variant only, never on the launch shape. FP32
- * single-image calls of the direct and separable variants run on LDS tiles
- * whose size the library chooses by the image's; an FP32 entry's shape is
- * that of the strip kernel, which runs PF_VAR_SEP_DIRECT (and images of a
- * few columns and over 2^28 rows). */
+ * single-image calls of the direct and separable variants, batch plans and
+ * servers run on LDS tiles whose size the library chooses by the image's or
+ * the batch's; an FP32 entry's shape is that of the strip kernel, which runs
+ * PF_VAR_SEP_DIRECT (and images of a few columns and over 2^28 rows).
+ * PF_TUNE_BATCH entries are set, loaded and saved as before and select
+ * nothing. */
 #define PF_TUNE_SINGLE 0
 #define PF_TUNE_BATCH  1
 
@@ -297,9 +298,8 @@ typedef struct pf_tune_entry {
     int32_t rows_per_wave;
     int32_t waves_per_group;
     float   us;               /* measured median time of the winning candidate (us), or 0:
-                                 one launch of the class image (PF_TUNE_SINGLE), one batch
-                                 launch of class images (PF_TUNE_BATCH, pf_autotune) or of
-                                 the whole tuned batch (PF_TUNE_BATCH, pf_batch_autotune) */
+                                 one launch of the class image (PF_TUNE_SINGLE), one launch
+                                 of the whole tuned batch (PF_TUNE_BATCH) */
     int32_t context;          /* PF_TUNE_SINGLE or PF_TUNE_BATCH */
 } pf_tune_entry;
 
@@ -320,30 +320,23 @@ pf_status pf_tune_save(const char *path);
  * (rows_per_wave in {8, 12, 16, 20, 24, 32, 48, 64}) x (waves_per_group in
  * {1, 2, 4, 8}) shape; for PF_KIND_U8 (r <= PF_U8_MFMA_R_MAX) also the
  * PF_VAR_MFMA variant at rows_per_wave in {16, 32, 48, 64} x
- * waves_per_group in {1, 2, 4, 8} within PF_U8_MFMA_TILE_MAX; and the
- * tile heights {8, 16, 32, 64} of the batch kernel on a batch of class
- * images (FP32 kinds). A candidate replaces the default only when at least
+ * waves_per_group in {1, 2, 4, 8} within PF_U8_MFMA_TILE_MAX. PF_TUNE_BATCH
+ * entries are not touched. A candidate replaces the default only when at least
  * 3% faster. Installs the winners and writes the table to `path` if it is
  * not NULL. Allocates and frees its own device buffers; synchronises the
  * device. */
 pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path);
-/* Workgroups (of four waves) per compute unit that persistent batch
- * launches use, a table-wide setting (saved with the table; reset to its
- * default, 1, by pf_tune_set and pf_tune_reset). `blocks_per_cu` in 1..8
- * sets it, 0 leaves it; the value before the call goes to `previous` if
- * not NULL. Fewer than fit at once is deliberate: on MI355X the fewest
- * tiles in flight ran fastest. Plans created earlier keep their grid. */
+/* A table-wide setting of earlier tables (workgroups per compute unit of
+ * batch launches), saved with the table and reset to its default, 1, by
+ * pf_tune_set and pf_tune_reset. `blocks_per_cu` in 1..8 sets it, 0 leaves
+ * it; the value before the call goes to `previous` if not NULL. Batch
+ * launches have one workgroup per tile whatever it is. */
 pf_status pf_tune_batch_blocks(int32_t blocks_per_cu, int32_t *previous);
-/* Tune the PF_TUNE_BATCH entries for one batch (the arguments of
- * pf_batch_plan_create and pf_batch_plan_run), timing whole-batch launches
- * on the device (median of 5 x `reps`): first a joint grid of workgroups
- * per compute unit (1..4, see pf_tune_batch_blocks) x one row-tile height
- * in {8, 16, 32, 64} for every key the batch uses, keeping the fastest
- * point; then for each (kind, r, size class) key the batch uses, the other
- * tile heights of that set and those up to 64 that fill whole row chunks of
- * the key's radius, keeping a change only when the batch gets at least 3%
- * faster. Single-image entries are not touched. Installs the result and
- * writes it to `path` if not NULL. Overwrites `out`. */
+/* Time one batch (the arguments of pf_batch_plan_create and
+ * pf_batch_plan_run) on the device (median of 5 x `reps` launches) and record
+ * the time in the PF_TUNE_BATCH entry of every (kind, r, size class) key it
+ * uses; the batch kernel has no shape left to choose. Single-image entries
+ * are not touched. Writes the table to `path` if not NULL. Overwrites `out`. */
 pf_status pf_batch_autotune(int32_t n,
                             PF_ARR(const int32_t, h, n), PF_ARR(const int32_t, w, n),
                             PF_ARR(const int32_t, r, n), PF_ARR(const int32_t, kind, n),
@@ -352,7 +345,7 @@ pf_status pf_batch_autotune(int32_t n,
                             PF_ARR(const float, in, npix), PF_ARR(const float, filt, nfilt),
                             PF_ARR(float, out, npix), int32_t reps, const char *path);
 
-/* ---- batch: many images, one persistent launch ---------------------------
+/* ---- batch: many images, one launch --------------------------------------
  * Arrays plus per-item offsets instead of arrays of pointers, the form the
  * paper gives OP2's rewritten kernel (Sec. III-A); every output element of
  * every image is an independent iteration (Sec. II-B.3), so all images'
@@ -361,8 +354,7 @@ pf_status pf_batch_autotune(int32_t n,
  * pixels at in + pix_off[i] and out + pix_off[i], radius r[i], filter kind
  * kind[i] with weights at filt + filt_off[i]. Offsets are in elements.
  * Plan creation validates everything (ranges inside npix / nfilt, images
- * disjoint), chooses each image's variant and shape from the tune table,
- * builds the tile table and uploads it to the device. The plan owns that
+ * disjoint), builds the tile table and uploads it to the device. The plan owns that
  * device table (and, with PF_BATCH_GRAPH, a captured hipGraph).
  * Variant choice depends only on (kind, r, pixels), never on the rest of
  * the batch, so each image's result equals what the single-image call with
@@ -384,15 +376,15 @@ pf_status pf_batch_plan_run(pf_batch_plan *plan, int64_t npix, int64_t nfilt,
                             PF_ARR(float, out, npix), void *stream);
 /* Per-image variant chosen by the plan (host array of n entries). */
 pf_status pf_batch_plan_variants(const pf_batch_plan *plan, int32_t n, PF_ARR(int32_t, variant, n));
-/* tasks: wave tiles in the plan; launches: kernels per run (1 or 2);
- * grid: workgroups of the main persistent launch. */
+/* tasks: tiles in the plan; launches: kernels per run (1); grid: workgroups
+ * of the launch. */
 pf_status pf_batch_plan_info(const pf_batch_plan *plan, PF_OUTP(int64_t, tasks),
                              PF_OUTP(int32_t, launches), PF_OUTP(int32_t, grid));
 pf_status pf_batch_plan_destroy(pf_batch_plan *plan);
 
 /* ---- serving: continuous batching under an HBM budget ----------------------
  * Independent calls (Sec. II-B.3) arriving over time share batches: the
- * filter requests of a batch run in one persistent launch (the batch form
+ * filter requests of a batch run in one launch (the batch form
  * above), its reductions (the `reduction` directive, Sec. II-B.3; OptiML's
  * sum, Sec. III-B) in the multi-array sum and histogram kernels.
  * A server owns a device arena of `hbm_budget_bytes` (results, uploaded

@@ -16,16 +16,15 @@ extern "C" {
 #endif
 
 /* Builds the host tables that pf_batch_plan_create would build for the same
- * arguments (same validation, same status on invalid input; tile heights
- * from the batch context of the active tune table) and replays on the host
- * where every wave tile of the persistent batch kernel reads and writes,
- * with the strip-geometry functions the kernel itself uses: every tile must
- * name a valid image, a strip and row band inside it, and every vector
- * load, halo load and unguarded vector store of each of its 64 lanes must
- * fall inside its image row; every image must lie inside the pixel arena.
+ * arguments (same validation, same status on invalid input) and replays on
+ * the host where every tile of the batch kernel reads and writes, with the
+ * tile-geometry functions the kernel itself uses: every tile must name a
+ * valid image and start inside it, every vector load must fall inside its
+ * image row and an unclamped tile's rows inside the image; every image must
+ * lie inside the pixel arena.
  * Batches are the arena-plus-offsets description of Sec. III-A; the check
  * is that each tile's accesses stay within its image's span of the arena.
- * tiles: number of wave tiles checked; violations: number found (PF_EINVAL
+ * tiles: number of tiles checked; violations: number found (PF_EINVAL
  * with the first described in pf_last_error() when > 0). */
 pf_status pf_batch_plan_check(int32_t n,
                               PF_ARR(const int32_t, h, n), PF_ARR(const int32_t, w, n),

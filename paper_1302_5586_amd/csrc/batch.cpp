@@ -1,11 +1,10 @@
-// Batch plans: many images of uneven sizes and radii in one persistent
+// Batch plans: many images of uneven sizes and radii in one
 // launch, optionally replayed from a hipGraph.
 //
 // The batch is described the way the paper rewrites OP2's kernel for
 // PENCIL (Sec. III-A): no arrays of pointers, only arenas plus per-image
 // offsets. Every image's outputs are independent iterations (Sec. II-B.3),
-// so all images' wave tiles form one flat list that a fixed grid of
-// workgroups walks with a static stride.
+// so all images' tiles form one flat list, a workgroup to each.
 #include <string.h>
 
 #include <algorithm>
@@ -21,18 +20,16 @@ struct pf_batch_plan {
     int32_t flags = 0;
     int device = -1;
     std::vector<int32_t> variant;  // per image
-    // Radius groups: 0 (radii 0..PF_BATCH_R_MAX); index 1 is kept empty.
-    int64_t ntasks[2] = {0, 0};
-    int32_t grid[2] = {0, 0};
-    int32_t mask[2] = {3, 3};  // compiled variant set of each group's kernel
-    int32_t wpg = 4;
-    void *dev = nullptr;  // descriptors and tile lists, one allocation
-    const pf::BatchImg *imgs[2] = {nullptr, nullptr};
-    const pf::BatchTask *tasks[2] = {nullptr, nullptr};
+    int64_t ntasks = 0;
+    int shape = 0;   // of the tiles (kBatchShapes)
+    int used = 3;    // variants in use, which select the kernel
+    void *dev = nullptr;  // descriptors and tile list, one allocation
+    const pf::BatchImg *imgs = nullptr;
+    const pf::BatchTask *tasks = nullptr;
     // Graph replay state.
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipGraphNode_t node[2] = {nullptr, nullptr};
+    hipGraphNode_t node = nullptr;
     const float *g_in = nullptr, *g_filt = nullptr;
     float *g_out = nullptr;
     std::mutex mu;
@@ -40,7 +37,7 @@ struct pf_batch_plan {
 
 namespace pf {
 
-// Sets kernel parameters for group g of plan p (pointers must outlive use).
+// Kernel parameters of a plan's launch (pointers must outlive use).
 struct BatchArgs {
     const BatchImg *imgs;
     const BatchTask *tasks;
@@ -59,13 +56,13 @@ struct BatchArgs {
     }
 };
 
-static hipKernelNodeParams node_params(pf_batch_plan *p, int g, BatchArgs &a) {
+static hipKernelNodeParams node_params(pf_batch_plan *p, BatchArgs &a) {
     a.fill();
     hipKernelNodeParams kp;
     memset(&kp, 0, sizeof kp);
-    kp.func = batch_kernel_fn(g, (p->flags & PF_FLAG_EXACT) != 0, p->mask[g]);
-    kp.gridDim = dim3(p->grid[g]);
-    kp.blockDim = dim3(p->wpg * 64);
+    kp.func = batch_kernel_fn((p->flags & PF_FLAG_EXACT) != 0, p->used, p->shape);
+    kp.gridDim = batch_grid(p->ntasks);
+    kp.blockDim = dim3(kTileThreads);
     kp.sharedMemBytes = 0;
     kp.kernelParams = a.params;
     kp.extra = nullptr;
@@ -73,9 +70,8 @@ static hipKernelNodeParams node_params(pf_batch_plan *p, int g, BatchArgs &a) {
 }
 
 // Validates a batch description (sizes, radii, kinds, arena ranges, no two
-// images overlapping) and builds the plan's host tables: per radius group
-// (all radii are in group 0, 0..PF_BATCH_R_MAX) the image descriptors with their variant and tile height from
-// the batch context of the tune table, and the flat list of wave tiles.
+// images overlapping) and builds the plan's host tables: the image
+// descriptors with their variant, and the flat list of tiles.
 pf_status build_plan_tables(int32_t n, const int32_t *h, const int32_t *w, const int32_t *r, const int32_t *kind,
                             const int64_t *pix_off, const int64_t *filt_off, int64_t npix, int64_t nfilt,
                             int32_t flags, PlanTables *t) {
@@ -108,21 +104,12 @@ pf_status build_plan_tables(int32_t n, const int32_t *h, const int32_t *w, const
             return fail(PF_EALIAS, "two images overlap in the pixel arena");
 
     t->variant.resize(n);
-    int64_t ntiles[2] = {0, 0};
+    t->imgs.resize(n);
     for (int i = 0; i < n; ++i) {
-        const int64_t px = (int64_t)h[i] * w[i];
-        pf_tune_entry e;
-        if (flags & PF_BATCH_NO_TUNE) {
-            e.variant = kind[i] == PF_KIND_SEP ? PF_VAR_SEPARABLE : PF_VAR_DIRECT;
-            e.rows_per_wave = 16;
-        } else {
-            e = tune_lookup_batch(kind[i], r[i], px);
-        }
         const int var = kind[i] == PF_KIND_2D ? PF_VAR_DIRECT : PF_VAR_SEPARABLE;
         t->variant[i] = var;
-        const int g = r[i] <= 4 ? 0 : 1;
-        t->used[g] |= 1 << var;
-        BatchImg d;
+        t->used |= 1 << var;
+        BatchImg &d = t->imgs[i];
         d.in_off = pix_off[i];
         d.out_off = pix_off[i];
         d.filt_off = filt_off[i];
@@ -130,74 +117,60 @@ pf_status build_plan_tables(int32_t n, const int32_t *h, const int32_t *w, const
         d.w = w[i];
         d.r = r[i];
         d.var = var;
-        d.by = e.rows_per_wave;
-        const int64_t nt = set_strips(d);
-        if (ntiles[g] + nt > INT32_MAX) return fail(PF_EUNSUPPORTED, "batch has more than 2^31-1 wave tiles");
-        ntiles[g] += nt;
-        t->imgs[g].push_back(d);
     }
-    for (int g = 0; g < 2; ++g) {
-        t->tasks[g].reserve((size_t)ntiles[g]);
-        for (size_t i = 0; i < t->imgs[g].size(); ++i) append_tiles(t->tasks[g], (int32_t)i, t->imgs[g][i]);
-    }
+    int64_t ntiles = 0;
+    t->shape = batch_shape(t->imgs, &ntiles);
+    if (ntiles > INT32_MAX) return fail(PF_EUNSUPPORTED, "batch has more than 2^31-1 tiles");
+    t->tasks.reserve((size_t)ntiles);
+    for (int i = 0; i < n; ++i) append_tiles(t->tasks, i, t->imgs[i]);
     return PF_OK;
 }
 
-// Replays, on the host, where every wave tile of the tables reads and
-// writes, with the geometry functions the FP32 strip kernel itself calls
-// (strip_mode, lane_col, vec_load_col, halo_load_col, tile_strip): each
-// tile must name a valid image and a strip and row band inside it; each
-// 16-byte load of a lane (kStripFast, kStripEdge), each halo load of an
-// aligned strip (kStripFast) and each plain 16-byte store (kStripFast
-// without halo lanes) must lie in [0, w) of its row; and the image must lie
-// inside the pixel arena. Loads of single clamped columns and stores
-// through range-checked buffer resources stay in bounds by construction.
-// Returns the number of violations; the first is described in *first.
+// Replays, on the host, where every tile of the tables reads and writes, with
+// the geometry functions the FP32 tile kernel itself calls (tile_inside,
+// tile_load_col): each tile must name a valid image and lie in it; the staged
+// rows and columns of a tile that loads without clamping must lie in the
+// image, each 16-byte load of one at the edge inside its row; and the image
+// must lie inside the pixel arena. Clamped rows, loads of single clamped
+// columns and the stores, guarded per column and row, stay in bounds by
+// construction. Returns the number of violations; the first is described in
+// *first.
 int64_t check_plan_tables(const PlanTables &t, int64_t npix, std::string *first) {
     int64_t bad = 0;
-    auto report = [&](int g, size_t k, const std::string &what) {
-        if (!bad++) *first = "group " + std::to_string(g) + " tile " + std::to_string(k) + ": " + what;
+    auto report = [&](size_t k, const std::string &what) {
+        if (!bad++) *first = "tile " + std::to_string(k) + ": " + what;
     };
-    for (int g = 0; g < 2; ++g) {
-        const std::vector<BatchImg> &imgs = t.imgs[g];
-        for (const BatchImg &d : imgs)
-            if (d.in_off < 0 || d.in_off + (int64_t)d.h * d.w > npix || d.out_off < 0 ||
-                d.out_off + (int64_t)d.h * d.w > npix) {
-                report(g, 0, "image outside the arena");
-            }
-        for (size_t k = 0; k < t.tasks[g].size(); ++k) {
-            const BatchTask tk = t.tasks[g][k];
-            if (tk.img < 0 || tk.img >= (int)imgs.size()) {
-                report(g, k, "image index out of range");
-                continue;
-            }
-            const BatchImg &d = imgs[tk.img];
-            if (tk.tile < 0 || tk.tile >= d.strips_x * d.strips_y) {
-                report(g, k, "tile number out of range");
-                continue;
-            }
-            int sx = 0, sy = 0;
-            tile_strip(kTileColMajorF32, tk.tile, d.strips_x, d.strips_y, sx, sy);
-            const int x0 = sx * strip_width(d.r), y0 = sy * d.by;
-            const int rows = std::min(d.by, d.h - y0);
-            if (x0 < 0 || x0 >= d.w || y0 < 0 || rows < 1 || y0 + rows > d.h) {
-                report(g, k, "strip origin or row band outside the image");
-                continue;
-            }
-            const int mode = strip_mode(d.r, x0, d.w);
-            for (int lane = 0; lane < 64; ++lane) {
-                const int xs = lane_col(d.r, x0, lane);
-                if (mode != kStripTiny) {
-                    const int c = vec_load_col(d.r, mode, xs, d.w);
-                    if (c < 0 || c + 4 > d.w) report(g, k, "16-byte load outside the row (lane " + std::to_string(lane) + ")");
-                }
-                if (mode == kStripFast && aligned_strip(d.r)) {
-                    const int c = halo_load_col(d.r, lane < 32, x0, d.w);
-                    if (c < 0 || c + d.r > d.w) report(g, k, "halo load outside the row (lane " + std::to_string(lane) + ")");
-                }
-                if (mode == kStripFast && idle_lanes(d.r) == 0 && (xs < 0 || xs + 4 > d.w))
-                    report(g, k, "16-byte store outside the row (lane " + std::to_string(lane) + ")");
-            }
+    for (const BatchImg &d : t.imgs)
+        if (d.in_off < 0 || d.in_off + (int64_t)d.h * d.w > npix || d.out_off < 0 ||
+            d.out_off + (int64_t)d.h * d.w > npix)
+            report(0, "image outside the arena");
+    const BatchShape sh = kBatchShapes[t.shape];
+    for (size_t k = 0; k < t.tasks.size(); ++k) {
+        const BatchTask tk = t.tasks[k];
+        if (tk.img < 0 || tk.img >= (int)t.imgs.size()) {
+            report(k, "image index out of range");
+            continue;
+        }
+        const BatchImg &d = t.imgs[tk.img];
+        if (tk.tile < 0 || tk.tile >= (int64_t)d.tiles_x * d.tiles_y) {
+            report(k, "tile number out of range");
+            continue;
+        }
+        const int ty = tk.tile / d.tiles_x, tx = tk.tile - ty * d.tiles_x;
+        const int x0 = tx * sh.w, y0 = ty * sh.h, pad = tile_pad(d.r);
+        if (x0 < 0 || x0 >= d.w || y0 < 0 || y0 >= d.h) {
+            report(k, "tile origin outside the image");
+            continue;
+        }
+        if (tile_inside(d.r, sh.w, sh.h, x0, y0, d.h, d.w)) {
+            if (x0 - pad < 0 || x0 + sh.w + pad > d.w || y0 - d.r < 0 || y0 + sh.h + d.r > d.h)
+                report(k, "unclamped load outside the image");
+            continue;
+        }
+        if (d.w < 4) continue;
+        for (int c = -pad; c < sh.w + pad; c += 4) {
+            const int at = x0 + tile_load_col(c, x0, d.w);
+            if (at < 0 || at + 4 > d.w) report(k, "16-byte load outside the row (column " + std::to_string(x0 + c) + ")");
         }
     }
     return bad;
@@ -228,33 +201,21 @@ pf_status pf_batch_plan_create(int32_t n, const int32_t *__restrict h, const int
     p->flags = flags;
     (void)hipGetDevice(&p->device);
     p->variant = t.variant;
-    size_t bytes = 0;
-    size_t off_imgs[2], off_tasks[2];
-    for (int g = 0; g < 2; ++g) {
-        const int64_t ntiles = (int64_t)t.tasks[g].size();
-        p->ntasks[g] = ntiles;
-        p->mask[g] = batch_mask(g, t.used[g]);
-        p->grid[g] = ntiles ? batch_grid(g, (flags & PF_FLAG_EXACT) != 0, p->mask[g], p->wpg, ntiles) : 0;
-        off_imgs[g] = bytes;
-        bytes += t.imgs[g].size() * sizeof(BatchImg);
-        bytes = (bytes + 255) & ~(size_t)255;
-        off_tasks[g] = bytes;
-        bytes += t.tasks[g].size() * sizeof(BatchTask);
-        bytes = (bytes + 255) & ~(size_t)255;
-    }
-    hipError_t e = hipMalloc(&p->dev, std::max<size_t>(bytes, 256));
+    p->ntasks = (int64_t)t.tasks.size();
+    p->shape = t.shape;
+    p->used = t.used;
+    const size_t bi = (t.imgs.size() * sizeof(BatchImg) + 255) & ~(size_t)255;
+    const size_t bytes = bi + t.tasks.size() * sizeof(BatchTask);
+    hipError_t e = hipMalloc(&p->dev, bytes);
     if (e != hipSuccess) {
         delete p;
         return fail_hip(e, "plan descriptor allocation");
     }
-    std::vector<char> host(std::max<size_t>(bytes, 256), 0);
-    for (int g = 0; g < 2; ++g) {
-        if (!t.imgs[g].empty()) memcpy(host.data() + off_imgs[g], t.imgs[g].data(), t.imgs[g].size() * sizeof(BatchImg));
-        if (!t.tasks[g].empty())
-            memcpy(host.data() + off_tasks[g], t.tasks[g].data(), t.tasks[g].size() * sizeof(BatchTask));
-        p->imgs[g] = (const BatchImg *)((char *)p->dev + off_imgs[g]);
-        p->tasks[g] = (const BatchTask *)((char *)p->dev + off_tasks[g]);
-    }
+    std::vector<char> host(bytes, 0);
+    memcpy(host.data(), t.imgs.data(), t.imgs.size() * sizeof(BatchImg));
+    memcpy(host.data() + bi, t.tasks.data(), t.tasks.size() * sizeof(BatchTask));
+    p->imgs = (const BatchImg *)p->dev;
+    p->tasks = (const BatchTask *)((char *)p->dev + bi);
     e = hipMemcpy(p->dev, host.data(), host.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(p->dev);
@@ -277,7 +238,7 @@ pf_status pf_batch_plan_check(int32_t n, const int32_t *__restrict h, const int3
     pf_status st = build_plan_tables(n, h, w, r, kind, pix_off, filt_off, npix, nfilt, flags, &t);
     if (st) return st;
     std::string first;
-    *tiles = (int64_t)(t.tasks[0].size() + t.tasks[1].size());
+    *tiles = (int64_t)t.tasks.size();
     *violations = check_plan_tables(t, npix, &first);
     if (*violations) return fail(PF_EINVAL, first);
     return PF_OK;
@@ -290,55 +251,38 @@ pf_status pf_batch_plan_run(pf_batch_plan *p, int64_t npix, int64_t nfilt, const
     if (npix != p->npix || nfilt != p->nfilt) return fail(PF_EINVAL, "arena sizes differ from the plan's");
     if (!in || !filt || !out) return fail(PF_EINVAL, "null arena pointer");
     if (((uintptr_t)in | (uintptr_t)filt | (uintptr_t)out) % 4) return fail(PF_EINVAL, "arenas must be 4-byte aligned");
-    const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out, nb = (uintptr_t)npix * 4;
-    if (a < b + nb && b < a + nb) return fail(PF_EALIAS, "input and output arenas overlap (restrict)");
+    const uintptr_t i0 = (uintptr_t)in, b = (uintptr_t)out, nb = (uintptr_t)npix * 4;
+    if (i0 < b + nb && b < i0 + nb) return fail(PF_EALIAS, "input and output arenas overlap (restrict)");
     const uintptr_t f = (uintptr_t)filt, fb = (uintptr_t)nfilt * 4;
     if (f < b + nb && b < f + fb) return fail(PF_EALIAS, "filter and output arenas overlap (restrict)");
     hipStream_t s = (hipStream_t)stream;
     const bool exact = (p->flags & PF_FLAG_EXACT) != 0;
     std::lock_guard<std::mutex> lk(p->mu);
     if (!(p->flags & PF_BATCH_GRAPH)) {
-        for (int g = 0; g < 2; ++g) {
-            if (!p->ntasks[g]) continue;
-            hipError_t e = launch_batch(g, exact, p->mask[g], p->imgs[g], p->tasks[g], (int)p->ntasks[g], p->grid[g],
-                                        p->wpg, in, filt, out, s);
-            if (e != hipSuccess) return fail_hip(e, "batch launch");
-        }
+        hipError_t e = launch_batch(exact, p->used, p->shape, p->imgs, p->tasks, p->ntasks, in, filt, out, s);
+        if (e != hipSuccess) return fail_hip(e, "batch launch");
         return PF_OK;
     }
     hipError_t e = hipSuccess;
+    BatchArgs a{p->imgs, p->tasks, (int)p->ntasks, in, filt, out, {}};
+    hipKernelNodeParams kp = node_params(p, a);
     if (!p->exec) {
-        // Build the graph once: one kernel node per non-empty group, in order.
+        // Build the graph once: the launch as its only node.
         if ((e = hipGraphCreate(&p->graph, 0)) != hipSuccess) return fail_hip(e, "graph create");
-        hipGraphNode_t prev = nullptr;
-        for (int g = 0; g < 2; ++g) {
-            if (!p->ntasks[g]) continue;
-            BatchArgs a{p->imgs[g], p->tasks[g], (int)p->ntasks[g], in, filt, out, {}};
-            hipKernelNodeParams kp = node_params(p, g, a);
-            e = hipGraphAddKernelNode(&p->node[g], p->graph, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
-            if (e != hipSuccess) return fail_hip(e, "graph kernel node");
-            prev = p->node[g];
-        }
+        if ((e = hipGraphAddKernelNode(&p->node, p->graph, nullptr, 0, &kp)) != hipSuccess)
+            return fail_hip(e, "graph kernel node");
         if ((e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0)) != hipSuccess) {
             p->exec = nullptr;
             return fail_hip(e, "graph instantiate");
         }
-        p->g_in = in;
-        p->g_filt = filt;
-        p->g_out = out;
     } else if (in != p->g_in || filt != p->g_filt || out != p->g_out) {
         // Re-point the replay at the new arenas.
-        for (int g = 0; g < 2; ++g) {
-            if (!p->ntasks[g]) continue;
-            BatchArgs a{p->imgs[g], p->tasks[g], (int)p->ntasks[g], in, filt, out, {}};
-            hipKernelNodeParams kp = node_params(p, g, a);
-            if ((e = hipGraphExecKernelNodeSetParams(p->exec, p->node[g], &kp)) != hipSuccess)
-                return fail_hip(e, "graph node update");
-        }
-        p->g_in = in;
-        p->g_filt = filt;
-        p->g_out = out;
+        if ((e = hipGraphExecKernelNodeSetParams(p->exec, p->node, &kp)) != hipSuccess)
+            return fail_hip(e, "graph node update");
     }
+    p->g_in = in;
+    p->g_filt = filt;
+    p->g_out = out;
     if ((e = hipGraphLaunch(p->exec, s)) != hipSuccess) return fail_hip(e, "graph launch");
     return PF_OK;
 }
@@ -355,9 +299,10 @@ pf_status pf_batch_plan_info(const pf_batch_plan *p, int64_t *const __restrict t
                              int32_t *const __restrict grid) {
     clear_error();
     if (!p || !tasks || !launches || !grid) return fail(PF_EINVAL, "null argument");
-    *tasks = p->ntasks[0] + p->ntasks[1];
-    *launches = (p->ntasks[0] > 0) + (p->ntasks[1] > 0);
-    *grid = p->ntasks[0] ? p->grid[0] : p->grid[1];
+    *tasks = p->ntasks;
+    *launches = 1;
+    const dim3 g = batch_grid(p->ntasks);
+    *grid = (int32_t)(g.x * g.y);
     return PF_OK;
 }
 

@@ -103,7 +103,7 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // Compile-time loop: f(std::integral_constant<int, I>) for I in [B, E).
 // Every lambda passed here is marked always_inline: a lambda the inliner
 // leaves as a call keeps the locals it captures by reference on the stack
-// (scratch memory), which the persistent batch kernel must not use.
+// (scratch memory).
 template <int B, int E, class F>
 __device__ __forceinline__ void static_for(F &&f) {
     if constexpr (B < E) {
@@ -591,48 +591,6 @@ __global__ __launch_bounds__(512) void k_filter_f32(const float *__restrict__ in
     tile_xy(t, strips_x, strips_y, sx, sy);
     const int y0 = sy * by;
     strip_f32<R, VAR, EXACT>(in, fa, fb, out, h, w, sx * strip_width(R), y0, min(by, h - y0), lane);
-}
-
-// Persistent batch kernel: a fixed grid of workgroups walks the list of all
-// images' wave tiles with a static stride (tiles in image order, row-major
-// inside each image). Each entry names an image and a tile; the image
-// descriptor gives the radius, variant, tile height and arena offsets.
-template <int RLO, int RHI, bool EXACT, int VMASK>
-__global__ __launch_bounds__(512) void k_batch_f32(const BatchImg *__restrict__ imgs,
-                                                   const BatchTask *__restrict__ tasks, int ntasks,
-                                                   const float *__restrict__ in, const float *__restrict__ filt,
-                                                   float *__restrict__ out) {
-    const int wpg = blockDim.x / kLanes;
-    const int wave = uniform(threadIdx.x / kLanes);
-    const int lane = threadIdx.x % kLanes;
-    const int stride = gridDim.x * wpg;
-    for (int t = xcd_remap(blockIdx.x, gridDim.x) * wpg + wave; t < ntasks; t += stride) {
-        const BatchTask tk = tasks[t];
-        const BatchImg d = imgs[uniform(tk.img)];
-        int sx, sy;
-        tile_xy(uniform(tk.tile), d.strips_x, d.strips_y, sx, sy);
-        const int y0 = sy * d.by;
-        const int rows = min(d.by, d.h - y0);
-        const float *src = global_at(in, d.in_off);
-        float *dst = global_at(out, d.out_off);
-        const float *fa = global_at(filt, d.filt_off);
-        const float *fb = fa + 2 * d.r + 1;
-        // Only the variants in VMASK are compiled in: the register budget of
-        // the kernel is the largest of its bodies.
-        static_for<RLO, RHI + 1>([&](auto rc) __attribute__((always_inline)) {
-            constexpr int RR = decltype(rc)::value;
-            if (d.r == RR) {
-                static_for<0, 3>([&](auto vc) __attribute__((always_inline)) {
-                    constexpr int VV = decltype(vc)::value;
-                    if constexpr ((VMASK >> VV) & 1) {
-                        if (d.var == VV)
-                            strip_f32<RR, VV, EXACT, PF_BATCH_CHUNK>(src, fa, fb, dst, d.h, d.w, sx * strip_width(RR), y0,
-                                                            rows, lane);
-                    }
-                });
-            }
-        });
-    }
 }
 
 // --------------------------------------------------------------- uint8 ---

@@ -1,8 +1,5 @@
-// Radius dispatch for the single-image kernels, the uint8 kernels and the
-// batch kernels' entry points.
-#include <algorithm>
-#include <mutex>
-
+// Radius dispatch for the single-image kernels and the uint8 kernels, and the
+// batch kernel's launch.
 #include "filter_body.h"
 
 namespace pf {
@@ -84,57 +81,20 @@ hipError_t launch_u8(int r, int var, const uint8_t *in, const int8_t *filt, uint
     }
 }
 
-void *batch_kernel_fn(int group, bool exact, int mask) {
-    if (group != 0) return nullptr;
-    switch (mask) {
-        case 1: return exact ? batch_fn<0, 1, 1>() : batch_fn<0, 0, 1>();
-        case 2: return exact ? batch_fn<0, 1, 2>() : batch_fn<0, 0, 2>();
-        default: return exact ? batch_fn<0, 1, 3>() : batch_fn<0, 0, 3>();
+void *batch_kernel_fn(bool exact, int used, int shape) {
+    switch (used) {
+        case 1: return exact ? batch_fn<1, 1>(shape) : batch_fn<0, 1>(shape);
+        case 2: return exact ? batch_fn<1, 2>(shape) : batch_fn<0, 2>(shape);
+        default: return exact ? batch_fn<1, 3>(shape) : batch_fn<0, 3>(shape);
     }
 }
 
-int batch_grid_limit(int group, bool exact, int mask, int wpg) {
-    // Cached per (device, exact, mask, waves per group): the occupancy query
-    // is host work that every server batch would otherwise repeat.
-    static std::mutex mu;
-    static int cache[64][2][4][9] = {};
-    const int dev = std::min(std::max(dev_info().device, 0), 63);
-    const int m = std::min(std::max(mask, 0), 3), wq = std::min(std::max(wpg, 0), 8);
-    {
-        std::lock_guard<std::mutex> lk(mu);
-        if (group == 0 && cache[dev][exact][m][wq]) return cache[dev][exact][m][wq];
-    }
-    int blocks = 0;
-    void *fn = batch_kernel_fn(group, exact, mask);
-    if (!fn ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, wpg * dev::kLanes, 0) != hipSuccess ||
-        blocks < 1)
-        blocks = 1;
-    const int limit = blocks * dev_info().cus;
-    if (group == 0) {
-        std::lock_guard<std::mutex> lk(mu);
-        cache[dev][exact][m][wq] = limit;
-    }
-    return limit;
-}
-
-int batch_grid(int group, bool exact, int mask, int wpg, int64_t ntiles) {
-    const int fit = batch_grid_limit(group, exact, mask, wpg);
-    const int64_t want = (int64_t)tune_batch_blocks_per_cu() * dev_info().cus;
-    const int64_t need = (ntiles + wpg - 1) / wpg;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, fit), need));
-}
-
-hipError_t launch_batch(int group, bool exact, int mask, const BatchImg *imgs, const BatchTask *tasks, int ntasks,
-                        int grid, int wpg, const float *in, const float *filt, float *out, hipStream_t s) {
-#define PF_LB(G, E, M) launch_batch_g<G, E, M>(imgs, tasks, ntasks, grid, wpg, in, filt, out, s)
-    if (group != 0) return hipErrorInvalidValue;
-    switch (mask) {
-        case 1: return exact ? PF_LB(0, 1, 1) : PF_LB(0, 0, 1);
-        case 2: return exact ? PF_LB(0, 1, 2) : PF_LB(0, 0, 2);
-        default: return exact ? PF_LB(0, 1, 3) : PF_LB(0, 0, 3);
-    }
-#undef PF_LB
+hipError_t launch_batch(bool exact, int used, int shape, const BatchImg *imgs, const BatchTask *tasks, int64_t ntasks,
+                        const float *in, const float *filt, float *out, hipStream_t s) {
+    int n = (int)ntasks;
+    void *params[] = {&imgs, &tasks, &n, &in, &filt, &out};
+    return hipLaunchKernel(batch_kernel_fn(exact, used, shape), batch_grid(ntasks), dim3(kTileThreads), params, 0,
+                           s);
 }
 
 }  // namespace pf

@@ -5,8 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
-
 #include <vector>
 
 #include "pf.h"
@@ -33,8 +33,7 @@ constexpr int strip_width(int r) { return 4 * (64 - 2 * idle_lanes(r)); }
 // The uint8 strip keeps its halo lanes at every radius.
 constexpr int strip_width_u8(int r) { return 4 * (64 - 2 * halo_lanes(r)); }
 
-// ---- strip geometry, shared by the FP32 strip kernels and the host-side
-// check of batch plans (constexpr functions compile for host and device).
+// ---- strip geometry of the FP32 strip kernel.
 
 // How a strip loads its rows (uniform over the wave):
 //   kStripFast: every lane's 4 columns lie inside the image (a halo lane
@@ -47,16 +46,12 @@ constexpr int strip_width_u8(int r) { return 4 * (64 - 2 * halo_lanes(r)); }
 constexpr int kStripFast = 0, kStripEdge = 1, kStripTiny = 2;
 
 // Rows per pipelined chunk of the FP32 strip: a multiple of K = 2r+1 (ring
-// residues stay compile-time constants) near `chunk` rows. Single-image
-// launches take 8, the persistent batch kernel 12 (both measured on
-// MI355X). Rows past the last whole chunk of a tile are taken in groups of
+// residues stay compile-time constants) near `chunk` rows (8 measured best).
+// Rows past the last whole chunk of a tile are taken in groups of
 // 2r+1 with a wait per group, so tile heights that fill whole chunks skip
-// that tail (the tuners try them).
+// that tail (the tuner tries them).
 #ifndef PF_CHUNK
 #define PF_CHUNK 8
-#endif
-#ifndef PF_BATCH_CHUNK
-#define PF_BATCH_CHUNK 12
 #endif
 constexpr int chunk_rows_of(int r, int chunk) {
     return (2 * r + 1) * (chunk / (2 * r + 1) > 0 ? chunk / (2 * r + 1) : 1);
@@ -111,9 +106,34 @@ constexpr void tile_strip(bool colmajor, int t, int strips_x, int strips_y, int 
     }
 }
 
-// One image of a batch as the persistent kernel sees it. `var` is the
-// executed variant (PF_VAR_*), `by` rows per wave tile; the image's wave
-// tiles are numbered column-major over (strip x, strip y).
+// ---- tile geometry, shared by the FP32 tile kernels and the host-side check
+// of batch plans.
+
+// Columns staged left and right of a tile: the radius in whole 16-byte vectors.
+constexpr int tile_pad(int r) { return 4 * ((r + 3) / 4); }
+
+// Whether the tw x th tile at (x0, y0) and its staged halo lie inside the
+// image, so that it is loaded without clamping (with 32-bit row offsets).
+constexpr bool tile_inside(int r, int tw, int th, int x0, int y0, int h, int w) {
+    return x0 >= tile_pad(r) && w - x0 >= tw + tile_pad(r) && y0 >= r && h - y0 >= th + r && w <= 1 << 24;
+}
+
+// Column, relative to x0, of the 16-byte load that serves columns c .. c+3 of
+// a tile at the image's edge: the nearest inside the row (w >= 4).
+constexpr int tile_load_col(int c, int x0, int w) { return clamp_int(c, -x0, w - 4 - x0); }
+
+// Tiles of a batch launch, columns x rows: 64 x 16 while all of the batch's
+// fit on the chip at once (8 workgroups of 4 waves on each of 256 CUs), since
+// the time is then one tile's; 256 x 16 beyond (512 images 268 us, with 128 x
+// 16 284 us, 64 x 32 312 us, 64 x 16 380 us).
+struct BatchShape {
+    int w, h;
+};
+constexpr BatchShape kBatchShapes[2] = {{64, 16}, {256, 16}};
+constexpr int64_t kBatchSmallTiles = 8 * 256;
+
+// One image of a batch as the batch kernel sees it. `var` is the executed
+// variant (PF_VAR_*); its tiles are numbered row by row, tiles_x to a row.
 // Element offsets are added to the kernel's base pointers as integers, so a
 // descriptor may also carry an absolute address (byte address / 4) with a
 // null base.
@@ -122,48 +142,62 @@ struct BatchImg {
     int64_t out_off;
     int64_t filt_off;
     int32_t h, w, r, var;
-    int32_t by, strips_x, strips_y, pad;
+    int32_t tiles_x, tiles_y;
 };
 
-// One entry of a wave's tile list: the image (index into the descriptor
+// One entry of a batch's tile list: the image (index into the descriptor
 // array) and the tile's number inside the image.
 struct BatchTask {
     int32_t img, tile;
 };
 
-// Fills strips_x and strips_y of a descriptor whose r, h, w and by are set;
-// returns its wave-tile count.
-inline int64_t set_strips(BatchImg &d) {
-    d.strips_x = (d.w + strip_width(d.r) - 1) / strip_width(d.r);
-    d.strips_y = (d.h + d.by - 1) / d.by;
-    d.pad = 0;
-    return (int64_t)d.strips_x * d.strips_y;
+inline int64_t batch_tiles(int h, int w, int shape) {
+    const BatchShape t = kBatchShapes[shape];
+    return (((int64_t)w + t.w - 1) / t.w) * (((int64_t)h + t.h - 1) / t.h);
 }
 
-// Appends the wave tiles of image `img` (descriptor d) to a batch's tile list.
+// The shape for the images of a batch (h and w set), whose tiles_x and
+// tiles_y it fills; *tiles: how many there are.
+inline int batch_shape(std::vector<BatchImg> &imgs, int64_t *tiles) {
+    int64_t n[2] = {0, 0};
+    for (const BatchImg &d : imgs)
+        for (int s = 0; s < 2; ++s) n[s] += batch_tiles(d.h, d.w, s);
+    const int shape = n[0] <= kBatchSmallTiles ? 0 : 1;
+    const BatchShape t = kBatchShapes[shape];
+    for (BatchImg &d : imgs) {
+        d.tiles_x = (int32_t)(((int64_t)d.w + t.w - 1) / t.w);
+        d.tiles_y = (int32_t)(((int64_t)d.h + t.h - 1) / t.h);
+    }
+    *tiles = n[shape];
+    return shape;
+}
+
+// Appends the tiles of image `img` (descriptor d) to a batch's tile list.
 inline void append_tiles(std::vector<BatchTask> &list, int32_t img, const BatchImg &d) {
-    const int32_t n = d.strips_x * d.strips_y;
+    const int32_t n = d.tiles_x * d.tiles_y;
     for (int32_t t = 0; t < n; ++t) list.push_back({img, t});
 }
 
-// Host tables of a batch plan (batch.cpp): per radius group (0: r 0..4,
-// 1: unused, radii above PF_BATCH_R_MAX are rejected) the image descriptors and the flat wave-tile list, the variant
-// of each image, and the variant set each group uses.
+// Host tables of a batch plan (batch.cpp): the image descriptors, the flat
+// tile list and the shape of its tiles, the variant of each image, and the
+// set of variants used (bit v: PF_VAR_*).
 struct PlanTables {
-    std::vector<BatchImg> imgs[2];
-    std::vector<BatchTask> tasks[2];
+    std::vector<BatchImg> imgs;
+    std::vector<BatchTask> tasks;
     std::vector<int32_t> variant;
-    int used[2] = {0, 0};
+    int shape = 0, used = 0;
 };
 pf_status build_plan_tables(int32_t n, const int32_t *h, const int32_t *w, const int32_t *r, const int32_t *kind,
                             const int64_t *pix_off, const int64_t *filt_off, int64_t npix, int64_t nfilt,
                             int32_t flags, PlanTables *t);
 int64_t check_plan_tables(const PlanTables &t, int64_t npix, std::string *first);
 
-// Workgroups of a batch launch over `ntiles` wave tiles: `blocks_per_cu`
-// per compute unit (from the tune table), at most what fits at once, at
-// most one tile per wave.
-int batch_grid(int group, bool exact, int mask, int wpg, int64_t ntiles);
+// Workgroups of a batch launch, one per tile: x is kept well inside the 2^32
+// work items of a launch dimension.
+inline dim3 batch_grid(int64_t ntasks) {
+    const int64_t x = std::min<int64_t>(ntasks, 1 << 22);
+    return dim3((unsigned)x, (unsigned)((ntasks + x - 1) / x));
+}
 
 // Size class used by the tune table.
 inline int size_class(int64_t pixels) {
@@ -205,12 +239,10 @@ hipError_t launch_u8_mfma(int r, const uint8_t *in, const int8_t *filt, uint8_t 
                           int shift, int rpw, int wpg, hipStream_t s);
 // Whether the uint8 variant runs at radius r with this launch shape.
 bool u8_variant_ok(int var, int r, int by, int wpg);
-// Persistent batch kernel over images with r <= 4 (group 0; group 1 is not
-// built and fails with hipErrorInvalidValue), compiled with the variants of
-// `mask` (see batch_mask).
-hipError_t launch_batch(int group, bool exact, int mask, const BatchImg *imgs, const BatchTask *tasks,
-                        int ntasks, int grid, int wpg, const float *in, const float *filt, float *out,
-                        hipStream_t s);
+// Batch kernel over images with r <= PF_BATCH_R_MAX and variants of `used`
+// (a set of bits).
+hipError_t launch_batch(bool exact, int used, int shape, const BatchImg *imgs, const BatchTask *tasks, int64_t ntasks,
+                        const float *in, const float *filt, float *out, hipStream_t s);
 // Fused chain of `passes` 2D passes under a border rule (chain.hip); also
 // the single-pass filter for borders other than clamp.
 hipError_t launch_chain(int r, bool exact, const float *in, const float *filt, float *out, int h, int w, int passes,
@@ -248,9 +280,7 @@ hipError_t launch_reduce_batch(const ReduceReq *reqs, const int32_t *sum_ids, in
 // its address on the current device.
 int64_t sum_noalloc_max();
 hipError_t sum_scratch(void **ptr);
-// Workgroups of the batch kernel that fit on the device at once.
-int batch_grid_limit(int group, bool exact, int mask, int wpg);
-void *batch_kernel_fn(int group, bool exact, int mask);
+void *batch_kernel_fn(bool exact, int used, int shape);
 
 // Per-radius FP32 launchers, each defined in its own instantiation unit.
 template <int R>
@@ -284,45 +314,25 @@ PF_DECL_RADIUS(7)
 PF_DECL_RADIUS(8)
 #undef PF_DECL_RADIUS
 
-// Batch kernels per (radius group, exact, variant mask), each in its own
-// unit. Masks: bit v for variant v: 1 (direct only), 2 (separable only)
-// and 3 (both). Only group 0 (radii 0..PF_BATCH_R_MAX) is built. The separable-as-2D
-// variant is not compiled into batch kernels (it runs in single-image calls
-// only) so that the persistent kernel stays small.
-template <int G, int E, int M>
-void *batch_fn();
-template <int G, int E, int M>
-hipError_t launch_batch_g(const BatchImg *imgs, const BatchTask *tasks, int ntasks, int grid, int wpg,
-                          const float *in, const float *filt, float *out, hipStream_t s);
-#define PF_DECL_BATCH(G, E, M)                                                                                 \
-    template <>                                                                                                \
-    void *batch_fn<G, E, M>();                                                                                 \
-    template <>                                                                                                \
-    hipError_t launch_batch_g<G, E, M>(const BatchImg *imgs, const BatchTask *tasks, int ntasks, int grid,      \
-                                       int wpg, const float *in, const float *filt, float *out, hipStream_t s);
-PF_DECL_BATCH(0, 0, 1)
-PF_DECL_BATCH(0, 1, 1)
-PF_DECL_BATCH(0, 0, 2)
-PF_DECL_BATCH(0, 1, 2)
-PF_DECL_BATCH(0, 0, 3)
-PF_DECL_BATCH(0, 1, 3)
+// Batch kernels per (exact, variant set), each in its own unit; the shape is
+// an index into kBatchShapes. Sets: bit v for variant v: 1 (direct only), 2
+// (separable only) and 3 (both). The separable-as-2D variant runs in
+// single-image calls only.
+template <int E, int M>
+void *batch_fn(int shape);
+#define PF_DECL_BATCH(E, M) \
+    template <>             \
+    void *batch_fn<E, M>(int shape);
+PF_DECL_BATCH(0, 1)
+PF_DECL_BATCH(1, 1)
+PF_DECL_BATCH(0, 2)
+PF_DECL_BATCH(1, 2)
+PF_DECL_BATCH(0, 3)
+PF_DECL_BATCH(1, 3)
 #undef PF_DECL_BATCH
 
-// Smallest compiled variant mask of a group that covers `used` (bit v set
-// if some image runs variant v).
-inline int batch_mask(int group, int used) {
-    if (group == 1) return 3;
-    if ((used & ~1) == 0) return 1;
-    if ((used & ~2) == 0) return 2;
-    return 3;
-}
-
-// Tune table lookups (tune.cpp): single-image calls, and the persistent
-// batch kernel of plans and servers.
+// Tune table lookup of single-image calls (tune.cpp).
 pf_tune_entry tune_lookup(int kind, int r, int64_t pixels);
-pf_tune_entry tune_lookup_batch(int kind, int r, int64_t pixels);
-// Workgroups per compute unit of persistent batch launches (tune.cpp).
-int tune_batch_blocks_per_cu();
 
 bool valid_shape(int by, int wpg);
 

@@ -7,7 +7,7 @@
 // Sec. II-B.3 and Sec. III-B). The engine thread admits requests first-come
 // first-served while their device bytes fit in the budget, packs admitted
 // requests into a batch whenever one of its streams is idle and launches
-// there: the persistent filter kernel for the filter requests, then the
+// there: the batch kernel for the filter requests, then the
 // multi-array sum and histogram kernels. Completions are observed through
 // per-stream events, so new arrivals run while earlier batches are still on
 // the device. Each filter request's variant and tile shape come from the
@@ -107,7 +107,7 @@ enum State { kQueued = 0, kAdmitted = 1, kLaunched = 2, kDone = 3, kFailed = 4 }
 struct Request {
     int64_t ticket = 0;
     int32_t op = kOpFilter;
-    int32_t h = 0, w = 0, r = 0, kind = 0, var = 0, by = 16;  // filter requests
+    int32_t h = 0, w = 0, r = 0, kind = 0, var = 0;  // filter requests
     int64_t n = 0;                                             // reductions: elements
     const void *in_dev = nullptr;   // resident input, or null when uploaded
     std::vector<uint8_t> in_host;   // upload mode: copy of the caller's input
@@ -257,7 +257,7 @@ pf_status ensure_slot(Slot &sl, size_t need, size_t need_ws) {
 pf_status launch_slot(pf_server *s, Slot &sl, bool after_copies) {
     const bool exact = (s->flags & PF_FLAG_EXACT) != 0;
     auto arena_addr = [&](int64_t off) { return (int64_t)((uintptr_t)s->arena_dev + off); };
-    // Filter requests: descriptors for the persistent batch kernel.
+    // Filter requests: descriptors for the batch kernel.
     std::vector<BatchImg> imgs;
     int64_t ntiles = 0;
     std::vector<float> weights;
@@ -279,9 +279,7 @@ pf_status launch_slot(pf_server *s, Slot &sl, bool after_copies) {
             d.w = q->w;
             d.r = q->r;
             d.var = q->var;
-            d.by = q->by;
             used |= 1 << q->var;
-            ntiles += set_strips(d);
             imgs.push_back(d);
         } else {
             ReduceReq d;
@@ -306,14 +304,12 @@ pf_status launch_slot(pf_server *s, Slot &sl, bool after_copies) {
             rreqs.push_back(d);
         }
     }
-    const int wpg = 4;
-    int mask = 1, grid = 0;
     std::vector<BatchTask> tasks;
+    int shape = 0;
+    if (!imgs.empty()) shape = batch_shape(imgs, &ntiles);
     if (ntiles) {
         if (ntiles > INT32_MAX || sum_tasks.size() > INT32_MAX || hist_tasks.size() > INT32_MAX)
             return fail(PF_EUNSUPPORTED, "batch too large");
-        mask = batch_mask(0, used);
-        grid = batch_grid(0, exact, mask, wpg, ntiles);
         tasks.reserve((size_t)ntiles);
         for (size_t i = 0; i < imgs.size(); ++i) append_tiles(tasks, (int32_t)i, imgs[i]);
     }
@@ -371,8 +367,8 @@ pf_status launch_slot(pf_server *s, Slot &sl, bool after_copies) {
         return fail_hip(e, "server descriptor upload");
     char *d = (char *)sl.dev;
     if (ntiles) {
-        e = launch_batch(0, exact, mask, (const BatchImg *)(d + o_i), (const BatchTask *)(d + o_t), (int)ntiles, grid,
-                         wpg, nullptr, (const float *)(d + o_w), nullptr, sl.stream);
+        e = launch_batch(exact, used, shape, (const BatchImg *)(d + o_i), (const BatchTask *)(d + o_t), ntiles, nullptr,
+                         (const float *)(d + o_w), nullptr, sl.stream);
         if (e != hipSuccess) return fail_hip(e, "server batch launch");
     }
     if (!rreqs.empty()) {
@@ -599,9 +595,7 @@ pf_status make_request(pf_server *s, int32_t h, int32_t w, int32_t r, int32_t ki
     const int k = 2 * r + 1;
     const int nf = kind == PF_KIND_2D ? k * k : 2 * k;
     q->filt.assign(filt, filt + nf);
-    const pf_tune_entry e = tune_lookup_batch(kind, r, (int64_t)h * w);
     q->var = kind == PF_KIND_2D ? PF_VAR_DIRECT : PF_VAR_SEPARABLE;
-    q->by = e.rows_per_wave;
     if (pf_status st = stage_input(s, *q, in, in_is_host != 0, stream, order)) return st;
     q->t_arrival = arrival_ns ? arrival_ns : now_ns();
     *out = q;

@@ -3,11 +3,12 @@
 // in "profile-based iterative compilation and auto-tuning", Sec. II, Fig. 1).
 //
 // The table is keyed by (context, kind, radius, size class). Context 0
-// holds the shapes of single-image calls, context 1 those of the persistent
-// batch kernel (batch plans and servers): the two launch differently (one
-// image and many small waves against a fixed grid walking many images), so
-// they are tuned and stored apart and neither tuner touches the other's
-// entries. Results never depend on the launch shape (each output's
+// holds the shapes of single-image calls, context 1 those of batch plans and
+// servers. The batch kernel takes its tiles' shape from the batch alone, so
+// context 1 and the workgroups per compute unit are kept for tables written
+// before it did (set, saved and loaded as they were) and select nothing; the
+// batch tuner records how long the batch takes.
+// Results never depend on the launch shape (each output's
 // arithmetic is fixed), only on the variant, and the variant depends only
 // on the key.
 #include <math.h>
@@ -28,8 +29,8 @@ namespace {
 
 // Tile heights (multiples of 4 in 8..64) whose rows fill whole chunks of
 // the FP32 strip's row pipeline for radius r (no one-by-one tail rows).
-std::vector<int> whole_chunk_heights(int r, int chunk) {
-    const int ch = chunk_rows_of(r, chunk);
+std::vector<int> whole_chunk_heights(int r) {
+    const int ch = chunk_rows_of(r, PF_CHUNK);
     std::vector<int> v;
     for (int by = ch; by <= 64; by += ch)
         if (by % 4 == 0 && by >= 8) v.push_back(by);
@@ -40,11 +41,9 @@ std::vector<int> whole_chunk_heights(int r, int chunk) {
 constexpr int kKinds = 3;  // PF_KIND_2D, PF_KIND_SEP, PF_KIND_U8
 constexpr int kSizes = 3;
 constexpr int kContexts = 2;  // PF_TUNE_SINGLE, PF_TUNE_BATCH
-constexpr int kBatchWaves = 4;  // waves per workgroup of persistent batch launches
+constexpr int kBatchWaves = 4;  // the only waves_per_group of context 1
 
-// Workgroups per compute unit of a persistent batch launch. One (four
-// waves, one per SIMD) measured best on MI355X: the fewest tiles in flight
-// keep the window of HBM pages the batch touches at once compact.
+// Default and limit of the table's workgroups per compute unit.
 constexpr int kBatchBlocksPerCu = 1;
 constexpr int kBatchBlocksPerCuMax = 8;
 
@@ -90,8 +89,7 @@ bool entry_ok(const pf_tune_entry &e) {
         return false;
     if (!valid_shape(e.rows_per_wave, e.waves_per_group)) return false;
     if (e.context == PF_TUNE_BATCH) {
-        // Batches hold FP32 images only; their kernel runs four waves per
-        // workgroup and compiles only the direct and separable bodies.
+        // Batches hold FP32 images only, and run them as what they are.
         if (e.kind == PF_KIND_U8 || e.waves_per_group != kBatchWaves) return false;
         return e.variant == (e.kind == PF_KIND_SEP ? PF_VAR_SEPARABLE : PF_VAR_DIRECT);
     }
@@ -123,16 +121,6 @@ bool parse_number(const std::string &obj, const char *key, double *out) {
 pf_tune_entry tune_lookup(int kind, int r, int64_t pixels) {
     std::lock_guard<std::mutex> lk(g_mu);
     return g_table.e[PF_TUNE_SINGLE][kind][r][size_class(pixels)];
-}
-
-pf_tune_entry tune_lookup_batch(int kind, int r, int64_t pixels) {
-    std::lock_guard<std::mutex> lk(g_mu);
-    return g_table.e[PF_TUNE_BATCH][kind][r][size_class(pixels)];
-}
-
-int tune_batch_blocks_per_cu() {
-    std::lock_guard<std::mutex> lk(g_mu);
-    return g_table.batch_blocks_per_cu;
 }
 
 // ---------------------------------------------------------------- autotune
@@ -179,67 +167,16 @@ pf_status time_launch(F &&launch, int nbuf, int reps, int trials, hipStream_t s,
     return PF_OK;
 }
 
-// Representative image of each size class, and how many of them one timed
-// batch launch holds (context 1 entries are timed on such a batch, context
-// 0 entries on single launches of one image).
-void class_shape(int sc, int kind, int *h, int *w, int *n) {
+// Representative image of each size class.
+void class_shape(int sc, int kind, int *h, int *w) {
     static const int hs[kSizes] = {160, 600, 4096};
     static const int ws[kSizes] = {200, 700, 4096};
-    static const int ns[kSizes] = {1024, 96, 4};
     *h = hs[sc];
     *w = ws[sc];
-    *n = ns[sc];
     if (kind == PF_KIND_U8 && sc == 2) {  // planar RGB at 1080p
         *h = 1080;
         *w = 1920;
     }
-}
-
-// Time one persistent batch launch over n images of h x w with radius r,
-// filter kind `kind` and row tiles of `by`, reading in[] and writing out[]
-// (n*h*w floats each) with the weights at filt.
-pf_status time_batch_class(int kind, int r, int h, int w, int n, int by, const float *in, float *out,
-                           const float *filt, int reps, hipStream_t s, float *us) {
-    const int g = r <= 4 ? 0 : 1;
-    const int var = kind == PF_KIND_SEP ? PF_VAR_SEPARABLE : PF_VAR_DIRECT;
-    const int mask = batch_mask(g, 1 << var);
-    std::vector<BatchImg> imgs(n);
-    int64_t ntiles = 0;
-    for (int i = 0; i < n; ++i) {
-        BatchImg &d = imgs[i];
-        d.in_off = d.out_off = (int64_t)i * h * w;
-        d.filt_off = 0;
-        d.h = h;
-        d.w = w;
-        d.r = r;
-        d.var = var;
-        d.by = by;
-        ntiles += set_strips(d);
-    }
-    const int wpg = 4;
-    const int grid = batch_grid(g, false, mask, wpg, ntiles);
-    std::vector<BatchTask> tasks;
-    for (int i = 0; i < n; ++i) append_tiles(tasks, i, imgs[i]);
-    void *dev = nullptr;
-    const size_t bi = imgs.size() * sizeof(BatchImg), bt = tasks.size() * sizeof(BatchTask);
-    hipError_t e = hipMalloc(&dev, bi + bt);
-    if (e != hipSuccess) return fail_hip(e, "autotune descriptors");
-    e = hipMemcpy(dev, imgs.data(), bi, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy((char *)dev + bi, tasks.data(), bt, hipMemcpyHostToDevice);
-    pf_status st = PF_OK;
-    if (e != hipSuccess) {
-        st = fail_hip(e, "autotune descriptors");
-    } else {
-        st = time_launch(
-            [&](int) {
-                return launch_batch(g, false, mask, (const BatchImg *)dev, (const BatchTask *)((char *)dev + bi),
-                                    (int)tasks.size(), grid, wpg, in, filt, out, s);
-            },
-            1, reps, 5, s, us);
-    }
-    (void)hipStreamSynchronize(s);
-    (void)hipFree(dev);
-    return st;
 }
 
 }  // namespace
@@ -427,8 +364,8 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
     auto better = [](float us, const pf_tune_entry &best) { return best.us == INFINITY || us < 0.97f * best.us; };
     for (int sc = 0; sc < kSizes && st == PF_OK; ++sc) {
         for (int kind = 0; kind < kKinds && st == PF_OK; ++kind) {
-            int h, w, n;
-            class_shape(sc, kind, &h, &w, &n);
+            int h, w;
+            class_shape(sc, kind, &h, &w);
             const size_t px = (size_t)h * w;
             const size_t planes = kind == PF_KIND_U8 ? 3 : 1;
             // rotating buffer sets of one image (uint8: 3 planes)
@@ -451,7 +388,7 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
                 std::vector<int> cand(bys, bys + 4);
                 if (kind == PF_KIND_U8) cand.insert(cand.end(), {12, 20, 24, 48});
                 else
-                    for (int by : whole_chunk_heights(r, PF_CHUNK))
+                    for (int by : whole_chunk_heights(r))
                         if (std::find(cand.begin(), cand.end(), by) == cand.end()) cand.push_back(by);
                 for (int by : cand)
                     for (int wpg : wpgs)
@@ -517,20 +454,6 @@ pf_status pf_autotune(int32_t r_max, int32_t reps, const char *path) {
                 }
                 if (st != PF_OK) break;
                 out.push_back(best);
-                // ---- batch kernel: tile heights, on a batch of n class images
-                if (kind == PF_KIND_U8 || r > PF_BATCH_R_MAX) continue;
-                pf_tune_entry bb = default_entry(PF_TUNE_BATCH, kind, r, sc);
-                bb.us = INFINITY;
-                for (int by : {bb.rows_per_wave, 8, 32, 64}) {
-                    float us = 0.0f;
-                    st = time_batch_class(kind, r, h, w, n, by, in, outb, filt, reps, s, &us);
-                    if (st != PF_OK) break;
-                    if (better(us, bb)) {
-                        bb.rows_per_wave = by;
-                        bb.us = us;
-                    }
-                }
-                if (st == PF_OK) out.push_back(bb);
             }
         }
     }
@@ -588,67 +511,8 @@ pf_status pf_batch_autotune(int32_t n, const int32_t *__restrict h, const int32_
         }
         std::sort(keys.begin(), keys.end());
     }
-    // A joint grid first: workgroups per compute unit x one tile height for
-    // every key the batch uses (the two interact: the grid sets how many
-    // tiles are in flight, the tile height how many tiles there are). The
-    // best point is kept outright.
-    auto set_all = [&](int by) {
-        std::lock_guard<std::mutex> lk(g_mu);
-        for (const auto &k : keys) g_table.e[PF_TUNE_BATCH][k[0]][k[1]][k[2]].rows_per_wave = by;
-    };
-    float best = INFINITY;
-    int best_bpc = 1, best_by = 16;
-    pf_status st = PF_OK;
-    for (int bpc = 1; bpc <= 4 && st == PF_OK; ++bpc) {
-        for (int by : {8, 16, 32, 64}) {
-            {
-                std::lock_guard<std::mutex> lk(g_mu);
-                g_table.batch_blocks_per_cu = bpc;
-            }
-            set_all(by);
-            float us = 0.0f;
-            st = measure(&us);
-            if (st != PF_OK) break;
-            if (us < best) {
-                best = us;
-                best_bpc = bpc;
-                best_by = by;
-            }
-        }
-    }
-    if (st == PF_OK) {
-        std::lock_guard<std::mutex> lk(g_mu);
-        g_table.batch_blocks_per_cu = best_bpc;
-    }
-    set_all(best_by);
-    // Then coordinate descent over the batch-context keys the batch uses, one
-    // key at a time: a new tile height is kept only when the whole batch gets
-    // at least 3% faster. Single-image entries are not touched.
-    for (const auto &k : keys) {
-        if (st != PF_OK) break;
-        std::vector<int> bys = {8, 16, 32, 64};
-        for (int by : whole_chunk_heights(k[1], PF_BATCH_CHUNK))
-            if (std::find(bys.begin(), bys.end(), by) == bys.end()) bys.push_back(by);
-        for (int by : bys) {
-            int keep = 0;
-            {
-                std::lock_guard<std::mutex> lk(g_mu);
-                pf_tune_entry &e = g_table.e[PF_TUNE_BATCH][k[0]][k[1]][k[2]];
-                if (e.rows_per_wave == by) continue;
-                keep = e.rows_per_wave;
-                e.rows_per_wave = by;
-            }
-            float us = 0.0f;
-            st = measure(&us);
-            if (st == PF_OK && us < 0.97f * best) {
-                best = us;
-            } else {
-                std::lock_guard<std::mutex> lk(g_mu);
-                g_table.e[PF_TUNE_BATCH][k[0]][k[1]][k[2]].rows_per_wave = keep;
-            }
-            if (st != PF_OK) break;
-        }
-    }
+    float best = 0.0f;
+    const pf_status st = measure(&best);
     (void)hipStreamDestroy(s);
     if (st != PF_OK) return st;
     {

@@ -210,3 +210,46 @@ def test_batch_autotune_keeps_results(tmp_path):
             assert_close(gi, ref, tol, "tuned batch image %d (%dx%d r=%d kind=%d)" % (i, h, w, r, k))
     finally:
         pf.tune_reset()
+
+
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("kinds", ["2d", "sep", "both"])
+@pytest.mark.parametrize("exact", [False, True])
+def test_batch_tiles_equal_single_calls(large, kinds, exact):
+    """Sizes around the tiles' edges (64 and 256 columns, 16 rows, images
+    under 4 columns, halos that leave the image on both sides), each radius,
+    in batches of few tiles and of many, which take tiles of another shape:
+    every image equals its single-image call bit for bit."""
+    dev = device()
+    import torch
+    rng = np.random.default_rng(91)
+    sizes = [(1, 1), (2, 3), (17, 4), (5, 63), (16, 64), (33, 65), (15, 255), (16, 256), (40, 257), (49, 525)]
+    if large:
+        sizes += [(700, 1030), (515, 777), (300, 1290)]
+    imgs, filts, ks = [], [], []
+    for i, (h, w) in enumerate(sizes):
+        for r in range(pf.PF_BATCH_R_MAX + 1):
+            sep = kinds == "sep" or (kinds == "both" and (i + r) % 2)
+            imgs.append(rng.standard_normal((h, w)).astype(np.float32))
+            filts.append(rng.standard_normal(2 * (2 * r + 1) if sep else (2 * r + 1) ** 2).astype(np.float32))
+            ks.append(pf.KIND_SEP if sep else pf.KIND_2D)
+    pk = pf.pack_batch(imgs, filts, ks)
+    x, fl = _t(pk.pixels, dev), _t(pk.filters, dev)
+    out = torch.full_like(x, float("nan"))
+    plan = pf.BatchPlan(pk.h, pk.w, pk.r, pk.kind, pk.pix_off, pk.filt_off, x.numel(), fl.numel(), exact=exact)
+    plan.run(x, fl, out)
+    got = out.cpu().numpy()
+    used = np.zeros(x.numel(), bool)
+    for i, img in enumerate(imgs):
+        h, w, r = int(pk.h[i]), int(pk.w[i]), int(pk.r[i])
+        span = slice(pk.pix_off[i], pk.pix_off[i] + h * w)
+        used[span] = True
+        f = _t(filts[i], dev)
+        k = 2 * r + 1
+        if ks[i] == pf.KIND_2D:
+            ref = pf.filter2d(_t(img, dev), f.reshape(k, k), exact=exact)
+        else:
+            ref = pf.filter_sep(_t(img, dev), f[:k].contiguous(), f[k:].contiguous(), exact=exact)
+        assert np.array_equal(got[span].reshape(h, w), ref.cpu().numpy()), (h, w, r, ks[i])
+    assert np.isnan(got[~used]).all()
+    plan.close()

@@ -111,7 +111,8 @@ __device__ __forceinline__ void stage_taps(const int8_t *__restrict__ filt, uint
 // byte selector (identity inside; a broadcast of the edge byte outside);
 // else one byte load per byte, of the clamped column. Loads are
 // unconditional (clamped rows) and issued kMfmaStage at a time; `between`
-// runs after the first batch is issued, before any of it is written.
+// runs once in every wave: after the first batch is issued, before any of it
+// is written, or alone in a wave that has no rows to stage.
 template <int R, bool ALIGNED, class F>
 __device__ __forceinline__ void stage_rows(const uint8_t *__restrict__ plane, uint8_t *rows, int h, int w, int x0,
                                            int y0, int nrows, int wave, int nwaves, int lane, F &&between) {
@@ -138,6 +139,7 @@ __device__ __forceinline__ void stage_rows(const uint8_t *__restrict__ plane, ui
     }
     uint8_t *dst = rows + lr * kMfmaRow + G * q;
     const int step = PER * nwaves;
+    if (PER * wave >= nrows) between();
     for (int base = PER * wave; base < nrows; base += kMfmaStage * step) {
         gran_t v[kMfmaStage];
 #pragma unroll
@@ -192,6 +194,7 @@ __device__ __forceinline__ void stage_rows_wide(const uint8_t *__restrict__ plan
     const uint32_t xo = (uint32_t)(x0 - kMfmaLeft + G * q);
     uint8_t *dst = rows + lr * kMfmaRow + G * q;
     const int step = PER * nwaves;
+    if (PER * wave >= nrows) between();
     for (int base = PER * wave; base < nrows; base += ST * step) {
         u4 v[ST];
 #pragma unroll

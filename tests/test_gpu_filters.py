@@ -440,3 +440,22 @@ def test_tiles_match_the_oracle_and_the_strip_kernel(r):
             assert np.array_equal(gots, strips, equal_nan=True), "sep r=%d %dx%d differs from the strip" % (r, h, w)
         assert np.array_equal(got2, ref2, equal_nan=True), "exact 2d r=%d %dx%d" % (r, h, w)
         assert np.array_equal(gots, refs, equal_nan=True), "exact sep r=%d %dx%d" % (r, h, w)
+
+
+@pytest.mark.parametrize("wpg", [1, 2, 4, 8])
+@pytest.mark.parametrize("r", range(1, pf.PF_U8_MFMA_R_MAX + 1))
+def test_u8_mfma_short_last_tile(r, wpg):
+    """A last row of tiles with so few rows that some waves of its workgroups
+    have none to stage, whose threads stage their share of the taps all the
+    same: every remainder of 1 to 8 rows."""
+    dev = device()
+    rng = np.random.default_rng(60 + r)
+    f = rng.integers(-8, 9, (2 * r + 1, 2 * r + 1), dtype=np.int8)
+    try:
+        pf.tune_set(_u8_entries(r, pf.VAR_MFMA, 16, wpg))
+        for rest in range(1, 9):
+            img = rng.integers(0, 256, (1, 16 * wpg + rest, 400), dtype=np.uint8)
+            got = pf.filter2d_u8(_t(img, dev), _t(f, dev), 5).cpu().numpy()
+            assert np.array_equal(got, oracle.filter2d_u8(img, f, 5)), rest
+    finally:
+        pf.tune_reset()

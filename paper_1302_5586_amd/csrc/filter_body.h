@@ -633,19 +633,22 @@ struct WeightsU8 {
     }
 };
 
+// A dword at any byte: rows of a width that is no multiple of 4 start
+// anywhere, and global memory is read and written at any alignment.
+typedef uint32_t u32u __attribute__((aligned(1)));
+
 // The dword a lane loads for bytes xs .. xs+3 of a row; the byte selector
 // of load_sel_u8 turns it into those bytes clamped to [0, w-1], packed
-// little-endian. kFast (rows 4-byte aligned, every lane's bytes end inside
-// the row): the dword at xs (at 0 for the halo lane left of byte 0, which
-// replicates byte 0). kEdge (aligned rows, w >= 4): the nearest in-bounds
-// dword. kTiny (unaligned rows or w < 4): one clamped byte load per byte,
-// already in place.
+// little-endian. kFast (every lane's bytes end inside the row): the dword at
+// xs (at 0 for the halo lane left of byte 0, which replicates byte 0). kEdge
+// (w >= 4): the nearest in-bounds dword. kTiny (w < 4): one clamped byte load
+// per byte, already in place.
 template <int MODE>
 __device__ __forceinline__ uint32_t load_u8(const uint8_t *__restrict__ row, int xs, int w) {
     if constexpr (MODE == kFast) {
-        return ld(reinterpret_cast<const uint32_t *>(row + max(xs, 0)));
+        return ld(reinterpret_cast<const u32u *>(row + max(xs, 0)));
     } else if constexpr (MODE == kEdge) {
-        return ld(reinterpret_cast<const uint32_t *>(row + clampi(xs, 0, w - 4)));
+        return ld(reinterpret_cast<const u32u *>(row + clampi(xs, 0, w - 4)));
     } else {
         uint32_t v = 0;
 #pragma unroll
@@ -849,8 +852,8 @@ __device__ __forceinline__ void rows_u8(const WeightsU8<R> &wt, const uint8_t *_
 // halo lanes on each side.
 template <int R>
 __device__ __forceinline__ void strip_u8(const uint8_t *__restrict__ in, const int8_t *__restrict__ filt,
-                                         uint8_t *__restrict__ out, int h, int w, int shift, bool aligned,
-                                         int x0, int y0, int rows, int lane) {
+                                         uint8_t *__restrict__ out, int h, int w, int shift, int x0, int y0,
+                                         int rows, int lane) {
     constexpr int K = 2 * R + 1;
     constexpr int NB = halo_lanes(R);
     WeightsU8<R> wt(filt);
@@ -861,10 +864,10 @@ __device__ __forceinline__ void strip_u8(const uint8_t *__restrict__ in, const i
     for (int s = 0; s < K; ++s)
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[s][k] = 0;
-    if (aligned && x0 + 4 * (kLanes - NB) <= w) {
+    if (x0 + 4 * (kLanes - NB) <= w) {
         wt.sel = load_sel_u8<kFast>(xs, w);
         rows_u8<R, kFast>(wt, in, out, acc, h, w, shift, xs, y0, rows, out_lane);
-    } else if (aligned && w >= 4) {
+    } else if (w >= 4) {
         wt.sel = load_sel_u8<kEdge>(xs, w);
         rows_u8<R, kEdge>(wt, in, out, acc, h, w, shift, xs, y0, rows, out_lane);
     } else {
@@ -877,8 +880,8 @@ __device__ __forceinline__ void strip_u8(const uint8_t *__restrict__ in, const i
 // strips_y): the rows are spread evenly over the tiles of a strip column.
 template <int R>
 __global__ __launch_bounds__(512) void k_filter_u8(const uint8_t *__restrict__ in, const int8_t *__restrict__ filt,
-                                                   uint8_t *__restrict__ out, int h, int w, int shift, int aligned,
-                                                   int strips_x, int strips_y, int tasks_per_plane, int ntasks) {
+                                                   uint8_t *__restrict__ out, int h, int w, int shift, int strips_x,
+                                                   int strips_y, int tasks_per_plane, int ntasks) {
     const int wpg = blockDim.x / kLanes;
     const int wave = uniform(threadIdx.x / kLanes);
     const int lane = threadIdx.x % kLanes;
@@ -891,7 +894,7 @@ __global__ __launch_bounds__(512) void k_filter_u8(const uint8_t *__restrict__ i
     const int y0 = (int)((int64_t)sy * h / strips_y);
     const int y1 = (int)((int64_t)(sy + 1) * h / strips_y);
     const int64_t plane = (int64_t)p * h * w;
-    strip_u8<R>(in + plane, filt, out + plane, h, w, shift, aligned != 0, sx * strip_width_u8(R), y0, y1 - y0, lane);
+    strip_u8<R>(in + plane, filt, out + plane, h, w, shift, sx * strip_width_u8(R), y0, y1 - y0, lane);
 }
 
 }  // namespace dev
@@ -957,9 +960,8 @@ hipError_t launch_u8_t(const uint8_t *in, const int8_t *filt, uint8_t *out, int 
     if (ntasks64 > INT32_MAX) return hipErrorInvalidValue;
     const int ntasks = (int)ntasks64;
     const int grid = cdiv(ntasks, wpg);
-    const int aligned = (w % 4 == 0) && ((uintptr_t)in % 4 == 0) && ((uintptr_t)out % 4 == 0);
-    hipLaunchKernelGGL((k_filter_u8<R>), dim3(grid), dim3(wpg * kLanes), 0, s, in, filt, out, h, w, shift, aligned,
-                       strips_x, (int)strips_y, (int)per_plane, ntasks);
+    hipLaunchKernelGGL((k_filter_u8<R>), dim3(grid), dim3(wpg * kLanes), 0, s, in, filt, out, h, w, shift, strips_x,
+                       (int)strips_y, (int)per_plane, ntasks);
     return hipGetLastError();
 }
 

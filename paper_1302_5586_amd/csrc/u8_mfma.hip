@@ -34,6 +34,12 @@
 // each wave reads its B operands with 16-byte LDS loads, eight column
 // blocks at a time. The bias is added back exactly as 128 * sum(weights),
 // the initial value of every accumulator.
+//
+// Rows of a width that is no multiple of 4 start at any byte. They take the
+// same wide loads and stores, which global memory and its buffers accept at
+// any alignment; with a load and a store per byte such images took 37.9 us at
+// 3 x 1080 x 1919, 7 x 7 (now 7.5 us; 3 x 1080 x 1920 5.7 us) and 141 us at 3
+// x 2160 x 3839 (now 17.2 us).
 #include "filter_body.h"
 
 namespace pf {
@@ -104,16 +110,15 @@ __device__ __forceinline__ void stage_taps(const int8_t *__restrict__ filt, uint
 // kMfmaGran. Rows 0 .. nrows - 1 and granules 0 .. kMfmaFill - 1: every byte
 // a nonzero tap reads. The lanes of a wave stage 64 / kMfmaFill rows per
 // pass, lane kMfmaFill k + q granule q of one of them, so the column part of
-// every load (clamp, byte selectors) is the lane's own constant. ALIGNED
-// (rows 4-byte aligned and w >= G, so w is a multiple of 4 and each dword
-// of a granule is either inside the image or wholly left or right of it):
-// one G-byte load from the clamped position, each dword of it picked by a
-// byte selector (identity inside; a broadcast of the edge byte outside);
-// else one byte load per byte, of the clamped column. Loads are
+// every load (clamp, byte selectors) is the lane's own constant. WIDE (w >=
+// G): one G-byte load, of any alignment, from the clamped position, whose
+// bytes a selector per dword puts in place (identity inside the image; the
+// edge byte repeated outside); else one byte load per byte, of the clamped
+// column. Loads are
 // unconditional (clamped rows) and issued kMfmaStage at a time; `between`
 // runs once in every wave: after the first batch is issued, before any of it
 // is written, or alone in a wave that has no rows to stage.
-template <int R, bool ALIGNED, class F>
+template <int R, bool WIDE, class F>
 __device__ __forceinline__ void stage_rows(const uint8_t *__restrict__ plane, uint8_t *rows, int h, int w, int x0,
                                            int y0, int nrows, int wave, int nwaves, int lane, F &&between) {
     constexpr int G = kMfmaGran, ND = G / 4;
@@ -123,8 +128,8 @@ __device__ __forceinline__ void stage_rows(const uint8_t *__restrict__ plane, ui
     const bool active = lr < PER;
     const int xc = x0 - kMfmaLeft + G * q;
     uint32_t xa = 0, sel[ND];
-    uint32_t xo[ALIGNED ? 1 : G];
-    if constexpr (ALIGNED) {
+    uint32_t xo[WIDE ? 1 : G];
+    if constexpr (WIDE) {
         xa = (uint32_t)clampi(xc, 0, w - G);
 #pragma unroll
         for (int j = 0; j < ND; ++j) {
@@ -146,10 +151,10 @@ __device__ __forceinline__ void stage_rows(const uint8_t *__restrict__ plane, ui
         for (int u = 0; u < kMfmaStage; ++u) {
             const int ly = min(base + u * step + lr, nrows - 1);
             const uint32_t roff = (uint32_t)clampi(y0 - R + ly, 0, h - 1) * (uint32_t)w;
-            if constexpr (ALIGNED) {
+            if constexpr (WIDE) {
                 // Selector values 0..3 pick bytes of the first dword, 4..7
                 // bytes of the second.
-                typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(4)));
+                typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(1)));
                 const u2 d = *(const u2 *)(plane + (roff + xo[0]));
 #pragma unroll
                 for (int j = 0; j < ND; ++j) v[u][j] = __builtin_amdgcn_perm(d[1], d[0], sel[j]);
@@ -177,8 +182,7 @@ __device__ __forceinline__ void stage_rows(const uint8_t *__restrict__ plane, ui
     }
 }
 
-// Staging for a tile whose staged columns all lie inside the image (and
-// rows 4-byte aligned): no column clamp, 16 bytes per lane (9 lanes per
+// Staging for a tile whose staged columns all lie inside the image: no column clamp, 16 bytes per lane (9 lanes per
 // row, 7 rows per wave pass), loads issued 4 at a time. At 1080p RGB, 7 x 7
 // (all but the edge tiles) 5.7 us against 6.0 us with the 8-byte staging.
 template <int R, class F>
@@ -187,7 +191,7 @@ __device__ __forceinline__ void stage_rows_wide(const uint8_t *__restrict__ plan
                                                 F &&between) {
     constexpr int G = 16, NL = kMfmaRow / G, PER = kLanes / NL, ST = 4;
     static_assert(kMfmaRow % G == 0, "whole 16-byte granules per staged row");
-    typedef uint32_t u4a __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t u4a __attribute__((ext_vector_type(4), aligned(1)));
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     const int lr = lane / NL, q = lane - lr * NL;
     const bool active = lr < PER;
@@ -226,25 +230,30 @@ __device__ __forceinline__ uint32_t pack_mfma_u8(const v4i &a, int shift) {
 }
 
 // 16 outputs of row y, columns x .. x + 15, as four dwords: one 16-byte
-// store when the rows are aligned and all 16 columns are in the image, else
-// dword stores (aligned rows: a dword is wholly inside or right of the
-// image) or byte stores, each dropped outside the image.
+// store, of any alignment, when all 16 columns are in the image; else a store
+// for each whole dword in it and up to three byte stores for the one that the
+// image's edge cuts (if its width leaves one). What lies outside the image is
+// dropped.
 __device__ __forceinline__ void store16_mfma_u8(const __amdgpu_buffer_rsrc_t &rs, int h, int w, int y, int x,
-                                                bool aligned, const v4i &v) {
+                                                const v4i &v) {
     constexpr uint32_t kDrop = 0x80000000u;
     const uint32_t off = (uint32_t)y * (uint32_t)w + (uint32_t)x;
-    if (aligned && x + 16 <= w) {
+    if (x + 16 <= w) {
         __builtin_amdgcn_raw_buffer_store_b128(v, rs, y < h ? off : kDrop, 0, kStoreAux);
-    } else if (aligned) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)v[k], rs, (y < h && x + 4 * k < w) ? off + 4 * k : kDrop, 0,
-                                                  kStoreAux);
     } else {
 #pragma unroll
-        for (int k = 0; k < 16; ++k)
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((uint32_t)v[k >> 2] >> (8 * (k & 3))), rs,
-                                                 (y < h && x + k < w) ? off + k : kDrop, 0, kStoreAux);
+        for (int k = 0; k < 4; ++k)
+            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)v[k], rs, (y < h && x + 4 * k + 4 <= w) ? off + 4 * k : kDrop,
+                                                  0, kStoreAux);
+        if (w & 3) {
+            const int left = w - x, k = left >> 2;  // the dword cut: k of 0 .. 3, if x < w
+            const uint32_t cut = (uint32_t)(k == 0 ? v[0] : (k == 1 ? v[1] : (k == 2 ? v[2] : v[3])));
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(cut >> (8 * j)), rs,
+                                                     (y < h && left > 0 && j < (left & 3)) ? off + 4 * k + j : kDrop, 0,
+                                                     kStoreAux);
+        }
     }
 }
 
@@ -255,7 +264,7 @@ __device__ __forceinline__ void store16_mfma_u8(const __amdgpu_buffer_rsrc_t &rs
 template <int R>
 __global__ __launch_bounds__(512) void k_filter_u8_mfma(const uint8_t *__restrict__ in,
                                                         const int8_t *__restrict__ filt, uint8_t *__restrict__ out,
-                                                        int h, int w, int shift, int aligned, int rpw, int tiles_x,
+                                                        int h, int w, int shift, int rpw, int tiles_x,
                                                         int tiles_per_plane, int ntiles) {
     constexpr int NS = mfma_steps<R>();
     extern __shared__ __align__(16) uint8_t lds[];
@@ -279,9 +288,9 @@ __global__ __launch_bounds__(512) void k_filter_u8_mfma(const uint8_t *__restric
     const int nwaves = nthr / kLanes;
     // The taps' loads are issued while the first rows' loads are in flight.
     auto taps_step = [&]() __attribute__((always_inline)) { stage_taps<R>(filt, taps, tid, nthr); };
-    if (aligned && x0 >= kMfmaLeft && x0 + kMfmaRow - kMfmaLeft <= w)
+    if (x0 >= kMfmaLeft && x0 + kMfmaRow - kMfmaLeft <= w)
         stage_rows_wide<R>(in + plane, rows, h, w, x0, y0, nstage, wave, nwaves, lane, taps_step);
-    else if (aligned && w >= kMfmaGran)
+    else if (w >= kMfmaGran)
         stage_rows<R, true>(in + plane, rows, h, w, x0, y0, nstage, wave, nwaves, lane, taps_step);
     else
         stage_rows<R, false>(in + plane, rows, h, w, x0, y0, nstage, wave, nwaves, lane, taps_step);
@@ -344,7 +353,7 @@ __global__ __launch_bounds__(512) void k_filter_u8_mfma(const uint8_t *__restric
         for (int i = 0; i < kMfmaN / RPI; ++i) {
             const int rr = RPI * i + lane / LPR, cc = 16 * (lane % LPR);
             const v4i v = *(const v4i *)(obuf + rr * kMfmaRow + cc);
-            store16_mfma_u8(rs, h, w, y0 + r0 + rr, x0 + cc, aligned != 0, v);
+            store16_mfma_u8(rs, h, w, y0 + r0 + rr, x0 + cc, v);
         }
     }
 }
@@ -360,9 +369,8 @@ hipError_t launch_u8_mfma_t(const uint8_t *in, const int8_t *filt, uint8_t *out,
     const int64_t per_plane = tiles_x * tiles_y;
     const int64_t ntiles = per_plane * c;
     if (ntiles > INT32_MAX) return hipErrorInvalidValue;
-    const int aligned = (w % 4 == 0) && ((uintptr_t)in % 4 == 0) && ((uintptr_t)out % 4 == 0);
     hipLaunchKernelGGL((k_filter_u8_mfma<R>), dim3((unsigned)ntiles), dim3(wpg * kLanes), lds, s, in, filt, out, h,
-                       w, shift, aligned, rpw, (int)tiles_x, (int)per_plane, (int)ntiles);
+                       w, shift, rpw, (int)tiles_x, (int)per_plane, (int)ntiles);
     return hipGetLastError();
 }
 

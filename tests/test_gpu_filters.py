@@ -459,3 +459,33 @@ def test_u8_mfma_short_last_tile(r, wpg):
             assert np.array_equal(got, oracle.filter2d_u8(img, f, 5)), rest
     finally:
         pf.tune_reset()
+
+
+@pytest.mark.parametrize("r", range(0, pf.PF_R_MAX + 1))
+@pytest.mark.parametrize("start", [0, 1, 3])
+def test_u8_any_alignment(r, start):
+    """Rows and planes that start at any byte: widths around the tiles, the
+    16-byte stores and the dword that the right edge cuts, arrays that begin
+    `start` bytes off alignment, on both uint8 kernels. Equal to the oracle,
+    and the bytes around the output keep their value."""
+    dev = device()
+    import torch
+    rng = np.random.default_rng(40 + r)
+    f = rng.integers(-8, 9, (2 * r + 1, 2 * r + 1), dtype=np.int8)
+    variants = [(pf.VAR_DIRECT, 16, 1)] + ([(pf.VAR_MFMA, 16, 4)] if r else [])
+    try:
+        for var, by, wpg in variants:
+            pf.tune_set([pf.TuneEntry(kind=pf.KIND_U8, r=r, size_class=sc, variant=var, rows_per_wave=by,
+                                      waves_per_group=wpg, us=0.0, context=pf.TUNE_SINGLE) for sc in range(3)])
+            for c, h, w in ((1, 3, 3), (2, 5, 7), (1, 17, 9), (3, 18, 130), (1, 33, 143), (2, 16, 257), (1, 70, 525)):
+                n = c * h * w
+                x = rng.integers(0, 256, (c, h, w), dtype=np.uint8)
+                xin = torch.zeros(n + 8, dtype=torch.uint8, device=dev)[start:start + n].view(c, h, w)
+                xin.copy_(torch.from_numpy(x))
+                buf = torch.full((n + 64,), 171, dtype=torch.uint8, device=dev)
+                pf.filter2d_u8(xin, torch.from_numpy(f).to(dev), 5, out=buf[32 + start:32 + start + n].view(c, h, w))
+                got = buf.cpu().numpy()
+                assert np.array_equal(got[32 + start:32 + start + n].reshape(c, h, w), oracle.filter2d_u8(x, f, 5)), (var, c, h, w)
+                assert (got[:32 + start] == 171).all() and (got[32 + start + n:] == 171).all(), (var, c, h, w)
+    finally:
+        pf.tune_reset()

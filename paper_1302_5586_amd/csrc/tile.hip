@@ -47,11 +47,11 @@ __global__ __launch_bounds__(kThreads) void k_tile_sep(const float *__restrict__
     tile_sep<R, EXACT, CX, Q>(buf, in, fx, fy, out, h, w, tx * 4 * CX, ty * (kThreads / CX) * Q);
 }
 
-template <int R, bool EXACT, int CX, int Q>
-hipError_t launch_shape(bool sep, const float *in, const float *fa, const float *fb, float *out, int h, int w,
-                        int border, hipStream_t s) {
+template <int R, bool EXACT, bool SEP, int CX, int Q>
+hipError_t launch_shape(const float *in, const float *fa, const float *fb, float *out, int h, int w, int border,
+                        hipStream_t s) {
     const int64_t tiles_x = dev::cdiv(w, 4 * CX), n = tiles_x * dev::cdiv(h, kThreads / CX * Q);
-    if (sep)
+    if constexpr (SEP)
         hipLaunchKernelGGL((k_tile_sep<R, EXACT, CX, Q>), dim3((unsigned)n), dim3(kThreads), 0, s, in, fa, fb, out, h,
                            w, (int)tiles_x);
     else
@@ -64,16 +64,36 @@ hipError_t launch_shape(bool sep, const float *in, const float *fa, const float 
 // of 4 waves per CU): the time is then one tile's, which a small tile keeps
 // short (256 x 256, R = 4: 3.5 us against 4.7 us for the larger one; 1080 x
 // 1920, 2040 tiles: 6.3 us against 7.3 us at R = 2). Beyond that a larger
-// tile, whose halo weighs less: 128 x 16 up to R = 3 (whole 512-byte row
-// pieces; 4096 x 4096, R = 1: 25.5 us against 27.5 us for 64 x 32), 64 x 32
-// above (half the vertical halo; separable R = 6: 31.6 us against 36.1 us).
-template <int R, bool EXACT>
-hipError_t launch(bool sep, const float *in, const float *fa, const float *fb, float *out, int h, int w, int border,
+// tile, whose halo weighs less (us, three images reused):
+//  * 2D: 128 x 32 at R = 1 (1533 x 2047 7.3, 128 x 16 8.0), 128 x 16 at R = 2
+//    and 3 (whole 512-byte row pieces; 1800 x 2500, R = 3 11.9, 128 x 32
+//    12.4), 64 x 32 above (1533 x 2047, R = 7 24.3, 64 x 64 25.0).
+//  * Separable: 128 x 32 (4096 x 4096, R = 6 25.1, 64 x 32 26.7, R = 8 28.4
+//    against 32.5; 1533 x 2047, R = 2 7.6, 128 x 16 8.2), but 128 x 16 for
+//    separate multiplies and adds at R = 3 (4096 x 4096 23.0, 128 x 32 25.4;
+//    the one radius where it is behind, why was not found). With separate
+//    multiplies and adds at R >= 5 arithmetic weighs more than the halo's
+//    loads, and few tiles leave CUs idle at the end: 64 x 32 up to 12 tiles
+//    per CU (1800 x 2500, R = 5 11.0, 128 x 32 12.2), then 64 x 64 (2160 x
+//    3840, R = 6 17.1, 64 x 32 18.0; 4096 x 4096, R = 8 35.2 against 44.2).
+template <int R, bool EXACT, bool SEP>
+hipError_t launch(const float *in, const float *fa, const float *fb, float *out, int h, int w, int border,
                   hipStream_t s) {
-    if ((int64_t)dev::cdiv(w, 64) * dev::cdiv(h, 16) <= 8 * (int64_t)dev_info().cus)
-        return launch_shape<R, EXACT, 16, 1>(sep, in, fa, fb, out, h, w, border, s);
-    if constexpr (R <= 3) return launch_shape<R, EXACT, 32, 2>(sep, in, fa, fb, out, h, w, border, s);
-    else return launch_shape<R, EXACT, 16, 2>(sep, in, fa, fb, out, h, w, border, s);
+    const int64_t cus = dev_info().cus;
+    auto tiles = [&](int tw, int th) { return (int64_t)dev::cdiv(w, tw) * dev::cdiv(h, th); };
+#define PF_SHAPE(CX, Q) return launch_shape<R, EXACT, SEP, CX, Q>(in, fa, fb, out, h, w, border, s)
+    if (tiles(64, 16) <= 8 * cus) PF_SHAPE(16, 1);
+    if constexpr (SEP && EXACT && R >= 5) {
+        if (tiles(64, 32) > 12 * cus) PF_SHAPE(16, 4);
+        PF_SHAPE(16, 2);
+    } else if constexpr ((SEP && !(EXACT && R == 3)) || R <= 1) {
+        PF_SHAPE(32, 4);
+    } else if constexpr (R <= 3) {
+        PF_SHAPE(32, 2);
+    } else {
+        PF_SHAPE(16, 2);
+    }
+#undef PF_SHAPE
 }
 
 }  // namespace tile
@@ -81,8 +101,11 @@ hipError_t launch(bool sep, const float *in, const float *fa, const float *fb, f
 template <>
 hipError_t launch_tile_radius<PF_R>(bool sep, bool exact, const float *in, const float *fa, const float *fb,
                                     float *out, int h, int w, int border, hipStream_t s) {
-    return exact ? tile::launch<PF_R, true>(sep, in, fa, fb, out, h, w, border, s)
-                 : tile::launch<PF_R, false>(sep, in, fa, fb, out, h, w, border, s);
+    if (sep)
+        return exact ? tile::launch<PF_R, true, true>(in, fa, fb, out, h, w, border, s)
+                     : tile::launch<PF_R, false, true>(in, fa, fb, out, h, w, border, s);
+    return exact ? tile::launch<PF_R, true, false>(in, fa, fb, out, h, w, border, s)
+                 : tile::launch<PF_R, false, false>(in, fa, fb, out, h, w, border, s);
 }
 
 }  // namespace pf

@@ -119,7 +119,7 @@ pf_status build_plan_tables(int32_t n, const int32_t *h, const int32_t *w, const
         d.var = var;
     }
     int64_t ntiles = 0;
-    t->shape = batch_shape(t->imgs, &ntiles);
+    t->shape = batch_shape(t->imgs, t->used, &ntiles);
     if (ntiles > INT32_MAX) return fail(PF_EUNSUPPORTED, "batch has more than 2^31-1 tiles");
     t->tasks.reserve((size_t)ntiles);
     for (int i = 0; i < n; ++i) append_tiles(t->tasks, i, t->imgs[i]);

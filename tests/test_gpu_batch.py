@@ -218,14 +218,17 @@ def test_batch_autotune_keeps_results(tmp_path):
 def test_batch_tiles_equal_single_calls(large, kinds, exact):
     """Sizes around the tiles' edges (64 and 256 columns, 16 rows, images
     under 4 columns, halos that leave the image on both sides), each radius,
-    in batches of few tiles and of many, which take tiles of another shape:
-    every image equals its single-image call bit for bit."""
+    in batches of few tiles, of many and (separable) of very many, which take
+    tiles of three shapes: every image equals its single-image call bit for
+    bit."""
     dev = device()
     import torch
     rng = np.random.default_rng(91)
     sizes = [(1, 1), (2, 3), (17, 4), (5, 63), (16, 64), (33, 65), (15, 255), (16, 256), (40, 257), (49, 525)]
     if large:
         sizes += [(700, 1030), (515, 777), (300, 1290)]
+    if large and kinds == "sep":
+        sizes += [(1100, 1500), (1031, 1300)]
     imgs, filts, ks = [], [], []
     for i, (h, w) in enumerate(sizes):
         for r in range(pf.PF_BATCH_R_MAX + 1):

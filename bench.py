@@ -1,11 +1,10 @@
 """Benchmark: Gpixel/s and % of the HBM roofline, batched vs plain, plus
 p50/p99 latency of the served stream, on one MI355X.
 
-One step = one replay of the batch plan over the 512-image batch (seeded
+One step = one run of the batch plan over the 512-image batch (seeded
 synthetic FP32 images, widths and heights log-uniform in [64, 2048], radius
-1..4, Gaussian sigma in [0.5, 2.0); the 2D and separable tile bodies chosen
-per image by the tune table), a single persistent launch captured in a
-hipGraph. `value` is output Gpixel/s over the timed steps.
+1..4, Gaussian sigma in [0.5, 2.0), separable), a single launch.
+`value` is output Gpixel/s over the timed steps.
 
 Printed as one JSON line with, besides the contract fields:
   roofline      the batch kernel's algorithmic bytes (8 per pixel) over its
@@ -185,11 +184,9 @@ def main():
     for _ in range(args.warmup):
         plan.run(x, fl, out)
     torch.cuda.synchronize()
-    # One event pair around the timed steps, on the stream the graph is
-    # launched on: an event recorded between two graph launches held the
-    # next launch back by about 20 us on MI355X (0.318 ms per step with
-    # per-step events against 0.297 ms without), which is event overhead,
-    # not the kernel's.
+    # One event pair around the timed steps, on the stream of the launches:
+    # an event recorded between two steps holds the next one back, which is
+    # event overhead, not the kernel's.
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
     w0 = time.perf_counter()
@@ -219,7 +216,7 @@ def main():
         "dtype": "f32",
         "data": "synthetic (seeded numpy PCG64 images; no dataset)",
         "config": {"workload": "batch of 512 FP32 images, sizes log-uniform 64..2048, r 1..4, Gaussian sigma "
-                               "0.5..2.0, seed 3; one persistent launch replayed from a hipGraph",
+                               "0.5..2.0, seed 3; one launch",
                    "images": b.n, "pixels": px, "wave_tiles": info["tasks"], "grid": info["grid"],
                    "launches_per_step": info["launches"],
                    "variants": {name: int((variants == v).sum()) for v, name in

@@ -604,7 +604,7 @@ def _np_ptr(a):
 
 
 class BatchPlan:
-    """Many images in one launch (optionally a graph replay).
+    """Many images in one launch. ``graph`` is accepted and changes nothing.
 
     Images live in one pixel arena (input and output arenas share the
     layout) at ``pix_off``; filters in one filter arena at ``filt_off``.

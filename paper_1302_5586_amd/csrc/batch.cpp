@@ -1,5 +1,4 @@
-// Batch plans: many images of uneven sizes and radii in one
-// launch, optionally replayed from a hipGraph.
+// Batch plans: many images of uneven sizes and radii in one launch.
 //
 // The batch is described the way the paper rewrites OP2's kernel for
 // PENCIL (Sec. III-A): no arrays of pointers, only arenas plus per-image
@@ -8,7 +7,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -26,48 +24,9 @@ struct pf_batch_plan {
     void *dev = nullptr;  // descriptors and tile list, one allocation
     const pf::BatchImg *imgs = nullptr;
     const pf::BatchTask *tasks = nullptr;
-    // Graph replay state.
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    hipGraphNode_t node = nullptr;
-    const float *g_in = nullptr, *g_filt = nullptr;
-    float *g_out = nullptr;
-    std::mutex mu;
 };
 
 namespace pf {
-
-// Kernel parameters of a plan's launch (pointers must outlive use).
-struct BatchArgs {
-    const BatchImg *imgs;
-    const BatchTask *tasks;
-    int ntasks;
-    const float *in;
-    const float *filt;
-    float *out;
-    void *params[6];
-    void fill() {
-        params[0] = &imgs;
-        params[1] = &tasks;
-        params[2] = &ntasks;
-        params[3] = &in;
-        params[4] = &filt;
-        params[5] = &out;
-    }
-};
-
-static hipKernelNodeParams node_params(pf_batch_plan *p, BatchArgs &a) {
-    a.fill();
-    hipKernelNodeParams kp;
-    memset(&kp, 0, sizeof kp);
-    kp.func = batch_kernel_fn((p->flags & PF_FLAG_EXACT) != 0, p->used, p->shape);
-    kp.gridDim = batch_grid(p->ntasks);
-    kp.blockDim = dim3(kTileThreads);
-    kp.sharedMemBytes = 0;
-    kp.kernelParams = a.params;
-    kp.extra = nullptr;
-    return kp;
-}
 
 // Validates a batch description (sizes, radii, kinds, arena ranges, no two
 // images overlapping) and builds the plan's host tables: the image
@@ -119,7 +78,7 @@ pf_status build_plan_tables(int32_t n, const int32_t *h, const int32_t *w, const
         d.var = var;
     }
     int64_t ntiles = 0;
-    t->shape = batch_shape(t->imgs, t->used, &ntiles);
+    t->shape = batch_shape(t->imgs, &ntiles);
     if (ntiles > INT32_MAX) return fail(PF_EUNSUPPORTED, "batch has more than 2^31-1 tiles");
     t->tasks.reserve((size_t)ntiles);
     for (int i = 0; i < n; ++i) append_tiles(t->tasks, i, t->imgs[i]);
@@ -255,35 +214,9 @@ pf_status pf_batch_plan_run(pf_batch_plan *p, int64_t npix, int64_t nfilt, const
     if (i0 < b + nb && b < i0 + nb) return fail(PF_EALIAS, "input and output arenas overlap (restrict)");
     const uintptr_t f = (uintptr_t)filt, fb = (uintptr_t)nfilt * 4;
     if (f < b + nb && b < f + fb) return fail(PF_EALIAS, "filter and output arenas overlap (restrict)");
-    hipStream_t s = (hipStream_t)stream;
-    const bool exact = (p->flags & PF_FLAG_EXACT) != 0;
-    std::lock_guard<std::mutex> lk(p->mu);
-    if (!(p->flags & PF_BATCH_GRAPH)) {
-        hipError_t e = launch_batch(exact, p->used, p->shape, p->imgs, p->tasks, p->ntasks, in, filt, out, s);
-        if (e != hipSuccess) return fail_hip(e, "batch launch");
-        return PF_OK;
-    }
-    hipError_t e = hipSuccess;
-    BatchArgs a{p->imgs, p->tasks, (int)p->ntasks, in, filt, out, {}};
-    hipKernelNodeParams kp = node_params(p, a);
-    if (!p->exec) {
-        // Build the graph once: the launch as its only node.
-        if ((e = hipGraphCreate(&p->graph, 0)) != hipSuccess) return fail_hip(e, "graph create");
-        if ((e = hipGraphAddKernelNode(&p->node, p->graph, nullptr, 0, &kp)) != hipSuccess)
-            return fail_hip(e, "graph kernel node");
-        if ((e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0)) != hipSuccess) {
-            p->exec = nullptr;
-            return fail_hip(e, "graph instantiate");
-        }
-    } else if (in != p->g_in || filt != p->g_filt || out != p->g_out) {
-        // Re-point the replay at the new arenas.
-        if ((e = hipGraphExecKernelNodeSetParams(p->exec, p->node, &kp)) != hipSuccess)
-            return fail_hip(e, "graph node update");
-    }
-    p->g_in = in;
-    p->g_filt = filt;
-    p->g_out = out;
-    if ((e = hipGraphLaunch(p->exec, s)) != hipSuccess) return fail_hip(e, "graph launch");
+    hipError_t e = launch_batch((p->flags & PF_FLAG_EXACT) != 0, p->used, p->shape, p->imgs, p->tasks, p->ntasks, in,
+                                filt, out, (hipStream_t)stream);
+    if (e != hipSuccess) return fail_hip(e, "batch launch");
     return PF_OK;
 }
 
@@ -309,8 +242,6 @@ pf_status pf_batch_plan_info(const pf_batch_plan *p, int64_t *const __restrict t
 pf_status pf_batch_plan_destroy(pf_batch_plan *p) {
     clear_error();
     if (!p) return PF_OK;
-    if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->graph) (void)hipGraphDestroy(p->graph);
     if (p->dev) (void)hipFree(p->dev);
     delete p;
     return PF_OK;

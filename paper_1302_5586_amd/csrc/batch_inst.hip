@@ -29,12 +29,12 @@ __device__ __forceinline__ void one_tile(float *buf, const BatchImg &d, const fl
 // One workgroup per tile of the list (which goes image by image, row by row
 // inside each), its image's radius and variant picked by a branch that is
 // uniform. Bound by HBM with what the halo costs on top: 512 images, 78 M
-// pixels, radii 1..4, separable: 261 us (4.8 TB/s) where the card copies the
+// pixels, radii 1..4, separable: 247 us (5.05 TB/s) where the card copies the
 // bytes in 208 us; rows that start anywhere cost 8%, radius 4 against 1
-// another 17%. The strips that a fixed grid of one workgroup per CU walked
+// another 7%. The strips that a fixed grid of one workgroup per CU walked
 // before took 300 us, and on smaller batches, where such a strip is a long
-// serial chain: 256 images 160 -> 134, 128 92 -> 70, 48 37.8 -> 23, 16 21 ->
-// 9.4 us.
+// serial chain: 256 images 160 -> 127, 128 92 -> 66, 48 37.8 -> 23.5, 16 21
+// -> 9 us.
 template <bool EXACT, int VMASK, int CX, int Q>
 __global__ __launch_bounds__(kThreads) void k_batch(const BatchImg *__restrict__ imgs,
                                                     const BatchTask *__restrict__ tasks, int ntasks,
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kThreads) void k_batch(const BatchImg *__restrict__
                                                     float *__restrict__ out) {
     __shared__ __align__(16) float buf[rows_of(PF_BATCH_R_MAX, CX, Q) * pitch_of(PF_BATCH_R_MAX, CX)];
     int zero, at;
-    window_tile(blockIdx.x, gridDim.x, 1, zero, at);
+    window_tile(blockIdx.x, gridDim.x, 1, kBatchWindow, zero, at);
     // No loop over tiles: the compiler would keep every radius' invariants in
     // registers across it (217 instead of 70).
     const int64_t t = (int64_t)blockIdx.y * gridDim.x + at;
@@ -68,11 +68,8 @@ __global__ __launch_bounds__(kThreads) void k_batch(const BatchImg *__restrict__
 template <>
 void *batch_fn<PF_EXACT, PF_VMASK>(int shape) {
     constexpr bool kExact = PF_EXACT != 0;
-    // kBatchShapes; the third only for separable filters.
-    if (shape == 0) return (void *)tile::k_batch<kExact, PF_VMASK, 16, 1>;
-    if constexpr (PF_VMASK == 1 << PF_VAR_SEPARABLE)
-        if (shape == 2) return (void *)tile::k_batch<kExact, PF_VMASK, 64, 8>;
-    return (void *)tile::k_batch<kExact, PF_VMASK, 64, 4>;
+    return shape == 0 ? (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[0].w / 4, 1>
+                      : (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[1].w / 4, 5>;
 }
 
 }  // namespace pf

@@ -258,7 +258,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_tiles(const float *__restric
                                                           int h, int w, int passes, int border, int tiles_x) {
     extern __shared__ __align__(16) float lds[];
     int tx, ty;
-    window_tile(blockIdx.x, gridDim.x, tiles_x, tx, ty);
+    window_tile(blockIdx.x, gridDim.x, tiles_x, 2048, tx, ty);
     const int x0 = tx * TX, y0 = ty * TY;
     chain_tile<R, EXACT, TX, TY, Q>(in, filt, out, h, w, passes, border, x0, y0, x0 + min(TX, w - x0),
                                     y0 + min(TY, h - y0), blockIdx.x & 3, lds);

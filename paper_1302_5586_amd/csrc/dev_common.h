@@ -19,21 +19,21 @@ __device__ __forceinline__ int xcd_remap(int b, int g) {
     return xcd * per + min(xcd, rem) + idx;
 }
 
-// Workgroup -> tile of one image, tiles numbered row by row (tiles_x per
-// row). The launch is taken in windows of about kWindow tiles, as many
-// workgroups as the chip holds at once (8 per CU): the tiles in flight cover
-// one compact band of the image that advances down it, and inside a window
+// Workgroup -> tile of a list (an image's tiles row by row, tiles_x per row).
+// The launch is taken in windows of about `window` tiles: the tiles in flight
+// cover one compact band that advances down the image, and inside a window
 // each XCD has a contiguous eighth, so that most of a tile's neighbours are
 // in the same L2. Measured on the FP32 tile kernel: one contiguous eighth of
 // the whole image per XCD keeps eight windows of HBM pages open: 30.0 us
 // against 27.5 us at 4096 x 4096, R = 2 (buffers rotated through 2 GiB; 26 us
 // against 25.2 us where three images are reused and partly in the last-level
 // cache). Dealt in groups of 32 tiles instead, halo rows cross XCDs: 14.5 us
-// against 13.7 us at 2160 x 3840 from that cache. Windows of 1024 and 4096
-// tiles measured within 3% of 2048.
-__device__ __forceinline__ void window_tile(int b, int n, int tiles_x, int &tx, int &ty) {
-    constexpr int kWindow = 2048;
-    const int windows = max(1, (n + kWindow / 2) / kWindow);
+// against 13.7 us at 2160 x 3840 from that cache. About 4 million pixels per
+// window serve single images best (separable 4096 x 4096, R = 2, tiles of 128
+// x 32, from HBM: 27.4 us with 1024 tiles, 28.8 with 2048; from the cache
+// 22.1 and 22.3; 512 tiles 27.3 and 22.8).
+__device__ __forceinline__ void window_tile(int b, int n, int tiles_x, int window, int &tx, int &ty) {
+    const int windows = max(1, (n + window / 2) / window);
     const int size = ((n + windows - 1) / windows + 7) / 8 * 8;  // a multiple of 8: workgroup b runs on XCD b mod 8
     const int first = b / size * size;
     const int t = first + xcd_remap(b - first, min(size, n - first));

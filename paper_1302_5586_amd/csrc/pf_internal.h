@@ -124,17 +124,23 @@ constexpr int tile_load_col(int c, int x0, int w) { return clamp_int(c, -x0, w -
 
 // Tiles of a batch launch, columns x rows: 64 x 16 while all of the batch's
 // fit on the chip at once (8 workgroups of 4 waves on each of 256 CUs), since
-// the time is then one tile's; 256 x 16 beyond (512 images 268 us, with 128 x
-// 16 284 us, 64 x 32 312 us, 64 x 16 380 us). Batches of separable filters
-// with many tiles take 256 x 32, whose halo weighs less (512 images 261 us,
-// 128 images of 6300 tiles of 256 x 16 70.0 us against 72.9 us; 48 images of
-// 2200 tiles 25.2 us against 22.7 us, the last tiles being longer); a 2D
-// filter's window for it would not fit in registers.
+// the time is then one tile's; 256 x 20 beyond. us for 512, 128, 48 and 16
+// separable images (24600, 6300, 2200 and 630 tiles of 256 x 16), windows of
+// 512 tiles: 256 x 20 247, 65.9, 23.5, 8.8; 256 x 16 255, 66.2, 23.3, 9.0;
+// 256 x 24 243, 66.0, 23.2, 9.7; with windows of 2048 256 x 32 257, 69.8,
+// 25.2, 10.5; 128 x 16 284, 75.7, 22.9, 8.8; 64 x 32 312, 82, 24.7, 8.4.
 struct BatchShape {
     int w, h;
 };
-constexpr BatchShape kBatchShapes[3] = {{64, 16}, {256, 16}, {256, 32}};
-constexpr int64_t kBatchSmallTiles = 8 * 256, kBatchManyTiles = 16 * 256;
+constexpr BatchShape kBatchShapes[2] = {{64, 16}, {256, 20}};
+constexpr int64_t kBatchSmallTiles = 8 * 256;
+
+// Tiles per window of the launch (window_tile): the images of a batch have few
+// rows of tiles each, and a small window keeps the HBM pages in use few (512
+// images, 256 x 20: 247 us, windows of 1024 252 us, of 2048 262 us; 128 images
+// 65.9, 68.1 and 70.6 us; of 256 244 and 65.5 us, but 48 images 24.1 against
+// 23.5 us).
+constexpr int kBatchWindow = 512;
 
 // One image of a batch as the batch kernel sees it. `var` is the executed
 // variant (PF_VAR_*); its tiles are numbered row by row, tiles_x to a row.
@@ -160,14 +166,13 @@ inline int64_t batch_tiles(int h, int w, int shape) {
     return (((int64_t)w + t.w - 1) / t.w) * (((int64_t)h + t.h - 1) / t.h);
 }
 
-// The shape for the images of a batch (h and w set) of the variants `used`;
-// fills their tiles_x and tiles_y. *tiles: how many there are.
-inline int batch_shape(std::vector<BatchImg> &imgs, int used, int64_t *tiles) {
-    int64_t n[3] = {0, 0, 0};
+// The shape for the images of a batch (h and w set), whose tiles_x and
+// tiles_y it fills; *tiles: how many there are.
+inline int batch_shape(std::vector<BatchImg> &imgs, int64_t *tiles) {
+    int64_t n[2] = {0, 0};
     for (const BatchImg &d : imgs)
-        for (int s = 0; s < 3; ++s) n[s] += batch_tiles(d.h, d.w, s);
-    int shape = n[0] <= kBatchSmallTiles ? 0 : 1;
-    if (n[1] > kBatchManyTiles && used == 1 << PF_VAR_SEPARABLE) shape = 2;
+        for (int s = 0; s < 2; ++s) n[s] += batch_tiles(d.h, d.w, s);
+    const int shape = n[0] <= kBatchSmallTiles ? 0 : 1;
     const BatchShape t = kBatchShapes[shape];
     for (BatchImg &d : imgs) {
         d.tiles_x = (int32_t)(((int64_t)d.w + t.w - 1) / t.w);

@@ -306,7 +306,7 @@ pf_status launch_slot(pf_server *s, Slot &sl, bool after_copies) {
     }
     std::vector<BatchTask> tasks;
     int shape = 0;
-    if (!imgs.empty()) shape = batch_shape(imgs, used, &ntiles);
+    if (!imgs.empty()) shape = batch_shape(imgs, &ntiles);
     if (ntiles) {
         if (ntiles > INT32_MAX || sum_tasks.size() > INT32_MAX || hist_tasks.size() > INT32_MAX)
             return fail(PF_EUNSUPPORTED, "batch too large");

@@ -33,7 +33,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_2d(const float *__restrict__ 
                                                       int border) {
     __shared__ __align__(16) float buf[rows_of(R, CX, Q) * pitch_of(R, CX)];
     int tx, ty;
-    window_tile(blockIdx.x, gridDim.x, tiles_x, tx, ty);
+    window_tile(blockIdx.x, gridDim.x, tiles_x, window_of(Q), tx, ty);
     tile_2d<R, EXACT, CX, Q>(buf, in, filt, out, h, w, tx * 4 * CX, ty * (kThreads / CX) * Q, border);
 }
 
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kThreads) void k_tile_sep(const float *__restrict__
                                                        int w, int tiles_x) {
     __shared__ __align__(16) float buf[rows_of(R, CX, Q) * pitch_of(R, CX)];
     int tx, ty;
-    window_tile(blockIdx.x, gridDim.x, tiles_x, tx, ty);
+    window_tile(blockIdx.x, gridDim.x, tiles_x, window_of(Q), tx, ty);
     tile_sep<R, EXACT, CX, Q>(buf, in, fx, fy, out, h, w, tx * 4 * CX, ty * (kThreads / CX) * Q);
 }
 

@@ -35,6 +35,8 @@ constexpr int pad_of(int r) { return tile_pad(r); }
 constexpr int pitch_of(int r, int cx) { return 4 * cx + 2 * pad_of(r); }
 constexpr int rows_of(int r, int cx, int q) { return kThreads / cx * q + 2 * r; }
 constexpr int window_vecs(int r) { return 1 + pad_of(r) / 2; }
+// Tiles per window of window_tile: 4 million pixels.
+constexpr int window_of(int q) { return (1 << 22) / (4 * kThreads * q); }
 
 // Stages image rows y0 - R .. and columns x0 - PAD .. into buf, extended past
 // the image by the border rule; all of a thread's loads are in flight before

@@ -218,9 +218,9 @@ def test_batch_autotune_keeps_results(tmp_path):
 def test_batch_tiles_equal_single_calls(large, kinds, exact):
     """Sizes around the tiles' edges (64 and 256 columns, 16 rows, images
     under 4 columns, halos that leave the image on both sides), each radius,
-    in batches of few tiles, of many and (separable) of very many, which take
-    tiles of three shapes: every image equals its single-image call bit for
-    bit."""
+    in batches of few tiles and of many, which take tiles of another shape
+    and several windows of the launch: every image equals its single-image
+    call bit for bit."""
     dev = device()
     import torch
     rng = np.random.default_rng(91)

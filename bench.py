@@ -77,6 +77,7 @@ def parse():
 
 KERNEL_SOURCES = ("paper_1302_5586_amd/csrc/filter_body.h", "paper_1302_5586_amd/csrc/pf_internal.h",
                   "paper_1302_5586_amd/csrc/dev_common.h", "paper_1302_5586_amd/csrc/batch_inst.hip",
+                  "paper_1302_5586_amd/csrc/tile_body.h", "paper_1302_5586_amd/csrc/tile.hip",
                   "paper_1302_5586_amd/csrc/f32_inst.hip", "paper_1302_5586_amd/csrc/launch.hip",
                   "paper_1302_5586_amd/csrc/u8_mfma.hip")
 
@@ -222,11 +223,11 @@ def main():
                    "variants": {name: int((variants == v).sum()) for v, name in
                                 ((0, "direct"), (1, "separable"), (2, "separable_as_2d"))}},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": committed_traffic("k_batch_f32_batch512"),
+                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": committed_traffic("k_batch_batch512"),
                      "traffic_unit": "bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
                      "traffic_source": "profiles/counters.json: rocprofv3 --pmc runs of this kernel source "
                                        "(null when the kernel sources changed since); not measured in this run",
-                     "kernel": "k_batch_f32", "algorithmic_bytes_per_launch": alg_bytes,
+                     "kernel": "k_batch", "algorithmic_bytes_per_launch": alg_bytes,
                      "avg_kernel_ms": round(k_avg_ms, 4)},
     }
 

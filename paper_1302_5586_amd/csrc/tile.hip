@@ -64,18 +64,21 @@ hipError_t launch_shape(const float *in, const float *fa, const float *fb, float
 // of 4 waves per CU): the time is then one tile's, which a small tile keeps
 // short (256 x 256, R = 4: 3.5 us against 4.7 us for the larger one; 1080 x
 // 1920, 2040 tiles: 6.3 us against 7.3 us at R = 2). Beyond that a larger
-// tile, whose halo weighs less (us, three images reused):
-//  * 2D: 128 x 32 at R = 1 (1533 x 2047 7.3, 128 x 16 8.0), 128 x 16 at R = 2
-//    and 3 (whole 512-byte row pieces; 1800 x 2500, R = 3 11.9, 128 x 32
-//    12.4), 64 x 32 above (1533 x 2047, R = 7 24.3, 64 x 64 25.0).
-//  * Separable: 128 x 32 (4096 x 4096, R = 6 25.1, 64 x 32 26.7, R = 8 28.4
-//    against 32.5; 1533 x 2047, R = 2 7.6, 128 x 16 8.2), but 128 x 16 for
-//    separate multiplies and adds at R = 3 (4096 x 4096 23.0, 128 x 32 25.4;
-//    the one radius where it is behind, why was not found). With separate
-//    multiplies and adds at R >= 5 arithmetic weighs more than the halo's
-//    loads, and few tiles leave CUs idle at the end: 64 x 32 up to 12 tiles
-//    per CU (1800 x 2500, R = 5 11.0, 128 x 32 12.2), then 64 x 64 (2160 x
-//    3840, R = 6 17.1, 64 x 32 18.0; 4096 x 4096, R = 8 35.2 against 44.2).
+// tile, whose halo weighs less (us; C: three images reused, partly in the
+// last-level cache, H: eight or more, from HBM):
+//  * 2D up to R = 2 and separable up to R = 3: 256 x 16, whole 1 KiB row
+//    pieces (3000 x 4001, separable R = 2: H 21.6, 128 x 16 22.8, 128 x 32
+//    23.3, 64 x 32 25.9; 1800 x 2500: C 8.2, 128 x 16 8.9), from 3 tiles per
+//    CU; below 128 x 32, which divides among the CUs better (1080 x 1920: C
+//    5.0 against 5.9; 1533 x 2047, 3 tiles per CU: both 7.6, 128 x 16 8.2).
+//  * Other 2D: 128 x 16 at R = 3 (1800 x 2500: C 11.9, 256 x 16 12.5), 64 x 32
+//    above (1533 x 2047, R = 7: C 24.3, 64 x 64 25.0).
+//  * Other separable: 128 x 32 (4096 x 4096, R = 6: C 25.1, 64 x 32 26.7,
+//    R = 8: H 31.0 against 35.1). With separate multiplies and adds at R >= 5
+//    arithmetic weighs more than the halo's loads, and few tiles leave CUs
+//    idle at the end: 64 x 32 up to 12 tiles per CU (1800 x 2500, R = 5: C
+//    11.0, 128 x 32 12.2), then 64 x 64 (2160 x 3840, R = 6: C 17.1, 64 x 32
+//    18.0; 4096 x 4096, R = 8: H 39.4 against 49.6).
 template <int R, bool EXACT, bool SEP>
 hipError_t launch(const float *in, const float *fa, const float *fb, float *out, int h, int w, int border,
                   hipStream_t s) {
@@ -86,7 +89,10 @@ hipError_t launch(const float *in, const float *fa, const float *fb, float *out,
     if constexpr (SEP && EXACT && R >= 5) {
         if (tiles(64, 32) > 12 * cus) PF_SHAPE(16, 4);
         PF_SHAPE(16, 2);
-    } else if constexpr ((SEP && !(EXACT && R == 3)) || R <= 1) {
+    } else if constexpr (R <= (SEP ? 3 : 2)) {
+        if (tiles(256, 16) >= 3 * cus) PF_SHAPE(64, 4);
+        PF_SHAPE(32, 4);
+    } else if constexpr (SEP) {
         PF_SHAPE(32, 4);
     } else if constexpr (R <= 3) {
         PF_SHAPE(32, 2);

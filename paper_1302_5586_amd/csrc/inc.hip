@@ -9,8 +9,9 @@
 //    self-loop edge twice, its second cell first). The kernel then gives
 //    each cell to one thread, which adds the cell's increments in exactly
 //    that order: no atomics, no colouring, and the result equals the
-//    sequential loop bit for bit. Large meshes in random order take a second
-//    form of the plan with the same property (k_rounds).
+//    sequential loop bit for bit. The plan has three forms with that
+//    property: lists (k_gather) for meshes of few edges, fours
+//    (k_gather_fours), and rounds (k_rounds) for large ones in random order.
 //  * A scatter with float64 atomic adds: one thread per edge. Fast to set
 //    up, but the order in which a cell's increments land varies from run
 //    to run, so only a tolerance holds.
@@ -30,6 +31,7 @@ namespace inc {
 
 typedef int32_t i2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+typedef int32_t i4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 
@@ -48,6 +50,9 @@ struct pf_inc_plan {
     void *dev = nullptr;  // all tables
     // Lists: offsets (ncells + 1), the cells' edges (2 * nedges).
     const int32_t *off = nullptr, *idx = nullptr;
+    // Fours: the cells' first edges, four to a cell, and the rest.
+    const pf::inc::i4 *four = nullptr;
+    const int32_t *more = nullptr;
     // Rounds (nbins > 0): the bins' first groups (nbins + 1); per group, the
     // edge base of each round and 64 entries of each.
     int32_t nbins = 0, per = 0;
@@ -78,6 +83,45 @@ __global__ __launch_bounds__(kThreads) void k_gather(const int32_t *__restrict__
         v = v + e3;
     }
     for (; k < k1; ++k) v = v + edge[idx[k]];
+    cell[c] = v;
+}
+
+// The same with each cell's first four edges in one 16-byte entry (-1: none),
+// the form of meshes whose cells have two or more edges on average: they and
+// the cell's value come in one round trip, their values in the next, where the
+// lists take three. A cell of more than four edges keeps three there and in
+// the fourth place -2 - k: more[k] further edges follow at more[k + 1]. Bound
+// by latency up to some 100,000 cells, then by the lines fetched for single
+// values. Lists -> fours, us: random quads 362 x 362 6.6 -> 5.8, 512 x 512
+// 10.5 -> 9.4, 724 x 724 25.0 -> 23.5; numbered row by row 1024 x 1024
+// 10.7 -> 9.0, 2048 x 2048 45 -> 39 (5.1 TB/s).
+__global__ __launch_bounds__(kThreads) void k_gather_fours(const i4 *__restrict__ four,
+                                                           const int32_t *__restrict__ more,
+                                                           const double *__restrict__ edge, double *__restrict__ cell,
+                                                           int32_t ncells) {
+    const int64_t c = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
+    if (c >= ncells) return;
+    const i4 e = four[c];
+    double v = cell[c], x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = edge[max(e[k], 0)];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (e[k] >= 0) v = v + x[k];
+    if (e[3] < -1) {
+        const int32_t *idx = more + (-2 - e[3]);
+        const int32_t n = *idx++;
+        int32_t k = 0;
+        for (; k + 4 <= n; k += 4) {
+            const int32_t i0 = idx[k], i1 = idx[k + 1], i2 = idx[k + 2], i3 = idx[k + 3];
+            const double e0 = edge[i0], e1 = edge[i1], e2 = edge[i2], e3 = edge[i3];
+            v = v + e0;
+            v = v + e1;
+            v = v + e2;
+            v = v + e3;
+        }
+        for (; k < n; ++k) v = v + edge[idx[k]];
+    }
     cell[c] = v;
 }
 
@@ -175,23 +219,37 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const int32_t *__restrict_
 namespace pf {
 namespace inc {
 
-// Which plans are rounds. From 10 MiB of edge values: below, the L2s hold
-// most of what k_gather fetches and the rounds' steps cost more (random quads:
-// 724 x 724, 8 MiB: 25.4 us against 33 us; 860 x 860: 42 us against 29 us).
-// Only where the edges next to each other name cells far apart (a sample):
-// with edges numbered along the cells the values of k_gather are in the L2
-// (2048 x 2048 numbered row by row: 44.6 us against 49.5 us; shuffled within a
-// sixteenth of the mesh: 103 us against 108 us).
-bool rounds_suit(int32_t ncells, int32_t nedges, const int32_t *e2c) {
-    if (nedges < (10 << 20) / 8 || ncells > 1 << 30) return false;  // cells: see Quotient
+// The form of a plan. Below 10 MiB of edge values the L2s hold most of what a
+// gather fetches: fours, or lists (make_fours). us, lists / fours / rounds:
+// random quads 724 x 724, 8 MiB 25.0 / 23.5 / 33; 860 x 860 42 / - / 29.
+// From there by how far apart the cells are that neighbouring edges name, in a
+// sample:
+//  * within 1024 cells for the most part: fours. The values of a gather are in
+//    the L2. 2048 x 2048 numbered row by row 45.1 / 39.3 / 49.9, its edges
+//    shuffled within 1024 58.1 / 56.5 / 60.7.
+//  * over a sixteenth of the mesh and 128 K cells (2 MiB of their edges) for
+//    the most part: rounds. 2048 x 2048 in random order 309 / - / 132; shuffled
+//    within a sixteenth 103 / 106 / 108, 1024 x 1024 within a quarter
+//    24.1 / 23.3 / 33.
+//  * between: lists, whose fewer loads in flight leave more of the L2 (2048 x
+//    2048 shuffled within 65536 edges 89 / 96 / 72, 1024 x 1024 20 / 19 / 34).
+enum Form { kLists, kFours, kRounds };
+
+Form form_of(int32_t ncells, int32_t nedges, const int32_t *e2c) {
+    if (nedges < (10 << 20) / 8) return kFours;
     constexpr int kSamples = 4096;
-    int far = 0;
+    const int32_t wide = std::max(ncells / 16, 1 << 17);
+    int near = 0, far = 0;
     for (int s = 0; s < kSamples; ++s) {
         const int64_t i = (int64_t)s * (nedges - 1) / kSamples;
-        for (int k = 0; k < 2; ++k)
-            far += abs(e2c[2 * i + k] - e2c[2 * i + 2 + k]) > ncells / 16;
+        for (int k = 0; k < 2; ++k) {
+            const int32_t d = abs(e2c[2 * i + k] - e2c[2 * i + 2 + k]);
+            near += d <= 1024;
+            far += d > wide;
+        }
     }
-    return far > kSamples;
+    if (near > kSamples) return kFours;
+    return far > kSamples && ncells <= 1 << 30 ? kRounds : kLists;  // cells: see Quotient
 }
 
 // n / d by a multiplication: exact for n < 2^30 and 2^10 <= d <= 2^14 and for
@@ -300,6 +358,53 @@ bool make_rounds(int32_t ncells, int32_t nedges, const int32_t *e2c, Rounds *out
     return longest * (size_t)nbins <= 2 * out->entries;
 }
 
+// The tables of k_gather_fours. False for meshes of under two visits per cell,
+// whose entries would mostly hold nothing (16 bytes a cell; the lists 4, and 4
+// per visit).
+bool make_fours(int32_t ncells, int32_t nedges, const int32_t *e2c, std::vector<int32_t> *four,
+                std::vector<int32_t> *more) {
+    if (nedges < ncells) return false;
+    four->assign((size_t)ncells * 4, -1);
+    {
+        // No cell of more than four edges, as in quad meshes: one pass.
+        std::vector<uint8_t> at((size_t)ncells, 0);
+        int64_t j = 0;
+        for (; j < 2 * (int64_t)nedges; ++j) {
+            const size_t c = (size_t)e2c[j ^ 1];  // the second cell is incremented first
+            if (at[c] == 4) break;
+            (*four)[c * 4 + at[c]++] = (int32_t)(j / 2);
+        }
+        if (j == 2 * (int64_t)nedges) return true;
+        four->assign((size_t)ncells * 4, -1);
+    }
+    std::vector<int32_t> at((size_t)ncells, 0);
+    for (int64_t j = 0; j < 2 * (int64_t)nedges; ++j) ++at[(size_t)e2c[j]];
+    int64_t rest = 0;  // sum of (visits - 2) over cells of five or more: under 2^31
+    for (int32_t c = 0; c < ncells; ++c)
+        if (at[(size_t)c] > 4) {
+            (*four)[(size_t)c * 4 + 3] = (int32_t)(-2 - rest);
+            rest += at[(size_t)c] - 2;
+        }
+    more->resize((size_t)rest);
+    std::fill(at.begin(), at.end(), 0);
+    auto visit = [&](int32_t c, int32_t i) {
+        const int32_t k = at[(size_t)c]++;
+        int32_t *f = &(*four)[(size_t)c * 4];
+        if (k < 3 || f[3] == -1) {
+            f[k] = i;
+        } else {
+            int32_t *m = &(*more)[(size_t)(-2 - f[3])];
+            m[0] = k - 2;
+            m[k - 2] = i;
+        }
+    };
+    for (int32_t i = 0; i < nedges; ++i) {
+        visit(e2c[2 * (int64_t)i + 1], i);  // the second cell is incremented first
+        visit(e2c[2 * (int64_t)i], i);
+    }
+    return true;
+}
+
 // Device memory for the plan's tables, filled from the host.
 struct Part {
     const void *p;
@@ -348,11 +453,12 @@ pf_status pf_inc_plan_create(int32_t ncells, int32_t nedges, const int32_t *__re
     p->ncells = ncells;
     p->nedges = nedges;
     (void)hipGetDevice(&p->device);
-    // Lists are made as well where rounds find no memory, on either side.
+    // The next form is made where one finds no memory, on either side.
+    const inc::Form form = inc::form_of(ncells, nedges, edge_to_cells);
     inc::Rounds rounds;
     bool made = false;
     try {
-        made = inc::rounds_suit(ncells, nedges, edge_to_cells) && inc::make_rounds(ncells, nedges, edge_to_cells, &rounds);
+        made = form == inc::kRounds && inc::make_rounds(ncells, nedges, edge_to_cells, &rounds);
     } catch (const std::bad_alloc &) {
     }
     if (made) {
@@ -370,6 +476,24 @@ pf_status pf_inc_plan_create(int32_t ncells, int32_t nedges, const int32_t *__re
         (void)hipGetLastError();
         rounds = inc::Rounds();
     }
+    std::vector<int32_t> four, more;
+    made = false;
+    try {
+        made = form == inc::kFours && inc::make_fours(ncells, nedges, edge_to_cells, &four, &more);
+    } catch (const std::bad_alloc &) {
+    }
+    if (made) {
+        const size_t b4 = four.size() * sizeof(int32_t), bm = more.size() * sizeof(int32_t);
+        const inc::Part parts[] = {{four.data(), b4}, {more.data(), bm}};
+        if (inc::upload(p, parts, 2) == hipSuccess) {
+            p->four = (const inc::i4 *)p->dev;
+            p->more = (const int32_t *)((char *)p->dev + b4);
+            *plan = p;
+            return PF_OK;
+        }
+        (void)hipGetLastError();
+    }
+    four = more = std::vector<int32_t>();
     // Counting sort of the (edge, slot) visits by cell, in visit order.
     std::vector<int32_t> off((size_t)ncells + 1, 0);
     for (int64_t j = 0; j < 2 * (int64_t)nedges; ++j) ++off[(size_t)edge_to_cells[j] + 1];
@@ -406,8 +530,12 @@ pf_status pf_inc_plan_run(const pf_inc_plan *p, int32_t ncells, int32_t nedges, 
         const int grid = (p->nbins + inc::kWaves - 1) / inc::kWaves;
         hipLaunchKernelGGL(inc::k_rounds, dim3(grid), dim3(64 * inc::kWaves), 0, (hipStream_t)stream, p->first, p->base,
                            p->entry, edge, cell, ncells, p->per);
+    } else if (p->four) {
+        const int grid = (int)(((int64_t)ncells + inc::kThreads - 1) / inc::kThreads);
+        hipLaunchKernelGGL(inc::k_gather_fours, dim3(grid), dim3(inc::kThreads), 0, (hipStream_t)stream, p->four,
+                           p->more, edge, cell, ncells);
     } else {
-        const int grid = (int)((ncells + inc::kThreads - 1) / inc::kThreads);
+        const int grid = (int)(((int64_t)ncells + inc::kThreads - 1) / inc::kThreads);
         hipLaunchKernelGGL(inc::k_gather, dim3(grid), dim3(inc::kThreads), 0, (hipStream_t)stream, p->off, p->idx, edge,
                            cell, ncells);
     }

@@ -40,14 +40,33 @@ def test_plan_bitwise(ncells, nedges):
     plan.close()
 
 
+@pytest.mark.parametrize("ncells,nedges", [(300, 299), (300, 300), (1025, 2500), (64, 5000)])
+def test_plan_degrees_bitwise(ncells, nedges):
+    """Meshes on both sides of the line between lists and fours, with a cell
+    of every number of edges from 0 to 12 among the others, so that the first
+    four, the fourth place and the rest behind it all occur."""
+    dev = device()
+    e2c, edge, cell = _random_mesh(ncells + nedges, ncells, nedges)
+    e2c = np.where(e2c < 13, 13 + e2c, e2c)      # cells 0..12 only as set here
+    e2c[np.arange(78), 1] = np.repeat(np.arange(13), np.arange(13))
+    edge[[2, 3]] = [np.inf, -0.0]
+    ref = oracle.edge_inc_f64(ncells, e2c, edge, cell)
+    plan = pf.IncPlan(ncells, e2c)
+    for _ in range(2):
+        got = plan.run(_t(edge, dev), _t(cell, dev)).cpu().numpy()
+        assert np.array_equal(got, ref, equal_nan=True)
+    plan.close()
+
+
 @pytest.mark.parametrize("kind,ncells,nedges", [
     ("random", 700001, 1400000), ("random", 4300000, 2700000), ("hub", 700001, 1400000), ("sparse", 700001, 5000000),
-    ("few", 1000, 1400000), ("ordered", 900000, 1400000)])
+    ("few", 1000, 1400000), ("ordered", 900000, 1400000), ("local", 900000, 1400000)])
 def test_large_plans_bitwise(kind, ncells, nedges):
     """Meshes above and around the sizes where a plan keeps its visits in
     rounds: a remainder of cells in the last bin, more cells than one sweep
     holds, a cell in very many edges, a bin visited a few times far apart,
-    few cells, and edges numbered along the cells."""
+    few cells, edges numbered along the cells, and edges shuffled among some
+    thousands of neighbours."""
     dev = device()
     e2c, edge, cell = _random_mesh(nedges, ncells, nedges)
     if kind == "hub":
@@ -56,6 +75,9 @@ def test_large_plans_bitwise(kind, ncells, nedges):
         e2c = np.maximum(e2c, 256)            # cells below 256 only as set here
         e2c[[7, 2500000, 4999999], 0] = 3
         e2c[4999998] = [255, 3]
+    elif kind == "local":
+        e2c[:, 0] = np.minimum(np.arange(nedges) * ncells // nedges + e2c[:, 0] % 20000, ncells - 1)
+        e2c[:, 1] = np.minimum(np.arange(nedges) * ncells // nedges + e2c[:, 1] % 20000, ncells - 1)
     elif kind == "ordered":
         e2c[:, 0] = np.arange(nedges) * ncells // nedges
         e2c[:, 1] = (e2c[:, 0] + 1) % ncells

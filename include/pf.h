@@ -446,12 +446,15 @@ pf_status pf_server_poll(pf_server *s, int64_t ticket, PF_OUTP(int32_t, done));
 /* Block until done or timeout (ns; < 0 waits forever): PF_ETIMEDOUT. */
 pf_status pf_server_wait(pf_server *s, int64_t ticket, int64_t timeout_ns);
 /* Copy the finished output (float[h*w]) to `out` (host if out_is_host,
- * else device) and release the request's arena bytes and ticket. */
+ * else device) and release the request's arena bytes and ticket. A copy to
+ * the device is queued on the null stream of the current device and may not
+ * have run when the call returns: work on a stream that does not synchronise
+ * with the null stream must be ordered against it by events. */
 pf_status pf_server_result(pf_server *s, int64_t ticket, int32_t h, int32_t w,
                            float *out, int32_t out_is_host);
 /* Copy a finished reduction's result (double[2] for PF_OP_SUM_F32,
- * int64_t[256] for PF_OP_HIST_U8; host if out_is_host, else device) and
- * release it. `op` must be the request's. */
+ * int64_t[256] for PF_OP_HIST_U8; host if out_is_host, else device, as
+ * pf_server_result) and release it. `op` must be the request's. */
 pf_status pf_server_result_reduce(pf_server *s, int64_t ticket, int32_t op, void *out, int32_t out_is_host);
 /* Release a finished request without copying its output. */
 pf_status pf_server_release(pf_server *s, int64_t ticket);

@@ -802,7 +802,8 @@ class Server:
         _check(load().pf_server_wait(self._s, ticket, -1 if timeout_s is None else int(timeout_s * 1e9)))
 
     def result(self, ticket: int, h: int, w: int, out=None):
-        """Copy the output to ``out`` (GPU tensor) or to a new numpy array."""
+        """Copy the output to ``out`` (GPU tensor, in the order of torch's current
+        stream) or to a new numpy array."""
         if out is None:
             a = np.empty((h, w), np.float32)
             _check(load().pf_server_result(self._s, ticket, h, w, _np_ptr(a), 1))
@@ -816,7 +817,15 @@ class Server:
                 return out
         torch = _torch()
         _dev_tensor(out, torch.float32, "out", (2,))
+        # The copy runs on the null stream, which torch's other streams do not
+        # synchronise with: it follows what the current stream has queued, and
+        # what is queued there next follows it.
+        null, cur = torch.cuda.default_stream(), torch.cuda.current_stream()
+        if cur != null:
+            null.wait_stream(cur)
         _check(load().pf_server_result(self._s, ticket, h, w, out.data_ptr(), 0))
+        if cur != null:
+            cur.wait_stream(null)
         self._inputs.pop(ticket, None)
         return out
 

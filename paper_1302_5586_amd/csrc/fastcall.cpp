@@ -297,12 +297,14 @@ PyObject *server_submit(PyObject *, PyObject *const *a, Py_ssize_t n) {
     });
 }
 
-// server_result(handle, ticket, h, w, out): the status.
+// server_result(handle, ticket, h, w, out): the status. The library copies on
+// the null stream: under another current stream the caller's Python code orders
+// the copy against it.
 PyObject *server_result(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return entry(n, 5, [&]() -> PyObject * {
         const at::Tensor *out = plain(a[4], at::kFloat, 2, 2);
         int32_t h, w;
-        if (!out || !small_int(a[2], &h) || !small_int(a[3], &w)) return not_handled();
+        if (!out || stream() || !small_int(a[2], &h) || !small_int(a[3], &w)) return not_handled();
         if (!PyLong_CheckExact(a[0]) || !PyLong_CheckExact(a[1])) return not_handled();
         void *srv = PyLong_AsVoidPtr(a[0]);
         const int64_t ticket = PyLong_AsLongLong(a[1]);

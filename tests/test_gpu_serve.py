@@ -287,3 +287,39 @@ def test_arena_bytes_wait_for_the_result_copy(late):
     torch.cuda.synchronize()
     for img, o in zip(imgs, outs):
         assert_close(o.cpu().numpy(), oracle.filter_sep_f32(img, g, g), tolerance_sep(img, g, g), "result copy")
+
+
+def test_result_follows_the_current_stream():
+    """A result taken under a side stream while the null stream is busy: work
+    queued on the side stream before it (a fill of the same tensor) is not
+    seen in it, work queued after it (a copy) sees it."""
+    dev = device()
+    import torch
+    h, w = 512, 768
+    rng = np.random.default_rng(78)
+    g = synth.gaussian_1d(2, 1.1)
+    imgs = [rng.random((h, w), dtype=np.float32) for _ in range(4)]
+    xs = [torch.from_numpy(a).to(dev) for a in imgs]
+    busy = torch.randn(4096, 4096, device=dev)
+    side = torch.cuda.Stream()
+    outs, copies = [torch.zeros(h, w, device=dev) for _ in imgs], []
+    torch.cuda.synchronize()
+    with pf.Server(1 << 26, n_streams=2, max_batch=4) as s:
+        for x, o in zip(xs, outs):
+            t = s.submit(x, 2, pf.KIND_SEP, np.concatenate([g, g]))
+            s.wait(t, timeout_s=60)
+            null = busy
+            for _ in range(4):
+                null = null @ busy * 1e-2
+            with torch.cuda.stream(side):
+                mine = busy
+                for _ in range(4):
+                    mine = mine @ busy * 1e-2
+                o.fill_(-1.0)
+                s.result(t, h, w, out=o)
+                copies.append(o.clone())
+    torch.cuda.synchronize()
+    for img, o, c in zip(imgs, outs, copies):
+        ref = oracle.filter_sep_f32(img, g, g)
+        for got in (o, c):
+            assert_close(got.cpu().numpy(), ref, tolerance_sep(img, g, g), "result under a side stream")

@@ -1,0 +1,86 @@
+"""Every tile shape that the FP32 launches choose, on images with tiles inside
+the image as well as ragged ones at its edges.
+
+The sizes select the shapes on 256 CUs: W is 6 tiles of 256 columns and a
+remainder, the heights give more or fewer tiles than the launch rules ask."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1302_5586_amd as pf
+import synth
+from gpu_util import U, device, gamma
+
+pytestmark = pytest.mark.gpu
+
+W = 1573
+
+
+def _t(a, dev):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+
+
+# 1317 rows: 2075 tiles of 64 x 16, 581 of 256 x 16, 1050 of 64 x 32. Above 1765
+# rows 777 tiles of 256 x 16; above 3941 rows 3100 tiles of 64 x 32.
+@pytest.mark.parametrize("h", [1317, 1765, 3941])
+@pytest.mark.parametrize("r", range(0, pf.PF_R_MAX + 1))
+def test_large_tiles(r, h):
+    """2D: 128 x 32 and 256 x 16 (r <= 2), 128 x 16 (r = 3), 64 x 32 above;
+    separable: 128 x 32 and 256 x 16 (r <= 3), 128 x 32 above, in exact mode
+    from r = 5 on 64 x 32 and 64 x 64. Exact mode bit for bit the oracle, both
+    modes bit for bit the strip kernel."""
+    dev = device()
+    rng = np.random.default_rng(7000 + 10 * r + h)
+    img = rng.standard_normal((h, W)).astype(np.float32)
+    img.flat[rng.integers(0, img.size)] = np.inf
+    x = _t(img, dev)
+    with np.errstate(invalid="ignore"):
+        if h < 3941:  # 2D shapes change with the first two heights only
+            f = rng.standard_normal((2 * r + 1, 2 * r + 1)).astype(np.float32)
+            fd = _t(f, dev)
+            for exact in (False, True):
+                got = pf.filter2d(x, fd, exact=exact).cpu().numpy()
+                strip = pf.filter_shaped(x, fd, r, pf.KIND_2D, pf.VAR_DIRECT, 32, 4, exact=exact).cpu().numpy()
+                assert np.array_equal(got, strip, equal_nan=True), "2d exact=%d" % exact
+            assert np.array_equal(got, oracle.filter2d_f32(img, f), equal_nan=True)
+        fx, fy = rng.standard_normal((2, 2 * r + 1)).astype(np.float32)
+        fxd, fyd, f2 = _t(fx, dev), _t(fy, dev), _t(np.concatenate([fx, fy]), dev)
+        for exact in (False, True):
+            got = pf.filter_sep(x, fxd, fyd, exact=exact).cpu().numpy()
+            strip = pf.filter_shaped(x, f2, r, pf.KIND_SEP, pf.VAR_SEPARABLE, 32, 4, exact=exact).cpu().numpy()
+            assert np.array_equal(got, strip, equal_nan=True), "sep exact=%d" % exact
+        assert np.array_equal(got, oracle.filter_sep_f32(img, fx, fy), equal_nan=True)
+
+
+@pytest.mark.parametrize("border", [pf.BORDER_ZERO, pf.BORDER_REFLECT, pf.BORDER_MIRROR])
+@pytest.mark.parametrize("r,h", [(1, 1317), (2, 1765), (3, 1317), (8, 1317)])
+def test_large_tiles_under_border_rules(r, h, border):
+    dev = device()
+    rng = np.random.default_rng(7500 + r + border)
+    img = rng.standard_normal((h, W)).astype(np.float32)
+    f = rng.standard_normal((2 * r + 1, 2 * r + 1)).astype(np.float32)
+    got = pf.filter2d_border(_t(img, dev), _t(f, dev), border, exact=True).cpu().numpy()
+    assert np.array_equal(got, oracle.filter2d_f32_border(img, f, border))
+
+
+# 533 columns: 245 rows are 272 tiles of 32 x 16 and 144 of 64 x 16, 899 rows
+# 513 of 64 x 16. Neither has rows enough for streams.
+@pytest.mark.parametrize("border", [pf.BORDER_CLAMP, pf.BORDER_ZERO, pf.BORDER_REFLECT, pf.BORDER_MIRROR])
+@pytest.mark.parametrize("r,passes", [(0, 3), (1, 16), (2, 3), (3, 5), (4, 2), (4, 4), (5, 3), (8, 2)])
+def test_chain_tile_forms(r, passes, border):
+    """Chains on tiles of 64 x 16 and of 64 x 32: exact mode bit for bit the
+    oracle at every pass; the default mode within the relative error that one
+    pass may have (gpu_util), once per pass, on non-negative data."""
+    dev = device()
+    rng = np.random.default_rng(7700 + 100 * r + 10 * passes + border)
+    f = synth.gaussian_2d(r, 1.3)
+    rel = 1e-5 if r <= 4 else 2 * gamma((2 * r + 1) ** 2) + U
+    for h in (245, 899):
+        img = rng.random((h, 533), dtype=np.float32)
+        x, fd = _t(img, dev), _t(f, dev)
+        ref = oracle.filter_chain_f32(img, f, passes, border)
+        got = pf.filter_chain(x, fd, passes, border, exact=True).cpu().numpy()
+        assert np.array_equal(got, ref), h
+        fma = pf.filter_chain(x, fd, passes, border).cpu().numpy().astype(np.float64)
+        assert np.all(np.abs(fma - ref) <= passes * rel * (1 + 1e-3) * np.abs(ref) + 1e-30), h

@@ -261,6 +261,23 @@ def _dev_tensor(t, dtype, name, ndim=None):
     return t
 
 
+def _room(t, nbytes: int, name: str):
+    """Require a GPU tensor whose elements, in memory it owns, reach ``nbytes``."""
+    if not t.is_cuda:
+        raise ValueError("%s must be on the GPU (got %s)" % (name, t.device))
+    size = t.element_size()
+    if min(t.numel() * size, t.untyped_storage().nbytes() - t.storage_offset() * size) < nbytes:
+        raise ValueError("%s must hold %d bytes" % (name, nbytes))
+
+
+def _reduce_buffers(out, nbytes: int, workspace):
+    """The result and workspace of a reduction; returns the workspace's bytes."""
+    _room(out, nbytes, "out")
+    wb = workspace.numel() * workspace.element_size()
+    _room(workspace, wb, "workspace")
+    return wb
+
+
 def _radius_of(n: int, what: str) -> int:
     if n % 2 != 1:
         raise ValueError("%s must have odd size 2r+1 (got %d)" % (what, n))
@@ -283,6 +300,7 @@ def filter2d(x, f, *, exact: bool = False, out=None, stream=None):
     if out is None:
         out = torch.empty_like(x)
     _dev_tensor(out, torch.float32, "out", (2,))
+    _room(out, 4 * h * w, "out")
     _check(load().pf_filter2d_f32(h, w, r, x.data_ptr(), f.data_ptr(), out.data_ptr(),
                                   FLAG_EXACT if exact else 0, _stream_ptr(stream)))
     return out
@@ -304,6 +322,7 @@ def filter2d_border(x, f, border: int, *, exact: bool = False, out=None, stream=
     if out is None:
         out = torch.empty_like(x)
     _dev_tensor(out, torch.float32, "out", (2,))
+    _room(out, 4 * h * w, "out")
     _check(load().pf_filter2d_f32_border(h, w, r, border, x.data_ptr(), f.data_ptr(), out.data_ptr(),
                                          FLAG_EXACT if exact else 0, _stream_ptr(stream)))
     return out
@@ -325,6 +344,7 @@ def filter_chain(x, f, passes: int, border: int = 0, *, exact: bool = False, out
     if out is None:
         out = torch.empty_like(x)
     _dev_tensor(out, torch.float32, "out", (2,))
+    _room(out, 4 * h * w, "out")
     _check(load().pf_filter_chain_f32(h, w, r, passes, border, x.data_ptr(), f.data_ptr(), out.data_ptr(),
                                       FLAG_EXACT if exact else 0, _stream_ptr(stream)))
     return out
@@ -352,8 +372,8 @@ def sum_f32(x, *, out=None, workspace=None, stream=None):
         out = torch.empty(2, dtype=torch.float64, device=x.device)
     if workspace is None:
         workspace = _workspace(load().pf_sum_workspace, n, x.device)
-    _check(load().pf_sum_f32(n, x.data_ptr(), out.data_ptr(), workspace.data_ptr(),
-                             workspace.numel() * workspace.element_size(), _stream_ptr(stream)))
+    wb = _reduce_buffers(out, 16, workspace)
+    _check(load().pf_sum_f32(n, x.data_ptr(), out.data_ptr(), workspace.data_ptr(), wb, _stream_ptr(stream)))
     return out
 
 
@@ -371,6 +391,7 @@ def sum_f32_noalloc(x, *, out=None, stream=None):
         raise ValueError("x must be a contiguous CUDA float32 tensor")
     if out is None:
         out = torch.empty(2, dtype=torch.float64, device=x.device)
+    _room(out, 16, "out")
     _check(load().pf_sum_f32_noalloc(x.numel(), x.data_ptr(), out.data_ptr(), _stream_ptr(stream)))
     return out
 
@@ -416,8 +437,8 @@ def hist256_u8(x, *, out=None, workspace=None, stream=None):
     if workspace is None:
         # One sub-histogram per CU and 32 KiB of data (see pf_hist256_u8).
         workspace = _workspace(load().pf_hist_workspace, n, x.device, 1024 * min(n // 32768 + 1, 256))
-    _check(load().pf_hist256_u8(n, x.data_ptr(), out.data_ptr(), workspace.data_ptr(),
-                                workspace.numel() * workspace.element_size(), _stream_ptr(stream)))
+    wb = _reduce_buffers(out, 2048, workspace)
+    _check(load().pf_hist256_u8(n, x.data_ptr(), out.data_ptr(), workspace.data_ptr(), wb, _stream_ptr(stream)))
     return out
 
 
@@ -489,6 +510,7 @@ def filter_sep(x, fx, fy, *, exact: bool = False, out=None, stream=None):
     if out is None:
         out = torch.empty_like(x)
     _dev_tensor(out, torch.float32, "out", (2,))
+    _room(out, 4 * h * w, "out")
     _check(load().pf_filter_sep_f32(h, w, r, x.data_ptr(), fx.data_ptr(), fy.data_ptr(), out.data_ptr(),
                                     FLAG_EXACT if exact else 0, _stream_ptr(stream)))
     return out
@@ -511,6 +533,7 @@ def filter2d_u8(x, f, shift: int = 6, *, out=None, stream=None):
     if out is None:
         out = torch.empty_like(x)
     _dev_tensor(out, torch.uint8, "out", (2, 3))
+    _room(out, c * h * w, "out")
     _check(load().pf_filter2d_u8(c, h, w, r, int(shift), x.data_ptr(), f.data_ptr(), out.data_ptr(), 0,
                                  _stream_ptr(stream)))
     return out
@@ -530,6 +553,7 @@ def filter_shaped(x, filt, r: int, kind: int, variant: int, rows_per_wave: int, 
     h, w = x.shape
     if out is None:
         out = torch.empty_like(x)
+    _room(out, 4 * h * w, "out")
     _check(load().pf_filter_f32_shaped(h, w, r, kind, variant, rows_per_wave, waves_per_group, x.data_ptr(),
                                        filt.data_ptr(), out.data_ptr(), FLAG_EXACT if exact else 0,
                                        _stream_ptr(stream)))
@@ -582,6 +606,7 @@ def autotune_batch(h, w, r, kind, pix_off, filt_off, x, filt, out, reps: int = 1
     _dev_tensor(x, torch.float32, "x")
     _dev_tensor(filt, torch.float32, "filt")
     _dev_tensor(out, torch.float32, "out")
+    _room(out, 4 * x.numel(), "out")
     hh, ww, rr, kk = _i32(h), _i32(w), _i32(r), _i32(kind)
     po, fo = _i64(pix_off), _i64(filt_off)
     _check(load().pf_batch_autotune(hh.size, _np_ptr(hh), _np_ptr(ww), _np_ptr(rr), _np_ptr(kk), _np_ptr(po),
@@ -756,6 +781,8 @@ class Server:
                 self._inputs[t] = x
                 return t
         f = np.ascontiguousarray(filt, dtype=np.float32).ravel()
+        if 0 <= r <= PF_R_MAX and f.size < ((2 * r + 1) ** 2 if kind == KIND_2D else 2 * (2 * r + 1)):
+            raise ValueError("filter has %d weights, too few for the kind at radius %d" % (f.size, r))
         t = _I64()
         if isinstance(x, np.ndarray):
             a = np.ascontiguousarray(x, dtype=np.float32)
@@ -817,6 +844,7 @@ class Server:
                 return out
         torch = _torch()
         _dev_tensor(out, torch.float32, "out", (2,))
+        _room(out, 4 * h * w, "out")
         # The copy runs on the null stream, which torch's other streams do not
         # synchronise with: it follows what the current stream has queued, and
         # what is queued there next follows it.

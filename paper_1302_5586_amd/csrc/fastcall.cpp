@@ -58,6 +58,20 @@ const at::Tensor *plain(PyObject *o, at::ScalarType type, int64_t lo, int64_t hi
     return &t;
 }
 
+// Whether t's elements, in memory it owns, reach `bytes` on the GPU.
+bool room(const at::Tensor &t, int64_t bytes) {
+    if (!t.defined() || !t.is_cuda()) return false;
+    const int64_t size = t.element_size();
+    return t.numel() * size >= bytes && (int64_t)t.storage().nbytes() - t.storage_offset() * size >= bytes;
+}
+
+// `out`: none given, or a plain tensor with as many elements as x.
+bool out_for(PyObject *out, const at::Tensor &x, int64_t lo, int64_t hi) {
+    if (out == Py_None) return true;
+    const at::Tensor *t = plain(out, x.scalar_type(), lo, hi);
+    return t && room(*t, x.numel() * x.element_size());
+}
+
 bool small_int(PyObject *o, int32_t *v) {
     if (!PyLong_CheckExact(o)) return false;
     int over = 0;
@@ -122,7 +136,7 @@ PyObject *filter2d(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const at::Tensor *x = plain(a[0], at::kFloat, 2, 2), *f = plain(a[1], at::kFloat, 2, 2);
         int32_t h, w;
         if (!x || !square_filter(f) || !image_sizes(*x, &h, &w)) return not_handled();
-        if (a[3] != Py_None && !plain(a[3], at::kFloat, 2, 2)) return not_handled();
+        if (!out_for(a[3], *x, 2, 2)) return not_handled();
         const int exact = PyObject_IsTrue(a[2]);
         if (exact < 0) return nullptr;
         return run(
@@ -141,7 +155,7 @@ PyObject *bordered(PyObject *px, PyObject *pf, PyObject *ppasses, PyObject *pbor
     int32_t h, w, passes = 0, border;
     if (!x || !square_filter(f) || !image_sizes(*x, &h, &w)) return not_handled();
     if ((ppasses && !small_int(ppasses, &passes)) || !small_int(pborder, &border)) return not_handled();
-    if (out != Py_None && !plain(out, at::kFloat, 2, 2)) return not_handled();
+    if (!out_for(out, *x, 2, 2)) return not_handled();
     const int exact = PyObject_IsTrue(pexact);
     if (exact < 0) return nullptr;
     return run(
@@ -174,7 +188,7 @@ PyObject *filter_sep(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (!x || !fx || !fy || !image_sizes(*x, &h, &w)) return not_handled();
         const int64_t k = fx->numel();
         if (k != fy->numel() || k % 2 != 1 || k >= 1024) return not_handled();
-        if (a[4] != Py_None && !plain(a[4], at::kFloat, 2, 2)) return not_handled();
+        if (!out_for(a[4], *x, 2, 2)) return not_handled();
         const int exact = PyObject_IsTrue(a[3]);
         if (exact < 0) return nullptr;
         return run(
@@ -193,7 +207,7 @@ PyObject *filter2d_u8(PyObject *, PyObject *const *a, Py_ssize_t n) {
         int32_t h, w, shift;
         if (!x || !square_filter(f) || !image_sizes(*x, &h, &w) || !small_int(a[2], &shift)) return not_handled();
         const int64_t c = x->dim() == 3 ? x->size(0) : 1;
-        if (c > INT32_MAX || (a[3] != Py_None && !plain(a[3], at::kByte, 2, 3))) return not_handled();
+        if (c > INT32_MAX || !out_for(a[3], *x, 2, 3)) return not_handled();
         return run(
             a[3], [&] { return at::empty_like(*x); },
             [&](const at::Tensor &y) {
@@ -209,13 +223,20 @@ at::Tensor workspace_for(PyObject *given, size_t bytes, const at::Tensor &x) {
     return at::empty({std::max<int64_t>((int64_t)(bytes + 7) / 8, 1)}, x.options().dtype(at::kDouble));
 }
 
-bool any_tensor(PyObject *o) { return o == Py_None || THPVariable_CheckExact(o); }
+// A reduction's result (`bytes` of it) or, for bytes < 0, its workspace: none
+// given, or a tensor of any type with that room.
+bool buffer(PyObject *o, int64_t bytes) {
+    if (o == Py_None) return true;
+    if (!THPVariable_CheckExact(o)) return false;
+    const at::Tensor &t = THPVariable_Unpack(o);
+    return t.defined() && room(t, bytes >= 0 ? bytes : t.numel() * (int64_t)t.element_size());
+}
 
 // sum_f32(x, out, workspace)
 PyObject *sum_f32(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return entry(n, 3, [&]() -> PyObject * {
         const at::Tensor *x = plain(a[0], at::kFloat, 0, 64);
-        if (!x || !any_tensor(a[1]) || !any_tensor(a[2])) return not_handled();
+        if (!x || !buffer(a[1], 2 * sizeof(double)) || !buffer(a[2], -1)) return not_handled();
         size_t need = 0;
         if (f_sum_ws(x->numel(), &need) != PF_OK) return not_handled();
         return run(
@@ -232,7 +253,7 @@ PyObject *sum_f32(PyObject *, PyObject *const *a, Py_ssize_t n) {
 PyObject *sum_f32_noalloc(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return entry(n, 2, [&]() -> PyObject * {
         const at::Tensor *x = plain(a[0], at::kFloat, 0, 64);
-        if (!x || !any_tensor(a[1])) return not_handled();
+        if (!x || !buffer(a[1], 2 * sizeof(double))) return not_handled();
         return run(
             a[1], [&] { return at::empty({2}, x->options().dtype(at::kDouble)); },
             [&](const at::Tensor &y) {
@@ -245,7 +266,7 @@ PyObject *sum_f32_noalloc(PyObject *, PyObject *const *a, Py_ssize_t n) {
 PyObject *hist256_u8(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return entry(n, 3, [&]() -> PyObject * {
         const at::Tensor *x = plain(a[0], at::kByte, 0, 64);
-        if (!x || !any_tensor(a[1]) || !any_tensor(a[2])) return not_handled();
+        if (!x || !buffer(a[1], 256 * sizeof(int64_t)) || !buffer(a[2], -1)) return not_handled();
         size_t need = 0;
         if (f_hist_ws(x->numel(), &need) != PF_OK) return not_handled();
         // One sub-histogram per CU and 32 KiB of data (see pf_hist256_u8).
@@ -280,7 +301,10 @@ PyObject *server_submit(PyObject *, PyObject *const *a, Py_ssize_t n) {
             return not_handled();
         }
         PyObject *res = nullptr;
-        if (b.itemsize == 4 && b.format && b.format[0] == 'f' && !b.format[1]) {
+        // Too few weights for the kind and radius: the Python code says so.
+        const int64_t k = 2 * (int64_t)r + 1, weights = kind == PF_KIND_2D ? k * k : 2 * k;
+        if (b.itemsize == 4 && b.format && b.format[0] == 'f' && !b.format[1] &&
+            (r < 0 || r > PF_R_MAX || b.len >= 4 * weights)) {
             int64_t ticket = 0;
             pf_status st;
             {
@@ -305,6 +329,7 @@ PyObject *server_result(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const at::Tensor *out = plain(a[4], at::kFloat, 2, 2);
         int32_t h, w;
         if (!out || stream() || !small_int(a[2], &h) || !small_int(a[3], &w)) return not_handled();
+        if (!room(*out, 4 * (int64_t)h * w)) return not_handled();
         if (!PyLong_CheckExact(a[0]) || !PyLong_CheckExact(a[1])) return not_handled();
         void *srv = PyLong_AsVoidPtr(a[0]);
         const int64_t ticket = PyLong_AsLongLong(a[1]);

@@ -94,3 +94,65 @@ def test_same_results_and_errors_as_the_python_path():
                 call(x, f, u, w, s)
     with pytest.raises(RuntimeError):  # a tensor without storage: the Python path reports it
         torch.vmap(lambda t: pf.filter2d(t, f))(torch.zeros((2, 8, 8), device=dev))
+
+
+@pytest.mark.gpu
+def test_refuses_tensors_that_are_too_small():
+    """Outputs, workspaces and filters that would be written or read past
+    their end are refused on both paths before anything is launched; an output
+    of another shape with enough room is taken."""
+    from gpu_util import device
+    dev = device()
+    _fast()
+    x = torch.rand((8, 12), device=dev)
+    u = torch.randint(0, 256, (2, 8, 12), device=dev, dtype=torch.uint8)
+    f, w = torch.rand((3, 3), device=dev), torch.ones((3, 3), device=dev, dtype=torch.int8)
+    f1, e = f[0].contiguous(), torch.empty
+    f64 = {"dtype": torch.float64, "device": dev}
+    small, small8 = e((8, 11), device=dev), e((2, 8, 11), device=dev, dtype=torch.uint8)
+    one = e(1, **f64)
+    calls = [
+        lambda s: pf.filter2d(x, f, out=small, stream=s),
+        lambda s: pf.filter2d_border(x, f, pf.BORDER_ZERO, out=small, stream=s),
+        lambda s: pf.filter_chain(x, f, 2, out=small, stream=s),
+        lambda s: pf.filter_sep(x, f1, f1, out=small, stream=s),
+        lambda s: pf.filter2d_u8(u, w, out=small8, stream=s),
+        lambda s: pf.filter2d_u8(u, w, out=small8[0], stream=s),
+        lambda s: pf.filter_shaped(x, f.ravel(), 1, pf.KIND_2D, pf.VAR_DIRECT, 16, 4, out=small, stream=s),
+        lambda s: pf.filter_shaped(x, f.ravel(), 1, pf.KIND_2D, pf.VAR_DIRECT, 16, 4, out=e((8, 12)), stream=s),
+        lambda s: pf.sum_f32(x, out=one, stream=s),
+        lambda s: pf.sum_f32(x, out=one.expand(2), stream=s),
+        lambda s: pf.sum_f32(x, out=e(2, dtype=torch.float64), stream=s),
+        lambda s: pf.sum_f32(x, workspace=one.expand(4), stream=s),
+        lambda s: pf.sum_f32(x, workspace=e(4, dtype=torch.float64), stream=s),
+        lambda s: pf.sum_f32_noalloc(x, out=one, stream=s),
+        lambda s: pf.hist256_u8(u, out=e(255, device=dev, dtype=torch.int64), stream=s),
+        lambda s: pf.hist256_u8(u, workspace=one.expand(512), stream=s),
+    ]
+    for i, call in enumerate(calls):
+        for s in (None, torch.cuda.current_stream()):
+            with pytest.raises(ValueError):
+                call(s)
+                pytest.fail("call %d was taken" % i)
+    room = e((12, 9), device=dev)
+    for s in (None, torch.cuda.current_stream()):
+        assert pf.filter2d(x, f, out=room, stream=s) is room
+        assert torch.equal(room.view(-1)[:96].view(8, 12), pf.filter2d(x, f, stream=s))
+    with pf.Server(1 << 20) as srv:
+        taps = np.ones(6, np.float32)
+        for s in (None, torch.cuda.current_stream()):
+            for kind, short in ((pf.KIND_SEP, taps[:5]), (pf.KIND_2D, taps), (pf.KIND_SEP, taps[:0])):
+                with pytest.raises(ValueError):
+                    srv.submit(x, 1, kind, short, stream=s)
+        with pytest.raises(ValueError):
+            srv.submit(x.cpu().numpy(), 2, pf.KIND_SEP, taps)
+        with pytest.raises(pf.PFInvalid):  # the library's own check comes first where there is no size to ask for
+            srv.submit(x, 9, pf.KIND_SEP, taps)
+        t = srv.submit(x, 1, pf.KIND_SEP, taps)
+        srv.wait(t, timeout_s=30)
+        with pytest.raises(ValueError):
+            srv.result(t, 8, 12, out=small)
+        with torch.cuda.stream(torch.cuda.Stream()), pytest.raises(ValueError):
+            srv.result(t, 8, 12, out=small)
+        assert torch.equal(srv.result(t, 8, 12, out=e((8, 12), device=dev)), pf.filter_sep(x, torch.ones(3, device=dev),
+                                                                                          torch.ones(3, device=dev)))

@@ -44,8 +44,8 @@ DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-pa
 # batch-kernel group is its own object so that they build in parallel.
 VARIANTS = {
     "f32_inst.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(9)],
-    "chain.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(9)],
-    "tile.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(9)],
+    "chain.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(1, 9)],
+    "tile.hip": [("r%d" % r, ["-DPF_R=%d" % r]) for r in range(1, 9)],
     "batch_inst.hip": [("e%dm%d" % (e, m), ["-DPF_EXACT=%d" % e, "-DPF_VMASK=%d" % m]) for m in (1, 2, 3) for e in (0, 1)],
 }
 

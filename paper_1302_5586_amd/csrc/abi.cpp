@@ -133,7 +133,7 @@ pf_status pf_filter2d_f32(int32_t h, int32_t w, int32_t r, const float *in, cons
     if (st) return st;
     if ((st = check_f32_bufs(h, w, in, out))) return st;
     const pf_tune_entry e = tune_lookup(PF_KIND_2D, r, (int64_t)h * w);
-    return run_f32(h, w, r, PF_KIND_2D, PF_VAR_DIRECT, tile_fits(h, w) ? 0 : e.rows_per_wave, e.waves_per_group, in, filt,
+    return run_f32(h, w, r, PF_KIND_2D, PF_VAR_DIRECT, tile_fits(r, h, w) ? 0 : e.rows_per_wave, e.waves_per_group, in, filt,
                    nullptr, out, flags, stream);
 }
 
@@ -256,7 +256,7 @@ pf_status pf_filter_sep_f32(int32_t h, int32_t w, int32_t r, const float *in, co
     // always runs the separable form.
     const bool exact = (flags & PF_FLAG_EXACT) != 0;
     const int var = (!exact && e.variant == PF_VAR_SEP_DIRECT) ? PF_VAR_SEP_DIRECT : PF_VAR_SEPARABLE;
-    const int by = var == PF_VAR_SEPARABLE && tile_fits(h, w) ? 0 : e.rows_per_wave;
+    const int by = var == PF_VAR_SEPARABLE && tile_fits(r, h, w) ? 0 : e.rows_per_wave;
     return run_f32(h, w, r, PF_KIND_SEP, var, by, e.waves_per_group, in, fx, fy, out, flags, stream);
 }
 

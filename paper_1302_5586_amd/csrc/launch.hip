@@ -23,7 +23,7 @@ hipError_t launch_f32(int r, int var, bool exact, const float *in, const float *
 hipError_t launch_tile(int r, bool sep, bool exact, const float *in, const float *fa, const float *fb, float *out,
                        int h, int w, int border, hipStream_t s) {
     switch (r) {
-        case 0: return launch_tile_radius<0>(sep, exact, in, fa, fb, out, h, w, border, s);
+        case 0: return launch_point(exact, in, fa, sep ? fb : nullptr, out, (int64_t)h * w, 1, s);
         case 1: return launch_tile_radius<1>(sep, exact, in, fa, fb, out, h, w, border, s);
         case 2: return launch_tile_radius<2>(sep, exact, in, fa, fb, out, h, w, border, s);
         case 3: return launch_tile_radius<3>(sep, exact, in, fa, fb, out, h, w, border, s);
@@ -38,11 +38,11 @@ hipError_t launch_tile(int r, bool sep, bool exact, const float *in, const float
 
 hipError_t launch_chain(int r, bool exact, const float *in, const float *filt, float *out, int h, int w, int passes,
                         int border, hipStream_t s) {
+    if (r == 0) return launch_point(exact, in, filt, nullptr, out, (int64_t)h * w, passes, s);
     // One pass has nothing to fuse: the tile kernel (4096 x 4096 reflect, R =
     // 1: 25 us, the chain's own tiles 29 us).
-    if (passes == 1 && tile_fits(h, w)) return launch_tile(r, false, exact, in, filt, nullptr, out, h, w, border, s);
+    if (passes == 1 && tile_fits(r, h, w)) return launch_tile(r, false, exact, in, filt, nullptr, out, h, w, border, s);
     switch (r) {
-        case 0: return launch_chain_radius<0>(exact, in, filt, out, h, w, passes, border, s);
         case 1: return launch_chain_radius<1>(exact, in, filt, out, h, w, passes, border, s);
         case 2: return launch_chain_radius<2>(exact, in, filt, out, h, w, passes, border, s);
         case 3: return launch_chain_radius<3>(exact, in, filt, out, h, w, passes, border, s);

@@ -230,15 +230,19 @@ void clear_error();
 // Launchers (kernels.hip). All validate nothing: callers have already.
 // Single-image calls on LDS tiles (tile.hip): fa: 2D taps (sep false) or
 // fx; fb: fy (ignored for 2D taps); border: PF_BORDER_* (2D; the separable
-// kernel clamps). tile_fits: the grid stays within the
-// 2^32 work items a launch dimension holds (images of a few columns and
-// hundreds of millions of rows do not; the strip kernel takes those).
+// kernel clamps); radius 0 goes to launch_point. tile_fits: the grid stays
+// within the 2^32 work items a launch dimension holds (images of a few columns
+// and hundreds of millions of rows do not; the strip kernel takes those).
 constexpr int kTileThreads = 256;
-inline bool tile_fits(int h, int w) {
-    return ((int64_t)w + 63) / 64 * (((int64_t)h + 15) / 16) * kTileThreads < ((int64_t)1 << 32);
+inline bool tile_fits(int r, int h, int w) {
+    return r == 0 || ((int64_t)w + 63) / 64 * (((int64_t)h + 15) / 16) * kTileThreads < ((int64_t)1 << 32);
 }
 hipError_t launch_tile(int r, bool sep, bool exact, const float *in, const float *fa, const float *fb, float *out,
                        int h, int w, int border, hipStream_t s);
+// Radius 0 (point.hip): n pixels, `passes` passes with the weight *fa, then one
+// with *fb unless it is null.
+hipError_t launch_point(bool exact, const float *in, const float *fa, const float *fb, float *out, int64_t n,
+                        int passes, hipStream_t s);
 // The strip kernel with an explicit shape. fa: 2D taps (PF_VAR_DIRECT) or fx; fb: fy (ignored for PF_VAR_DIRECT).
 hipError_t launch_f32(int r, int var, bool exact, const float *in, const float *fa, const float *fb, float *out,
                       int h, int w, int by, int wpg, hipStream_t s);
@@ -302,18 +306,20 @@ hipError_t launch_tile_radius(bool sep, bool exact, const float *in, const float
 template <int R>
 hipError_t launch_chain_radius(bool exact, const float *in, const float *filt, float *out, int h, int w, int passes,
                                int border, hipStream_t s);
+#define PF_DECL_STRIP(R)                                                                                   \
+    template <>                                                                                            \
+    hipError_t launch_f32_radius<R>(int var, bool exact, const float *in, const float *fa, const float *fb, \
+                                    float *out, int h, int w, int by, int wpg, hipStream_t s);
 #define PF_DECL_RADIUS(R)                                                                                  \
+    PF_DECL_STRIP(R)                                                                                       \
     template <>                                                                                            \
     hipError_t launch_tile_radius<R>(bool sep, bool exact, const float *in, const float *fa,               \
                                      const float *fb, float *out, int h, int w, int border,                \
                                      hipStream_t s);                                                       \
     template <>                                                                                            \
     hipError_t launch_chain_radius<R>(bool exact, const float *in, const float *filt, float *out, int h,    \
-                                      int w, int passes, int border, hipStream_t s);                       \
-    template <>                                                                                            \
-    hipError_t launch_f32_radius<R>(int var, bool exact, const float *in, const float *fa, const float *fb, \
-                                    float *out, int h, int w, int by, int wpg, hipStream_t s);
-PF_DECL_RADIUS(0)
+                                      int w, int passes, int border, hipStream_t s);
+PF_DECL_STRIP(0)
 PF_DECL_RADIUS(1)
 PF_DECL_RADIUS(2)
 PF_DECL_RADIUS(3)
@@ -323,6 +329,7 @@ PF_DECL_RADIUS(6)
 PF_DECL_RADIUS(7)
 PF_DECL_RADIUS(8)
 #undef PF_DECL_RADIUS
+#undef PF_DECL_STRIP
 
 // Batch kernels per (exact, variant set), each in its own unit; the shape is
 // an index into kBatchShapes. Sets: bit v for variant v: 1 (direct only), 2

@@ -84,3 +84,32 @@ def test_chain_tile_forms(r, passes, border):
         assert np.array_equal(got, ref), h
         fma = pf.filter_chain(x, fd, passes, border).cpu().numpy().astype(np.float64)
         assert np.all(np.abs(fma - ref) <= passes * rel * (1 + 1e-3) * np.abs(ref) + 1e-30), h
+
+
+@pytest.mark.parametrize("h,w", [(1, 1), (1, 3), (2, 2), (1, 4099), (5, 3277), (16385, 1), (1027, 1029)])
+def test_radius_0(h, w):
+    """Radius 0, where a pixel meets one weight per pass: ends of vectors and
+    of workgroups, rows off 16-byte alignment, every border rule. The oracle's
+    values in both modes: with nothing to add, a fused multiply-add rounds once
+    as the multiplication does."""
+    dev = device()
+    import torch
+    rng = np.random.default_rng(7900 + h)
+    img = rng.standard_normal((h, w)).astype(np.float32)
+    img.flat[0] = np.inf
+    f, g = np.array([[-1.7]], np.float32), np.array([[0.3]], np.float32)
+    buf = torch.zeros(h * w + 1, device=dev)
+    x = buf[1:].view(h, w)
+    x.copy_(_t(img, dev))
+    fd, gd = _t(f, dev), _t(g, dev)
+    for exact in (False, True):
+        out = torch.full((h * w + 2,), 7.0, device=dev)
+        pf.filter2d(x, fd, exact=exact, out=out[1:-1].view(h, w))
+        got = out.cpu().numpy()
+        assert np.array_equal(got[1:-1].reshape(h, w), oracle.filter2d_f32(img, f)) and got[0] == got[-1] == 7.0
+        assert np.array_equal(pf.filter_sep(x, fd[0], gd[0], exact=exact).cpu().numpy(),
+                              oracle.filter_sep_f32(img, f[0], g[0]))
+        for border in (pf.BORDER_CLAMP, pf.BORDER_ZERO, pf.BORDER_REFLECT, pf.BORDER_MIRROR):
+            for passes in (1, 5, 40):
+                assert np.array_equal(pf.filter_chain(x, gd, passes, border, exact=exact).cpu().numpy(),
+                                      oracle.filter_chain_f32(img, g, passes, border))

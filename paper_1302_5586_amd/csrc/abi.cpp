@@ -77,6 +77,24 @@ static pf_status check_f32_bufs(int32_t h, int32_t w, const float *in, const flo
     return PF_OK;
 }
 
+// Images of more than eight 64-column tiles per CU and so few rows that a tile
+// is mostly padding: the strip kernel, which has none below the image, is ahead
+// of every tile shape (10^6 columns, us, strip / best tile: R = 1, 4 rows 6.3 /
+// 9.3, 8 rows 10.8 / 12.5; R = 3, 12 rows 27.1 / 28.4; separable R = 3, 8 rows
+// 10.8 / 14.7, 12 rows 17.5 / 17.9; R = 4, 16 rows 23.0 / 27.5; R = 6, 8 rows
+// 32.0 / 30.2). Not 2D at R >= 4 (R = 4, 1 row 47.7 / 46.9; 8 rows 73.4 / 47.2).
+static bool strip_wins(int32_t kind, int32_t r, int32_t h, int32_t w) {
+    if (r == 0) return false;
+    const int rows = kind == PF_KIND_2D ? (r <= 2 ? 8 : (r == 3 ? 12 : 0)) : (r <= 3 ? 12 : (r == 4 ? 16 : 8));
+    return h <= rows && ((int64_t)w + 63) / 64 > 8 * (int64_t)dev_info().cus;
+}
+
+// rows_per_wave of a call without a forced shape: the table's for the strip
+// kernel, 0 for the tile kernel.
+static int rows_for(int32_t kind, int32_t r, int32_t h, int32_t w, const pf_tune_entry &e) {
+    return tile_fits(r, h, w) && !strip_wins(kind, r, h, w) ? 0 : e.rows_per_wave;
+}
+
 // fa: 2D taps or fx; fb: fy (separable kinds only). by > 0: the strip kernel
 // with that shape; by == 0: the tile kernel, which chooses its own (direct
 // and separable variants).
@@ -133,7 +151,7 @@ pf_status pf_filter2d_f32(int32_t h, int32_t w, int32_t r, const float *in, cons
     if (st) return st;
     if ((st = check_f32_bufs(h, w, in, out))) return st;
     const pf_tune_entry e = tune_lookup(PF_KIND_2D, r, (int64_t)h * w);
-    return run_f32(h, w, r, PF_KIND_2D, PF_VAR_DIRECT, tile_fits(r, h, w) ? 0 : e.rows_per_wave, e.waves_per_group, in, filt,
+    return run_f32(h, w, r, PF_KIND_2D, PF_VAR_DIRECT, rows_for(PF_KIND_2D, r, h, w, e), e.waves_per_group, in, filt,
                    nullptr, out, flags, stream);
 }
 
@@ -256,7 +274,7 @@ pf_status pf_filter_sep_f32(int32_t h, int32_t w, int32_t r, const float *in, co
     // always runs the separable form.
     const bool exact = (flags & PF_FLAG_EXACT) != 0;
     const int var = (!exact && e.variant == PF_VAR_SEP_DIRECT) ? PF_VAR_SEP_DIRECT : PF_VAR_SEPARABLE;
-    const int by = var == PF_VAR_SEPARABLE && tile_fits(r, h, w) ? 0 : e.rows_per_wave;
+    const int by = var == PF_VAR_SEPARABLE ? rows_for(PF_KIND_SEP, r, h, w, e) : e.rows_per_wave;
     return run_f32(h, w, r, PF_KIND_SEP, var, by, e.waves_per_group, in, fx, fy, out, flags, stream);
 }
 

@@ -17,7 +17,8 @@
 // R = 6 84 -> 20.5; 4096 x 4096 R = 1 27.6 -> 25.4, R = 2 28.2 -> 26.0, R = 6
 // 202 -> 86; separable 4096 x 4096 R = 2 27.6 -> 25.0, R = 6 56 -> 31; partly
 // from the last-level cache (three images reused) 4096 x 4096 R = 2 22.9 ->
-// 22.0. The strip won at no size from 64 x 64 to 8192 x 8192.
+// 22.0. The strip won at no size from 64 x 64 to 8192 x 8192; it does on large
+// images of a few rows (strip_wins in abi.cpp).
 #include "tile_body.h"
 
 #ifndef PF_R
@@ -79,22 +80,37 @@ hipError_t launch_shape(const float *in, const float *fa, const float *fb, float
 //    idle at the end: 64 x 32 up to 12 tiles per CU (1800 x 2500, R = 5: C
 //    11.0, 128 x 32 12.2), then 64 x 64 (2160 x 3840, R = 6: C 17.1, 64 x 32
 //    18.0; 4096 x 4096, R = 8: H 39.4 against 49.6).
+// Images thinner than that tile waste it on padding (us, three images reused;
+// the tile the rule above names, then the one taken):
+//  * Up to 16 rows at R >= 4: 64 x 16 (16 x 10^6: 2D R = 4 81 and 49, R = 6 157
+//    and 88; separable R = 6 42 and 34). Up to a few rows the strip kernel is
+//    ahead of every tile at most radii; those calls do not come here.
+//  * Of columns, where a narrower tile has a quarter less of them: 64 x 32 up to
+//    64 and from 129 to 192 (400000 x 16: R = 1 71 and 28, separable R = 3 95
+//    and 34; 50000 x 130, separable R = 3 17.2 and 15.1), 128 x 32 up to 128 and
+//    from 257 to 384 (50000 x 100, R = 1: 13.9 and 9.9; 50000 x 300 23.0 and
+//    21.9).
 template <int R, bool EXACT, bool SEP>
 hipError_t launch(const float *in, const float *fa, const float *fb, float *out, int h, int w, int border,
                   hipStream_t s) {
     const int64_t cus = dev_info().cus;
     auto tiles = [&](int tw, int th) { return (int64_t)dev::cdiv(w, tw) * dev::cdiv(h, th); };
 #define PF_SHAPE(CX, Q) return launch_shape<R, EXACT, SEP, CX, Q>(in, fa, fb, out, h, w, border, s)
-    if (tiles(64, 16) <= 8 * cus) PF_SHAPE(16, 1);
+    auto columns = [&](int tw) { return (int64_t)dev::cdiv(w, tw) * tw; };  // with the padding
+    auto quarter_less = [&](int tw) { return 4 * columns(tw) <= 3 * columns(2 * tw); };
+    if (tiles(64, 16) <= 8 * cus || (R >= 4 && h <= 16)) PF_SHAPE(16, 1);
     if constexpr (SEP && EXACT && R >= 5) {
         if (tiles(64, 32) > 12 * cus) PF_SHAPE(16, 4);
         PF_SHAPE(16, 2);
     } else if constexpr (R <= (SEP ? 3 : 2)) {
-        if (tiles(256, 16) >= 3 * cus) PF_SHAPE(64, 4);
+        if (quarter_less(64)) PF_SHAPE(16, 2);
+        if (tiles(256, 16) >= 3 * cus && !quarter_less(128)) PF_SHAPE(64, 4);
         PF_SHAPE(32, 4);
     } else if constexpr (SEP) {
+        if (quarter_less(64)) PF_SHAPE(16, 2);
         PF_SHAPE(32, 4);
     } else if constexpr (R <= 3) {
+        if (quarter_less(64)) PF_SHAPE(16, 2);
         PF_SHAPE(32, 2);
     } else {
         PF_SHAPE(16, 2);

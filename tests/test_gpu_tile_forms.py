@@ -113,3 +113,29 @@ def test_radius_0(h, w):
             for passes in (1, 5, 40):
                 assert np.array_equal(pf.filter_chain(x, gd, passes, border, exact=exact).cpu().numpy(),
                                       oracle.filter_chain_f32(img, g, passes, border))
+
+
+# More than 2048 tiles of 64 x 16 on 256 CUs, thinner than the tile of larger
+# images: rows on both sides of the lines to the strip kernel and to 64 x 16
+# tiles, columns on 64 x 32 and 128 x 32 tiles.
+@pytest.mark.parametrize("h,w", [(3, 131137), (9, 131137), (13, 131137), (16, 131137), (17, 131137), (32785, 5),
+                                 (16401, 130), (16401, 100), (7001, 300)])
+@pytest.mark.parametrize("r", range(1, pf.PF_R_MAX + 1))
+def test_thin_images(r, h, w):
+    dev = device()
+    rng = np.random.default_rng(8000 + 10 * r + h)
+    img = rng.standard_normal((h, w)).astype(np.float32)
+    f = rng.standard_normal((2 * r + 1, 2 * r + 1)).astype(np.float32)
+    fx, fy = rng.standard_normal((2, 2 * r + 1)).astype(np.float32)
+    x, fd, fxd, fyd, f2 = (_t(a, dev) for a in (img, f, fx, fy, np.concatenate([fx, fy])))
+    for exact in (False, True):
+        got, gots = pf.filter2d(x, fd, exact=exact), pf.filter_sep(x, fxd, fyd, exact=exact)
+        assert (got == pf.filter_shaped(x, fd, r, pf.KIND_2D, pf.VAR_DIRECT, 16, 2, exact=exact)).all()
+        assert (gots == pf.filter_shaped(x, f2, r, pf.KIND_SEP, pf.VAR_SEPARABLE, 16, 2, exact=exact)).all()
+    rows = slice(max(0, h // 2 - 8), h // 2 + 9)  # the oracle on a band and its halo, of the columns at both ends
+    for cols in (slice(0, 500), slice(max(0, w - 500), w)):
+        band = img[max(0, rows.start - r):rows.stop + r, max(0, cols.start - r):cols.stop + r]
+        at = (slice(min(rows.start, r), min(rows.start, r) + min(rows.stop, h) - rows.start),
+              slice(min(cols.start, r), min(cols.start, r) + min(cols.stop, w) - cols.start))
+        assert np.array_equal(got[rows, cols].cpu().numpy(), oracle.filter2d_f32(band, f)[at])
+        assert np.array_equal(gots[rows, cols].cpu().numpy(), oracle.filter_sep_f32(band, fx, fy)[at])

@@ -68,8 +68,12 @@ __global__ __launch_bounds__(kThreads) void k_batch(const BatchImg *__restrict__
 template <>
 void *batch_fn<PF_EXACT, PF_VMASK>(int shape) {
     constexpr bool kExact = PF_EXACT != 0;
-    return shape == 0 ? (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[0].w / 4, 1>
-                      : (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[1].w / 4, 5>;
+    switch (shape) {
+        case 0: return (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[0].w / 4, 1>;
+        case 1: return (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[1].w / 4, 2>;
+        case 2: return (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[2].w / 4, 1>;
+        default: return (void *)tile::k_batch<kExact, PF_VMASK, kBatchShapes[3].w / 4, 5>;
+    }
 }
 
 }  // namespace pf

@@ -122,17 +122,29 @@ constexpr bool tile_inside(int r, int tw, int th, int x0, int y0, int h, int w) 
 // a tile at the image's edge: the nearest inside the row (w >= 4).
 constexpr int tile_load_col(int c, int x0, int w) { return clamp_int(c, -x0, w - 4 - x0); }
 
-// Tiles of a batch launch, columns x rows: 64 x 16 while all of the batch's
-// fit on the chip at once (8 workgroups of 4 waves on each of 256 CUs), since
-// the time is then one tile's; 256 x 20 beyond. us for 512, 128, 48 and 16
-// separable images (24600, 6300, 2200 and 630 tiles of 256 x 16), windows of
-// 512 tiles: 256 x 20 247, 65.9, 23.5, 8.8; 256 x 16 255, 66.2, 23.3, 9.0;
-// 256 x 24 243, 66.0, 23.2, 9.7; with windows of 2048 256 x 32 257, 69.8,
-// 25.2, 10.5; 128 x 16 284, 75.7, 22.9, 8.8; 64 x 32 312, 82, 24.7, 8.4.
+// Tiles of a batch launch, columns x rows.
+//  * 64 x 16 while all of the batch's fit on the chip at once (8 workgroups of
+//    4 waves on each of 256 CUs), since the time is then one tile's.
+//  * 64 x 32 where there are at most 1.8 of them to one of 256 x 20: in images of
+//    up to some 200 columns a wide tile is mostly padding, and a tile of 64 x 32
+//    takes about half its time even so. us, separable, radius 1, 256 x 20 / 64 x
+//    32: 4096 images of 64 x 64 (0.5 to one) 59 / 25, 2000 of 100 x 100 (1.6)
+//    40.5 / 36.2, 3000 of 70 x 300 (1.9) 86.5 / 90; sizes log-uniform 16..96 (0.8)
+//    41 / 22, 32..512 (1.7) 81 / 67, 64..1024 (2.1) 124 / 148; 2D, radius 4: 64 x
+//    64 240 / 56, 32..512 158 / 115, 64..1024 188 / 190.
+//  * 256 x 4 for images of a few rows: where there are at most 2 of them to one of
+//    256 x 20 and 1.5 to one of 64 x 32 (a tile takes half the time of the former
+//    or less, 0.6 of the latter's).
+//  * 256 x 20 otherwise. us for 512, 128, 48 and 16 separable images (24600,
+//    6300, 2200 and 630 tiles of 256 x 16), windows of 512 tiles: 256 x 20 247,
+//    65.9, 23.5, 8.8; 256 x 16 255, 66.2, 23.3, 9.0; 256 x 24 243, 66.0, 23.2,
+//    9.7; with windows of 2048 256 x 32 257, 69.8, 25.2, 10.5; 128 x 16 284, 75.7,
+//    22.9, 8.8; 64 x 32 312, 82, 24.7, 8.4.
 struct BatchShape {
     int w, h;
 };
-constexpr BatchShape kBatchShapes[2] = {{64, 16}, {256, 20}};
+constexpr int kBatchShapeCount = 4;
+constexpr BatchShape kBatchShapes[kBatchShapeCount] = {{64, 16}, {64, 32}, {256, 4}, {256, 20}};
 constexpr int64_t kBatchSmallTiles = 8 * 256;
 
 // Tiles per window of the launch (window_tile): the images of a batch have few
@@ -169,10 +181,13 @@ inline int64_t batch_tiles(int h, int w, int shape) {
 // The shape for the images of a batch (h and w set), whose tiles_x and
 // tiles_y it fills; *tiles: how many there are.
 inline int batch_shape(std::vector<BatchImg> &imgs, int64_t *tiles) {
-    int64_t n[2] = {0, 0};
+    int64_t n[kBatchShapeCount] = {};
     for (const BatchImg &d : imgs)
-        for (int s = 0; s < 2; ++s) n[s] += batch_tiles(d.h, d.w, s);
-    const int shape = n[0] <= kBatchSmallTiles ? 0 : 1;
+        for (int s = 0; s < kBatchShapeCount; ++s) n[s] += batch_tiles(d.h, d.w, s);
+    int shape = 3;
+    if (n[0] <= kBatchSmallTiles) shape = 0;
+    else if (n[2] <= 2 * n[3] && 2 * n[2] <= 3 * n[1]) shape = 2;
+    else if (5 * n[1] <= 9 * n[3]) shape = 1;
     const BatchShape t = kBatchShapes[shape];
     for (BatchImg &d : imgs) {
         d.tiles_x = (int32_t)(((int64_t)d.w + t.w - 1) / t.w);

@@ -139,3 +139,52 @@ def test_thin_images(r, h, w):
               slice(min(cols.start, r), min(cols.start, r) + min(cols.stop, w) - cols.start))
         assert np.array_equal(got[rows, cols].cpu().numpy(), oracle.filter2d_f32(band, f)[at])
         assert np.array_equal(gots[rows, cols].cpu().numpy(), oracle.filter_sep_f32(band, fx, fy)[at])
+
+
+@pytest.mark.parametrize("rows", [159, 4])
+@pytest.mark.parametrize("kinds", ["2d", "sep", "both"])
+@pytest.mark.parametrize("exact", [False, True])
+def test_batches_of_small_images(kinds, exact, rows):
+    """More images than the chip takes at once, none of which fills a 256 x 20
+    tile: tiles of 64 x 32 for images of few columns, of 256 x 4 for images of
+    few rows, every radius, sizes at the tiles' edges and drawn. Every image
+    equals its single-image call bit for bit."""
+    dev = device()
+    import torch
+    rng = np.random.default_rng(8300)
+    if rows == 4:
+        sizes = [(1, 1), (2, 3), (3, 255), (4, 256), (4, 257), (5, 40), (1, 4001)]
+        sizes += [(int(h), int(w)) for h, w in zip(rng.integers(1, 6, 43), rng.integers(1, 1300, 43))]
+    else:
+        sizes = [(1, 1), (2, 3), (31, 63), (32, 64), (33, 65), (64, 64), (65, 128), (97, 130)]
+        sizes += [(int(h), int(w)) for h, w in rng.integers(1, rows + 1, (52, 2))]
+    imgs, filts, ks = [], [], []
+    for i, (h, w) in enumerate(sizes):
+        for r in range(pf.PF_BATCH_R_MAX + 1):
+            sep = kinds == "sep" or (kinds == "both" and (i + r) % 2)
+            imgs.append(rng.standard_normal((h, w)).astype(np.float32))
+            filts.append(rng.standard_normal(2 * (2 * r + 1) if sep else (2 * r + 1) ** 2).astype(np.float32))
+            ks.append(pf.KIND_SEP if sep else pf.KIND_2D)
+    pk = pf.pack_batch(imgs, filts, ks)
+    cover = lambda th, tw: int((-(-pk.h // th) * -(-pk.w // tw)).sum())
+    tiles = cover(4, 256) if rows == 4 else cover(32, 64)
+    assert cover(16, 64) > 2048
+    x, fl = _t(pk.pixels, dev), _t(pk.filters, dev)
+    out = torch.full_like(x, float("nan"))
+    plan = pf.BatchPlan(pk.h, pk.w, pk.r, pk.kind, pk.pix_off, pk.filt_off, x.numel(), fl.numel(), exact=exact)
+    assert plan.info()["tasks"] == tiles
+    assert pf.batch_plan_check(pk.h, pk.w, pk.r, pk.kind, pk.pix_off, pk.filt_off, x.numel(),
+                               fl.numel()) == {"tiles": tiles, "violations": 0}
+    plan.run(x, fl, out)
+    got = out.cpu().numpy()
+    used = np.zeros(x.numel(), bool)
+    for i, img in enumerate(imgs):
+        h, w, r = int(pk.h[i]), int(pk.w[i]), int(pk.r[i])
+        span = slice(pk.pix_off[i], pk.pix_off[i] + h * w)
+        used[span] = True
+        f, k = _t(filts[i], dev), 2 * r + 1
+        ref = (pf.filter2d(_t(img, dev), f.reshape(k, k), exact=exact) if ks[i] == pf.KIND_2D else
+               pf.filter_sep(_t(img, dev), f[:k].contiguous(), f[k:].contiguous(), exact=exact))
+        assert np.array_equal(got[span].reshape(h, w), ref.cpu().numpy()), (h, w, r, ks[i])
+    assert np.isnan(got[~used]).all()
+    plan.close()

@@ -19,8 +19,10 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <memory>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "dev_common.h"
@@ -261,6 +263,30 @@ struct Quotient {
     int32_t operator()(int32_t n) const { return (int32_t)((uint64_t)n * m >> 44); }
 };
 
+// f(0) .. f(threads - 1), one to a thread; what finds no thread runs here. False
+// where one of them found no memory.
+template <class F>
+bool shares(int threads, F f) {
+    std::atomic<bool> ok{true};
+    auto run = [&](int t) {
+        try {
+            f(t);
+        } catch (const std::bad_alloc &) {
+            ok = false;
+        }
+    };
+    std::vector<std::thread> pool;
+    int t = 1;
+    try {
+        for (; t < threads; ++t) pool.emplace_back(run, t);
+    } catch (const std::exception &) {
+    }
+    run(0);
+    for (; t < threads; ++t) run(t);
+    for (std::thread &th : pool) th.join();
+    return ok;
+}
+
 struct Rounds {
     int32_t nbins = 0, per = 0;
     std::vector<int32_t> first, base;
@@ -271,8 +297,14 @@ struct Rounds {
 // The visits of each bin in rounds of 64 (k_rounds). False where the rounds
 // would be more than a quarter padding, or the longest bin more than twice
 // the mean: a cell in many edges has a round for each of its visits.
+// By up to 8 threads: by one, a plan took longer to make than the lists (ms on
+// the host of an MI355X with 16 CPUs, lists / rounds by one / by 8: 860 x 860
+// quads 6.3 / 16.9 / 3.5, 1024 x 1024 12.1 / 23.7 / 4.7, 2048 x 2048 127 / 120 /
+// 31).
 bool make_rounds(int32_t ncells, int32_t nedges, const int32_t *e2c, Rounds *out) {
     const int64_t visits = 2 * (int64_t)nedges;
+    const int threads = (int)std::max<int64_t>(
+        1, std::min<int64_t>({8, (int64_t)std::thread::hardware_concurrency(), visits >> 18}));
     // Bins for one workgroup per CU, or for as many sweeps of 256 workgroups as
     // the cells need; at least 192 cells, since small bins leave no 64 visits
     // of different cells to choose from (17% padding at 192, over 25% at 128).
@@ -280,22 +312,42 @@ bool make_rounds(int32_t ncells, int32_t nedges, const int32_t *e2c, Rounds *out
     const int64_t sweeps = (ncells + kResident * kMaxCells - 1) / (kResident * kMaxCells);
     const int32_t per = (int32_t)std::max<int64_t>(192, (ncells + kResident * sweeps * 64 - 1) / (kResident * sweeps * 64) * 64);
     const int32_t nbins = (int32_t)((ncells + (int64_t)per - 1) / per);
-    // First by workgroup: few enough streams for the caches, in edge order.
+    // First by workgroup: few enough streams for the caches, in edge order. A
+    // thread takes a range of the edges; at: where its visits of a workgroup go.
     const int32_t block = per * kWaves, nblocks = (int32_t)((ncells + (int64_t)block - 1) / block);
     const Quotient by_block(block), by_per(per);
     struct Visit {
         int32_t edge, slot;
     };
-    std::vector<int64_t> at((size_t)nblocks + 1, 0);
-    for (int64_t j = 0; j < visits; ++j) ++at[(size_t)by_block(e2c[j]) + 1];
-    for (int32_t b = 0; b < nblocks; ++b) at[(size_t)b + 1] += at[b];
-    std::vector<int64_t> fill(at.begin(), at.end() - 1);
+    auto range = [&](int t) { return (int32_t)((int64_t)nedges * t / threads); };
+    std::vector<std::vector<int64_t>> at((size_t)threads);
+    std::vector<int64_t> start((size_t)nblocks + 1, 0);
     std::unique_ptr<Visit[]> list(new Visit[(size_t)visits]);
-    for (int32_t i = 0; i < nedges; ++i)
-        for (int k = 1; k >= 0; --k) {  // the second cell is incremented first
-            const int32_t c = e2c[2 * (int64_t)i + k], b = by_block(c);
-            list[(size_t)fill[(size_t)b]++] = {i, c - b * block};
+    if (!shares(threads, [&](int t) {
+            std::vector<int64_t> n((size_t)nblocks, 0);
+            for (int64_t j = 2 * (int64_t)range(t); j < 2 * (int64_t)range(t + 1); ++j) ++n[(size_t)by_block(e2c[j])];
+            at[(size_t)t] = std::move(n);
+        }))
+        return false;
+    int64_t total = 0;
+    for (int32_t b = 0; b < nblocks; ++b) {
+        start[(size_t)b] = total;
+        for (std::vector<int64_t> &n : at) {
+            const int64_t here = n[(size_t)b];
+            n[(size_t)b] = total;
+            total += here;
         }
+    }
+    start[(size_t)nblocks] = total;
+    shares(threads, [&](int t) {
+        int64_t *fill = at[(size_t)t].data();
+        for (int32_t i = range(t); i < range(t + 1); ++i)
+            for (int k = 1; k >= 0; --k) {  // the second cell is incremented first
+                const int32_t c = e2c[2 * (int64_t)i + k], b = by_block(c);
+                list[(size_t)fill[b]++] = {i, c - b * block};
+            }
+    });
+    // Then each workgroup's bins, the workgroups dealt to the threads.
     struct Round {
         int32_t base, count;
     };
@@ -304,58 +356,95 @@ bool make_rounds(int32_t ncells, int32_t nedges, const int32_t *e2c, Rounds *out
         std::vector<Round> round;
         std::vector<uint32_t> entry;
     };
+    struct Block {
+        std::vector<int32_t> groups, base;  // groups: of each bin
+        std::vector<uint32_t> entry;
+    };
     const size_t most = (size_t)(visits + visits / 4);
-    out->first.assign(1, 0);
-    out->entry.reset(new uint32_t[most]);
-    std::vector<Bin> bins(kWaves);
-    std::vector<int32_t> last((size_t)block);  // the cells' last rounds
-    size_t longest = 0;
-    for (int32_t w = 0; w < nblocks; ++w) {
-        for (Bin &q : bins) {
-            q.low = 0;
-            q.round.clear();
-            q.entry.clear();
-        }
-        std::fill(last.begin(), last.end(), -1);
-        const Visit *v = list.get() + at[(size_t)w], *const end = list.get() + at[(size_t)w + 1];
-        for (; v != end; ++v) {
-            const int32_t edge = v->edge, in = by_per(v->slot);
-            Bin &q = bins[(size_t)in];
-            const int32_t n = (int32_t)q.round.size();
-            Round *const rd = q.round.data();
-            auto closed = [&](int32_t r) { return rd[r].count == 64 || edge - rd[r].base >= kSpan; };
-            int32_t low = q.low;
-            while (low < n && closed(low)) ++low;
-            q.low = low;
-            int32_t r = std::max(low, last[(size_t)v->slot] + 1);
-            while (r < n && closed(r)) ++r;
-            last[(size_t)v->slot] = r;
-            if (r == n) {
-                if (r % kGroup == 0) {
-                    if (q.entry.size() >= most) return false;
-                    q.entry.resize(q.entry.size() + 64 * kGroup, (uint32_t)kMaxCells);
-                }
-                q.round.push_back({edge, 0});
+    std::vector<Block> blocks((size_t)nblocks);
+    // What all threads write lies apart from what they read for every visit
+    // (beside it: 7.6 ms instead of 1.9 at 860 x 860).
+    struct alignas(128) Shared {
+        std::atomic<int32_t> next{0};
+        std::atomic<size_t> entries{0};
+    } all;
+    const bool made = shares(threads, [&, by_per, per](int) {
+        std::vector<Bin> bins(kWaves);
+        std::vector<int32_t> last((size_t)block);  // the cells' last rounds
+        for (int32_t w; (w = all.next++) < nblocks;) {
+            size_t here = 0;
+            for (Bin &q : bins) {
+                q.low = 0;
+                q.round.clear();
+                q.entry.clear();
             }
-            Round &t = q.round[(size_t)r];
-            q.entry[((size_t)(r / kGroup) * 64 + (size_t)t.count++) * kGroup + r % kGroup] =
-                (uint32_t)(edge - t.base) << kSlotBits | (uint32_t)(v->slot - in * per);
+            std::fill(last.begin(), last.end(), -1);
+            const Visit *v = list.get() + start[(size_t)w], *const end = list.get() + start[(size_t)w + 1];
+            for (; v != end; ++v) {
+                const int32_t edge = v->edge, in = by_per(v->slot);
+                Bin &q = bins[(size_t)in];
+                const int32_t n = (int32_t)q.round.size();
+                Round *const rd = q.round.data();
+                auto closed = [&](int32_t r) { return rd[r].count == 64 || edge - rd[r].base >= kSpan; };
+                int32_t low = q.low;
+                while (low < n && closed(low)) ++low;
+                q.low = low;
+                int32_t r = std::max(low, last[(size_t)v->slot] + 1);
+                while (r < n && closed(r)) ++r;
+                last[(size_t)v->slot] = r;
+                if (r == n) {
+                    if (r % kGroup == 0) {
+                        here += 64 * kGroup;
+                        if (all.entries + here > most) {
+                            all.entries += here;
+                            return;
+                        }
+                        q.entry.resize(q.entry.size() + 64 * kGroup, (uint32_t)kMaxCells);
+                    }
+                    q.round.push_back({edge, 0});
+                }
+                Round &t = q.round[(size_t)r];
+                q.entry[((size_t)(r / kGroup) * 64 + (size_t)t.count++) * kGroup + r % kGroup] =
+                    (uint32_t)(edge - t.base) << kSlotBits | (uint32_t)(v->slot - in * per);
+            }
+            all.entries += here;
+            Block &o = blocks[(size_t)w];
+            o.entry.reserve(here);
+            for (int32_t k = 0; k < kWaves && w * kWaves + k < nbins; ++k) {
+                Bin &q = bins[(size_t)k];
+                o.entry.insert(o.entry.end(), q.entry.begin(), q.entry.end());
+                q.round.resize(q.entry.size() / 64, {0, 0});  // a round of padding reads edge 0
+                for (const Round &t : q.round) o.base.push_back(t.base);
+                o.groups.push_back((int32_t)(q.round.size() / kGroup));
+            }
         }
-        for (int32_t k = 0; k < kWaves && w * kWaves + k < nbins; ++k) {
-            Bin &q = bins[(size_t)k];
-            if (out->entries + q.entry.size() > most) return false;
-            if (!q.entry.empty())
-                memcpy(out->entry.get() + out->entries, q.entry.data(), q.entry.size() * sizeof(uint32_t));
-            out->entries += q.entry.size();
-            longest = std::max(longest, q.entry.size());
-            q.round.resize(q.entry.size() / 64, {0, 0});  // a round of padding reads edge 0
-            for (const Round &t : q.round) out->base.push_back(t.base);
-            out->first.push_back((int32_t)(out->base.size() / kGroup));
+    });
+    if (!made || all.entries > most) return false;
+    list.reset();
+    out->entries = all.entries;
+    out->entry.reset(new uint32_t[out->entries]);
+    out->first.assign(1, 0);
+    std::vector<size_t> to((size_t)nblocks, 0);
+    int32_t longest = 0;
+    for (int32_t w = 0; w < nblocks; ++w) {
+        const Block &o = blocks[(size_t)w];
+        to[(size_t)w] = (size_t)out->base.size() * 64;
+        out->base.insert(out->base.end(), o.base.begin(), o.base.end());
+        for (int32_t g : o.groups) {
+            out->first.push_back(out->first.back() + g);
+            longest = std::max(longest, g);
         }
     }
+    all.next = 0;
+    shares(threads, [&](int) {
+        for (int32_t w; (w = all.next++) < nblocks;) {
+            const Block &o = blocks[(size_t)w];
+            if (!o.entry.empty()) memcpy(out->entry.get() + to[(size_t)w], o.entry.data(), o.entry.size() * 4);
+        }
+    });
     out->nbins = nbins;
     out->per = per;
-    return longest * (size_t)nbins <= 2 * out->entries;
+    return (size_t)longest * 64 * kGroup * (size_t)nbins <= 2 * out->entries;
 }
 
 // The tables of k_gather_fours. False for meshes of under two visits per cell,

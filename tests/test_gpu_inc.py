@@ -139,3 +139,17 @@ def test_plan_rejects():
     with pytest.raises(pf.PFAlias):
         pf._check(pf.load().pf_inc_plan_run(plan._h, 3, 1, x.data_ptr(), x.data_ptr(), None))
     plan.close()
+
+
+def test_large_plans_made_at_once():
+    """Plans of large random meshes, each made by several threads, made from
+    four threads at the same time: every one gives the sequential loop's bits."""
+    from concurrent.futures import ThreadPoolExecutor
+    dev = device()
+    meshes = [_random_mesh(seed, 500000 + 70001 * seed, 1400000) for seed in range(4)]
+    ncells = [500000 + 70001 * seed for seed in range(4)]
+    with ThreadPoolExecutor(4) as pool:
+        plans = list(pool.map(lambda k: pf.IncPlan(ncells[k], meshes[k][0]), range(4)))
+    for n, (e2c, edge, cell), plan in zip(ncells, meshes, plans):
+        assert np.array_equal(plan.run(_t(edge, dev), _t(cell, dev)).cpu().numpy(), oracle.edge_inc_f64(n, e2c, edge, cell))
+        plan.close()

@@ -52,9 +52,8 @@ struct pf_inc_plan {
     void *dev = nullptr;  // all tables
     // Lists: offsets (ncells + 1), the cells' edges (2 * nedges).
     const int32_t *off = nullptr, *idx = nullptr;
-    // Fours: the cells' first edges, four to a cell, and the rest.
+    // Fours: the cells' edges, four to a cell.
     const pf::inc::i4 *four = nullptr;
-    const int32_t *more = nullptr;
     // Rounds (nbins > 0): the bins' first groups (nbins + 1); per group, the
     // edge base of each round and 64 entries of each.
     int32_t nbins = 0, per = 0;
@@ -88,17 +87,18 @@ __global__ __launch_bounds__(kThreads) void k_gather(const int32_t *__restrict__
     cell[c] = v;
 }
 
-// The same with each cell's first four edges in one 16-byte entry (-1: none),
-// the form of meshes whose cells have two or more edges on average: they and
-// the cell's value come in one round trip, their values in the next, where the
-// lists take three. A cell of more than four edges keeps three there and in
-// the fourth place -2 - k: more[k] further edges follow at more[k + 1]. Bound
-// by latency up to some 100,000 cells, then by the lines fetched for single
-// values. Lists -> fours, us: random quads 362 x 362 6.6 -> 5.8, 512 x 512
-// 10.5 -> 9.4, 724 x 724 25.0 -> 23.5; numbered row by row 1024 x 1024
-// 10.7 -> 9.0, 2048 x 2048 45 -> 39 (5.1 TB/s).
+// The same with each cell's edges in one 16-byte entry (-1: none), the form of
+// meshes whose cells have at most four and, on average, two or more, as in quad
+// meshes: they and the cell's value come in one round trip, their values in the
+// next, where the lists take three. Bound by latency up to some 100,000 cells,
+// then by the lines fetched for single values. Lists -> fours, us: random quads
+// 362 x 362 6.6 -> 5.8, 512 x 512 10.5 -> 9.4, 724 x 724 25.0 -> 23.5; numbered
+// row by row 1024 x 1024 10.7 -> 9.0, 2048 x 2048 45 -> 39 (5.1 TB/s). Cells of
+// more edges stay on lists: with three edges in the entry and the rest behind it
+// 300,000 cells took, random edges, 10.8 us at 1.5 edges to a cell (lists 9.9),
+// 13.7 (13.2) at 2, 20.9 (21.9) at 3, but their plans 2 to 3 times as long to
+// make (4.0 and 1.9 ms, 5.8 and 2.4, 7.7 and 3.1).
 __global__ __launch_bounds__(kThreads) void k_gather_fours(const i4 *__restrict__ four,
-                                                           const int32_t *__restrict__ more,
                                                            const double *__restrict__ edge, double *__restrict__ cell,
                                                            int32_t ncells) {
     const int64_t c = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
@@ -110,20 +110,6 @@ __global__ __launch_bounds__(kThreads) void k_gather_fours(const i4 *__restrict_
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         if (e[k] >= 0) v = v + x[k];
-    if (e[3] < -1) {
-        const int32_t *idx = more + (-2 - e[3]);
-        const int32_t n = *idx++;
-        int32_t k = 0;
-        for (; k + 4 <= n; k += 4) {
-            const int32_t i0 = idx[k], i1 = idx[k + 1], i2 = idx[k + 2], i3 = idx[k + 3];
-            const double e0 = edge[i0], e1 = edge[i1], e2 = edge[i2], e3 = edge[i3];
-            v = v + e0;
-            v = v + e1;
-            v = v + e2;
-            v = v + e3;
-        }
-        for (; k < n; ++k) v = v + edge[idx[k]];
-    }
     cell[c] = v;
 }
 
@@ -226,7 +212,7 @@ namespace inc {
 // random quads 724 x 724, 8 MiB 25.0 / 23.5 / 33; 860 x 860 42 / - / 29.
 // From there by how far apart the cells are that neighbouring edges name, in a
 // sample:
-//  * within 1024 cells for the most part: fours. The values of a gather are in
+//  * within 1024 cells for the most part: fours, or lists. The values of a gather are in
 //    the L2. 2048 x 2048 numbered row by row 45.1 / 39.3 / 49.9, its edges
 //    shuffled within 1024 58.1 / 56.5 / 60.7.
 //  * over a sixteenth of the mesh and 128 K cells (2 MiB of their edges) for
@@ -239,7 +225,7 @@ enum Form { kLists, kFours, kRounds };
 
 Form form_of(int32_t ncells, int32_t nedges, const int32_t *e2c) {
     if (nedges < (10 << 20) / 8) return kFours;
-    constexpr int kSamples = 4096;
+    constexpr int kSamples = 1024;
     const int32_t wide = std::max(ncells / 16, 1 << 17);
     int near = 0, far = 0;
     for (int s = 0; s < kSamples; ++s) {
@@ -447,50 +433,21 @@ bool make_rounds(int32_t ncells, int32_t nedges, const int32_t *e2c, Rounds *out
     return (size_t)longest * 64 * kGroup * (size_t)nbins <= 2 * out->entries;
 }
 
-// The tables of k_gather_fours. False for meshes of under two visits per cell,
-// whose entries would mostly hold nothing (16 bytes a cell; the lists 4, and 4
-// per visit).
-bool make_fours(int32_t ncells, int32_t nedges, const int32_t *e2c, std::vector<int32_t> *four,
-                std::vector<int32_t> *more) {
+// The table of k_gather_fours. False for meshes with a cell of more than four
+// visits, or of under two visits per cell, whose entries would mostly hold
+// nothing (16 bytes a cell; the lists 4, and 4 per visit).
+bool make_fours(int32_t ncells, int32_t nedges, const int32_t *e2c, std::unique_ptr<int32_t[]> *four) {
     if (nedges < ncells) return false;
-    four->assign((size_t)ncells * 4, -1);
-    {
-        // No cell of more than four edges, as in quad meshes: one pass.
-        std::vector<uint8_t> at((size_t)ncells, 0);
-        int64_t j = 0;
-        for (; j < 2 * (int64_t)nedges; ++j) {
-            const size_t c = (size_t)e2c[j ^ 1];  // the second cell is incremented first
-            if (at[c] == 4) break;
-            (*four)[c * 4 + at[c]++] = (int32_t)(j / 2);
-        }
-        if (j == 2 * (int64_t)nedges) return true;
-        four->assign((size_t)ncells * 4, -1);
+    four->reset(new int32_t[(size_t)ncells * 4]);
+    int32_t *const f = four->get();
+    std::vector<uint8_t> at((size_t)ncells, 0);
+    for (int64_t j = 0; j < 2 * (int64_t)nedges; ++j) {
+        const size_t c = (size_t)e2c[j ^ 1];  // the second cell is incremented first
+        if (at[c] == 4) return false;
+        f[c * 4 + at[c]++] = (int32_t)(j / 2);
     }
-    std::vector<int32_t> at((size_t)ncells, 0);
-    for (int64_t j = 0; j < 2 * (int64_t)nedges; ++j) ++at[(size_t)e2c[j]];
-    int64_t rest = 0;  // sum of (visits - 2) over cells of five or more: under 2^31
-    for (int32_t c = 0; c < ncells; ++c)
-        if (at[(size_t)c] > 4) {
-            (*four)[(size_t)c * 4 + 3] = (int32_t)(-2 - rest);
-            rest += at[(size_t)c] - 2;
-        }
-    more->resize((size_t)rest);
-    std::fill(at.begin(), at.end(), 0);
-    auto visit = [&](int32_t c, int32_t i) {
-        const int32_t k = at[(size_t)c]++;
-        int32_t *f = &(*four)[(size_t)c * 4];
-        if (k < 3 || f[3] == -1) {
-            f[k] = i;
-        } else {
-            int32_t *m = &(*more)[(size_t)(-2 - f[3])];
-            m[0] = k - 2;
-            m[k - 2] = i;
-        }
-    };
-    for (int32_t i = 0; i < nedges; ++i) {
-        visit(e2c[2 * (int64_t)i + 1], i);  // the second cell is incremented first
-        visit(e2c[2 * (int64_t)i], i);
-    }
+    for (size_t c = 0; c < (size_t)ncells; ++c)
+        for (size_t k = at[c]; k < 4; ++k) f[c * 4 + k] = -1;
     return true;
 }
 
@@ -565,24 +522,22 @@ pf_status pf_inc_plan_create(int32_t ncells, int32_t nedges, const int32_t *__re
         (void)hipGetLastError();
         rounds = inc::Rounds();
     }
-    std::vector<int32_t> four, more;
+    std::unique_ptr<int32_t[]> four;
     made = false;
     try {
-        made = form == inc::kFours && inc::make_fours(ncells, nedges, edge_to_cells, &four, &more);
+        made = form == inc::kFours && inc::make_fours(ncells, nedges, edge_to_cells, &four);
     } catch (const std::bad_alloc &) {
     }
     if (made) {
-        const size_t b4 = four.size() * sizeof(int32_t), bm = more.size() * sizeof(int32_t);
-        const inc::Part parts[] = {{four.data(), b4}, {more.data(), bm}};
-        if (inc::upload(p, parts, 2) == hipSuccess) {
+        const inc::Part part = {four.get(), (size_t)ncells * sizeof(inc::i4)};
+        if (inc::upload(p, &part, 1) == hipSuccess) {
             p->four = (const inc::i4 *)p->dev;
-            p->more = (const int32_t *)((char *)p->dev + b4);
             *plan = p;
             return PF_OK;
         }
         (void)hipGetLastError();
     }
-    four = more = std::vector<int32_t>();
+    four.reset();
     // Counting sort of the (edge, slot) visits by cell, in visit order.
     std::vector<int32_t> off((size_t)ncells + 1, 0);
     for (int64_t j = 0; j < 2 * (int64_t)nedges; ++j) ++off[(size_t)edge_to_cells[j] + 1];
@@ -622,7 +577,7 @@ pf_status pf_inc_plan_run(const pf_inc_plan *p, int32_t ncells, int32_t nedges, 
     } else if (p->four) {
         const int grid = (int)(((int64_t)ncells + inc::kThreads - 1) / inc::kThreads);
         hipLaunchKernelGGL(inc::k_gather_fours, dim3(grid), dim3(inc::kThreads), 0, (hipStream_t)stream, p->four,
-                           p->more, edge, cell, ncells);
+                           edge, cell, ncells);
     } else {
         const int grid = (int)(((int64_t)ncells + inc::kThreads - 1) / inc::kThreads);
         hipLaunchKernelGGL(inc::k_gather, dim3(grid), dim3(inc::kThreads), 0, (hipStream_t)stream, p->off, p->idx, edge,

@@ -153,3 +153,28 @@ def test_large_plans_made_at_once():
     for n, (e2c, edge, cell), plan in zip(ncells, meshes, plans):
         assert np.array_equal(plan.run(_t(edge, dev), _t(cell, dev)).cpu().numpy(), oracle.edge_inc_f64(n, e2c, edge, cell))
         plan.close()
+
+
+@pytest.mark.parametrize("ncells", [257, 40000])
+@pytest.mark.parametrize("fifth", [False, True])
+def test_plan_of_four_edges_to_a_cell(ncells, fifth):
+    """Every cell in at most four edges, some in fewer and some in none, with
+    self-loops and repeated edges, and the same mesh with one cell in a fifth."""
+    dev = device()
+    rng = np.random.default_rng(ncells)
+    ends = rng.permutation(np.repeat(np.arange(1, ncells), 4))[:2 * ncells + 2]
+    e2c = ends.reshape(-1, 2).astype(np.int32)
+    free = np.flatnonzero(np.bincount(ends, minlength=ncells) == 0)
+    e2c[5] = free[1]                # a self-loop
+    e2c[7] = e2c[9] = [free[2], free[3]]
+    if fifth:
+        full = np.flatnonzero(np.bincount(e2c.ravel(), minlength=ncells) == 4)[-1]
+        e2c = np.concatenate([e2c, [[full, free[4]]]]).astype(np.int32)
+    assert np.bincount(e2c.ravel(), minlength=ncells).max() == (5 if fifth else 4) and len(e2c) >= ncells
+    edge, cell = rng.standard_normal(len(e2c)), rng.standard_normal(ncells)
+    edge[[2, 3]] = [np.inf, -0.0]
+    ref = oracle.edge_inc_f64(ncells, e2c, edge, cell)
+    plan = pf.IncPlan(ncells, e2c)
+    for _ in range(2):
+        assert np.array_equal(plan.run(_t(edge, dev), _t(cell, dev)).cpu().numpy(), ref, equal_nan=True)
+    plan.close()

@@ -446,21 +446,38 @@ hipError_t launch_stream(const float *in, const float *filt, float *out, int h, 
     return hipGetLastError();
 }
 
-// Passes a stream is built for: its rings fit in registers (at most 160 of
-// them). At R = 4 the 81 taps no longer fit in scalar registers beside the
-// rest and the tiles are as fast.
-constexpr int stream_max(int r) { return r == 1 || r == 2 ? 8 : (r == 3 ? 5 : 0); }
+// Passes a stream is built for: its rings fit in registers (at most 192 of
+// them; 15 and 16 passes at R = 1 leave some to the accumulation registers). At
+// R = 4 the 81 taps no longer fit in scalar registers beside the rest and the
+// tiles are as fast.
+constexpr int stream_max(int r) { return r == 1 ? 16 : (r == 2 ? 8 : (r == 3 ? 5 : 0)); }
+
+// The least share of useful work at which a stream is ahead of the tiles. Both
+// repeat their halo, the tiles more of it the more passes there are; separate
+// multiplies and adds weigh more on a stream, which hides less behind them. us,
+// stream / tiles, by share: R = 2, 3 passes 0.39 19.8 / 15.9, 0.49 22.9 / 25.3;
+// R = 3, 4 passes 0.39 122 / 114, 0.52 86 / 109; exact R = 2, 5 passes 0.56 103 /
+// 89, 0.69 152 / 160; exact R = 3, 4 passes 0.52 160 / 132, 0.66 239 / 243;
+// R = 1, 12 passes 0.25 38 / 46, exact 50.0 / 50.3; 16 passes 0.34 218 / 196,
+// 0.46 114 / 184.
+inline double stream_share(int r, bool exact, int passes) {
+    constexpr double one[2][8] = {{0.31, 0.29, 0.25, 0.20, 0.20, 0.20, 0.42, 0.42},  // R = 1, from 9 passes
+                                   {0.38, 0.37, 0.34, 0.32, 0.30, 0.28, 0.45, 0.45}};
+    constexpr double two[2][9] = {{0, 0, 0.56, 0.47, 0.40, 0.34, 0.31, 0.29, 0.28},  // R = 2
+                                  {0, 0, 0.90, 0.80, 0.70, 0.62, 0.54, 0.47, 0.42}};
+    if (r == 1) return one[exact][passes - 9];
+    return two[exact][passes] * (r == 3 ? 1.2 : 1.0);
+}
 
 // The stream's plan, or false where the tiles are faster. Bands are as tall
 // as one wave per SIMD makes them (a second one per SIMD repeats 2H more halo
 // rows per band), but half that where the bands are still at least 8H tall
 // and a pixel costs 27 multiply-adds or more: two waves then hide each
 // other's waits (4096 x 4096, us, one / two: R = 1, 4 passes 34.0 / 30.1; 8
-// passes 58 / 65; 2 passes 23.9 / 26.3, HBM-bound). Least rows per band, from
-// streams / tiles (us): R = 1, 9 rows (1300 x 1800), 4 passes 12.5 / 14.8;
-// R = 2, 9 rows 26.7 / 24.8, 12 rows (1533 x 2047) 27.7 / 31.8; R = 3, 18 rows
-// (1800 x 2400), 3 passes 47.3 / 44.8, 24 rows (2160 x 2600) 47.9 / 52.6.
-inline bool stream_plan(int r, int passes, int h, int w, StreamPlan &pl) {
+// passes 58 / 65; 2 passes 23.9 / 26.3, HBM-bound). R = 1 up to 8 passes: from 8
+// rows per band (9 rows, 1300 x 1800, 4 passes 12.5 us, tiles 14.8 us). Else by
+// the share of the strips' columns and rows that are outputs of one strip alone.
+inline bool stream_plan(int r, bool exact, int passes, int h, int w, StreamPlan &pl) {
     if (passes < 2 || passes > stream_max(r)) return false;
     const int H = r * passes, IL = (H + 3) / 4, SW = 4 * (64 - 2 * IL);
     pl.xa = kFrameX, pl.ya = kFrameY;
@@ -469,7 +486,8 @@ inline bool stream_plan(int r, int passes, int h, int w, StreamPlan &pl) {
     const int simds = 4 * std::max(dev_info().cus, 1), rows = pl.yb - pl.ya;
     pl.strips = dev::cdiv(pl.xb - pl.xa, SW);
     pl.by = dev::cdiv(rows, std::max(1, simds / pl.strips));
-    if (pl.by < (r == 1 ? 8 : (r == 2 ? 10 : 20))) return false;
+    const double share = (double)(pl.xb - pl.xa) / (256.0 * pl.strips) * pl.by / (pl.by + 2.0 * H);
+    if (r == 1 && passes <= 8 ? pl.by < 8 : share < stream_share(r, exact, passes)) return false;
     if (pl.by >= 16 * H && passes * (2 * r + 1) * (2 * r + 1) >= 27)
         pl.by = dev::cdiv(rows, std::max(1, 2 * simds / pl.strips));
     pl.bands = dev::cdiv(rows, pl.by);
@@ -494,16 +512,21 @@ hipError_t launch_stream_passes(const float *in, const float *filt, float *out, 
 // Tiles of 64 x 32; of 64 x 16 while there are at most two per CU, where a
 // tile's latency is the launch's time (400 x 600, 8 x (5 x 5): 19.5 us against
 // 23.9 us); of 32 x 16 at one per CU at most (257 x 255: 16.8 us against
-// 19.4 us).
+// 19.4 us). A thread of a 64 x 32 tile takes two rows at a time, but one at R = 2
+// and 3 (3 to 6% faster) and at a halo of 16 there and at R = 1, where the spare
+// row in LDS costs the third workgroup per CU (R = 1, 16 passes over 4000 x 4000
+// 337 us against 376, R = 2, 8 passes over 2160 x 3840 137 against 164).
 template <int R, bool EXACT>
 hipError_t launch(const float *in, const float *filt, float *out, int h, int w, int passes, int border,
                   hipStream_t s) {
     StreamPlan pl;
-    if (stream_plan(R, passes, h, w, pl))
+    if (stream_plan(R, EXACT, passes, h, w, pl))
         return launch_stream_passes<R, EXACT>(in, filt, out, h, w, passes, border, pl, s);
     const int64_t cus = std::max(dev_info().cus, 1), rows16 = dev::cdiv(h, 16);
     if (dev::cdiv(w, 32) * rows16 <= cus) return launch_tiles<R, EXACT, 32, 16, 1>(in, filt, out, h, w, passes, border, s);
     if (dev::cdiv(w, 64) * rows16 <= 2 * cus) return launch_tiles<R, EXACT, 64, 16, 1>(in, filt, out, h, w, passes, border, s);
+    if constexpr (R <= 3)
+        if (R > 1 || passes == 16) return launch_tiles<R, EXACT, 64, 32, 1>(in, filt, out, h, w, passes, border, s);
     return launch_tiles<R, EXACT, 64, 32, 2>(in, filt, out, h, w, passes, border, s);
 }
 

@@ -188,3 +188,32 @@ def test_batches_of_small_images(kinds, exact, rows):
         assert np.array_equal(got[span].reshape(h, w), ref.cpu().numpy()), (h, w, r, ks[i])
     assert np.isnan(got[~used]).all()
     plan.close()
+
+
+# Rows per band that give the streams the share of useful work they ask for on
+# 256 CUs (two strips of columns, 512 bands, the last one short).
+@pytest.mark.parametrize("r,passes,by,border", [
+    (1, 9, 24, pf.BORDER_CLAMP), (1, 11, 24, pf.BORDER_ZERO), (1, 14, 30, pf.BORDER_REFLECT), (1, 15, 46, pf.BORDER_MIRROR),
+    (1, 16, 46, pf.BORDER_CLAMP), (2, 3, 80, pf.BORDER_MIRROR), (2, 5, 56, pf.BORDER_ZERO), (2, 8, 44, pf.BORDER_REFLECT),
+    (3, 2, 44, pf.BORDER_CLAMP), (3, 4, 400, pf.BORDER_REFLECT), (3, 5, 40, pf.BORDER_MIRROR)])
+def test_chain_streams_of_many_rows(r, passes, by, border):
+    """Bands of rows at the top, inside and at the bottom of a large image: exact
+    mode bit for bit the oracle, both modes bit for bit the chain of the band
+    alone, which runs on tiles."""
+    dev = device()
+    import torch
+    halo = r * passes
+    side = 4 * ((halo + 3) // 4)
+    h, w = 32 + 512 * by - 3 + halo, 64 + 2 * (256 - 2 * side) + side
+    x = torch.rand((h, w), generator=torch.Generator(device=dev).manual_seed(r * 100 + passes), device=dev)
+    f = synth.gaussian_2d(r, 1.1)
+    fd = _t(f, dev)
+    got = {exact: pf.filter_chain(x, fd, passes, border, exact=exact) for exact in (False, True)}
+    n = 130
+    for y0 in (0, h // 2 // by * by + 7, h - n):
+        lo, hi = y0 + (halo if y0 else 0), y0 + n - (halo if y0 + n < h else 0)  # rows the band alone determines
+        band = x[y0:y0 + n].contiguous()
+        ref = oracle.filter_chain_f32(band.cpu().numpy(), f, passes, border)
+        assert np.array_equal(got[True][lo:hi].cpu().numpy(), ref[lo - y0:hi - y0]), y0
+        for exact in (False, True):
+            assert torch.equal(got[exact][lo:hi], pf.filter_chain(band, fd, passes, border, exact=exact)[lo - y0:hi - y0]), y0

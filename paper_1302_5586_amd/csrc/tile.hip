@@ -28,36 +28,60 @@
 namespace pf {
 namespace tile {
 
+// Images of few rows and many columns: an XCD's contiguous share of a window's
+// tiles would be part of one row of them, whose neighbours above and below are
+// in other L2s. They are taken in panels of kPanel columns of tiles instead (64
+// to 400 rows of 16000 to 100000 columns, three images reused, us: 100 x 64000 R =
+// 1 11.4 -> 9.9, 200 x 32000 11.2 -> 9.8, separable R = 3 12.4 -> 10.0, 400 x
+// 16000 11.0 -> 10.2; 800 x 8000 unchanged, 3000 x 12000 would take 57 instead of
+// 53). Not in the 2D kernel at R >= 3, which is bound by arithmetic (unchanged
+// there, and 1 to 2% slower for the other images).
+constexpr int kPanel = 8, kPanelRows = 400;
+
+// This workgroup's tile; panel: tiles of a panel, or 0.
+template <bool PANELS>
+__device__ __forceinline__ void own_tile(int tiles_x, int panel, int window, int &tx, int &ty) {
+    window_tile(blockIdx.x, gridDim.x, tiles_x, window, tx, ty);
+    if (!PANELS || panel == 0) return;
+    const int t = ty * tiles_x + tx, first = t / panel * kPanel;
+    const int in = t - first / kPanel * panel, columns = min(kPanel, tiles_x - first);
+    ty = in / columns;
+    tx = first + in - ty * columns;
+}
+
 template <int R, bool EXACT, int CX, int Q>
 __global__ __launch_bounds__(kThreads) void k_tile_2d(const float *__restrict__ in, const float *__restrict__ filt,
-                                                      float *__restrict__ out, int h, int w, int tiles_x,
+                                                      float *__restrict__ out, int h, int w, int tiles_x, int panel,
                                                       int border) {
     __shared__ __align__(16) float buf[rows_of(R, CX, Q) * pitch_of(R, CX)];
     int tx, ty;
-    window_tile(blockIdx.x, gridDim.x, tiles_x, window_of(Q), tx, ty);
+    own_tile<R <= 2>(tiles_x, panel, window_of(Q), tx, ty);
     tile_2d<R, EXACT, CX, Q>(buf, in, filt, out, h, w, tx * 4 * CX, ty * (kThreads / CX) * Q, border);
 }
 
 template <int R, bool EXACT, int CX, int Q>
 __global__ __launch_bounds__(kThreads) void k_tile_sep(const float *__restrict__ in, const float *__restrict__ fx,
                                                        const float *__restrict__ fy, float *__restrict__ out, int h,
-                                                       int w, int tiles_x) {
+                                                       int w, int tiles_x, int panel) {
     __shared__ __align__(16) float buf[rows_of(R, CX, Q) * pitch_of(R, CX)];
     int tx, ty;
-    window_tile(blockIdx.x, gridDim.x, tiles_x, window_of(Q), tx, ty);
+    own_tile<true>(tiles_x, panel, window_of(Q), tx, ty);
     tile_sep<R, EXACT, CX, Q>(buf, in, fx, fy, out, h, w, tx * 4 * CX, ty * (kThreads / CX) * Q);
 }
 
 template <int R, bool EXACT, bool SEP, int CX, int Q>
 hipError_t launch_shape(const float *in, const float *fa, const float *fb, float *out, int h, int w, int border,
                         hipStream_t s) {
-    const int64_t tiles_x = dev::cdiv(w, 4 * CX), n = tiles_x * dev::cdiv(h, kThreads / CX * Q);
+    const int64_t tiles_x = dev::cdiv(w, 4 * CX), tiles_y = dev::cdiv(h, kThreads / CX * Q), n = tiles_x * tiles_y;
+    // Not the smallest shape, whose tiles are all in flight at once.
+    const bool panels = CX * Q > 16 && tiles_y > 1 && h <= kPanelRows && tiles_x >= 4 * kPanel;
+    const int panel = panels ? (int)tiles_y * kPanel : 0;
     if constexpr (SEP)
         hipLaunchKernelGGL((k_tile_sep<R, EXACT, CX, Q>), dim3((unsigned)n), dim3(kThreads), 0, s, in, fa, fb, out, h,
-                           w, (int)tiles_x);
+                           w, (int)tiles_x, panel);
     else
         hipLaunchKernelGGL((k_tile_2d<R, EXACT, CX, Q>), dim3((unsigned)n), dim3(kThreads), 0, s, in, fa, out, h, w,
-                           (int)tiles_x, border);
+                           (int)tiles_x, panel, border);
     return hipGetLastError();
 }
 

@@ -217,3 +217,20 @@ def test_chain_streams_of_many_rows(r, passes, by, border):
         assert np.array_equal(got[True][lo:hi].cpu().numpy(), ref[lo - y0:hi - y0]), y0
         for exact in (False, True):
             assert torch.equal(got[exact][lo:hi], pf.filter_chain(band, fd, passes, border, exact=exact)[lo - y0:hi - y0]), y0
+
+
+@pytest.mark.parametrize("h,w", [(40, 60001), (100, 33001), (395, 16129), (64, 40193)])
+@pytest.mark.parametrize("r", [1, 3, 4, 6])
+def test_wide_images(r, h, w):
+    """Images of few rows of tiles and many columns, whose tiles are taken in
+    panels, the last one ragged: every pixel equals the strip kernel's."""
+    dev = device()
+    import torch
+    g = torch.Generator(device=dev).manual_seed(8500 + r)
+    x = torch.randn((h, w), generator=g, device=dev)
+    f, k = torch.randn((2 * r + 1, 2 * r + 1), generator=g, device=dev), 2 * r + 1
+    for exact in (False, True):
+        assert torch.equal(pf.filter2d(x, f, exact=exact),
+                           pf.filter_shaped(x, f.ravel(), r, pf.KIND_2D, pf.VAR_DIRECT, 32, 4, exact=exact))
+        assert torch.equal(pf.filter_sep(x, f[0], f[1], exact=exact),
+                           pf.filter_shaped(x, f[:2].ravel(), r, pf.KIND_SEP, pf.VAR_SEPARABLE, 32, 4, exact=exact))

@@ -158,11 +158,24 @@ def build_fastcall(verbose: bool = False, incremental: bool = False) -> str:
     return FASTCALL
 
 
+def _try_fastcall(verbose: bool, incremental: bool) -> None:
+    """``build_fastcall`` where torch's headers and a compiler for them are
+    there. The library needs neither, and the binding's Python path serves
+    every call without it; one built from older sources is taken away."""
+    try:
+        build_fastcall(verbose, incremental)
+    except Exception as e:  # noqa: BLE001 - whatever keeps it from being built
+        if os.path.exists(FASTCALL):
+            os.remove(FASTCALL)
+        sys.stderr.write("the binding's short path is not built (%s): its Python path serves all calls\n" % e)
+
+
 def build(verbose: bool = False, jobs: int = 0, defines=(), out: str = LIB, incremental: bool = False) -> str:
     """Compile every source and link the shared library; returns its path.
     ``defines`` (e.g. ["-DPF_STRIP_ALIGNED=0"]) and ``out`` build a variant
-    of the library elsewhere, in its own object directory. ``incremental``
-    keeps objects newer than their source, every header and this script."""
+    of the library elsewhere, in its own object directory, and leave the
+    binding's short path as it is. ``incremental`` keeps objects newer than
+    their source, every header and this script."""
     objdir = OBJDIR if not defines else OBJDIR + "_" + "_".join(d.lstrip("-D").replace("=", "") for d in defines)
     os.makedirs(objdir, exist_ok=True)
     work = _jobs()
@@ -170,9 +183,9 @@ def build(verbose: bool = False, jobs: int = 0, defines=(), out: str = LIB, incr
     work.sort(key=lambda j: (not j[0].endswith(".hip"), -len(j[1])))
     jobs = jobs or min(os.cpu_count() or 8, 16, len(work))
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        fast = ex.submit(build_fastcall, verbose, incremental)
+        if out == LIB and not defines:
+            ex.submit(_try_fastcall, verbose, incremental)
         objs = list(ex.map(lambda j: _compile(j, verbose, objdir, defines, incremental), work))
-        fast.result()
     check_resources(objs, os.path.join(objdir, "resource_usage.txt"))
     tmp = out + ".tmp%d" % os.getpid()
     cmd = [HIPCC, *DEVICE, "-shared", "-fPIC", "-o", tmp, *objs, "-lpthread"]

@@ -16,7 +16,6 @@ struct pf_batch_plan {
     int32_t n = 0;
     int64_t npix = 0, nfilt = 0;
     int32_t flags = 0;
-    int device = -1;
     std::vector<int32_t> variant;  // per image
     int64_t ntasks = 0;
     int shape = 0;   // of the tiles (kBatchShapes)
@@ -158,7 +157,6 @@ pf_status pf_batch_plan_create(int32_t n, const int32_t *__restrict h, const int
     p->npix = npix;
     p->nfilt = nfilt;
     p->flags = flags;
-    (void)hipGetDevice(&p->device);
     p->variant = t.variant;
     p->ntasks = (int64_t)t.tasks.size();
     p->shape = t.shape;

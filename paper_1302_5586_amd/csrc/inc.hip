@@ -250,14 +250,14 @@ struct Quotient {
 };
 
 // f(0) .. f(threads - 1), one to a thread; what finds no thread runs here. False
-// where one of them found no memory.
+// where one of them threw (found no memory).
 template <class F>
 bool shares(int threads, F f) {
     std::atomic<bool> ok{true};
     auto run = [&](int t) {
         try {
             f(t);
-        } catch (const std::bad_alloc &) {
+        } catch (const std::exception &) {
             ok = false;
         }
     };

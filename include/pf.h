@@ -284,7 +284,8 @@ pf_status pf_filter_f32_shaped(int32_t h, int32_t w, int32_t r, int32_t kind, in
  * single-image calls of the direct and separable variants, batch plans and
  * servers run on LDS tiles whose size the library chooses by the image's or
  * the batch's; an FP32 entry's shape is that of the strip kernel, which runs
- * PF_VAR_SEP_DIRECT (and images of a few columns and over 2^28 rows).
+ * PF_VAR_SEP_DIRECT, large images of a few rows, and images of a few columns
+ * and over 2^28 rows.
  * PF_TUNE_BATCH entries are set, loaded and saved as before and select
  * nothing. */
 #define PF_TUNE_SINGLE 0

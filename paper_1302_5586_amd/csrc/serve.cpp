@@ -10,10 +10,10 @@
 // there: the batch kernel for the filter requests, then the
 // multi-array sum and histogram kernels. Completions are observed through
 // per-stream events, so new arrivals run while earlier batches are still on
-// the device. Each filter request's variant and tile shape come from the
-// tune table keyed by (kind, radius, pixels) only, and each reduction is
-// computed part by part with the same device code as the single-array
-// calls, so a result is the same whichever batch the request lands in.
+// the device. Each filter request's variant is its kind's, no bits depend on the
+// shape of a batch's tiles, and each reduction is computed part by part with the
+// same device code as the single-array calls, so a result is the same whichever
+// batch the request lands in.
 #include <string.h>
 #include <time.h>
 
